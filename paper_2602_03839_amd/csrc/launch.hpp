@@ -115,12 +115,12 @@ struct OuterListDesc {
 };
 
 struct OuterParams {
-  uint32_t nunits;
+  uint32_t ntiles;
   int ntensors;
   int nlists;
   float mu;
   float alpha;
-  uint32_t tile_begin[kMaxBatch + 1];  // first work unit of each tensor
+  uint32_t tile_begin[kMaxBatch + 1];
   OuterTensorDesc t[kMaxBatch];
   OuterListDesc l[kMaxLists];
 };
@@ -303,7 +303,8 @@ hipError_t launch_apply(const ApplyParams& p, hipStream_t stream);
 hipError_t launch_cast(const float* src, uint16_t* dst, uint64_t n, hipStream_t stream);
 // p[0 .. nwords) = 0 by a kernel (not a memset, so a captured graph replays it as a kernel)
 hipError_t launch_zero_words(uint64_t* p, uint64_t nwords, hipStream_t stream);
-uint64_t outer_unit_elems();
+uint64_t outer_tile_elems();
+uint64_t outer_max_tiles();  // of a launch
 // Largest capacity (entries, bytes or pairs) the index-stream kernels take.
 uint64_t stream_max_items();
 hipError_t launch_varint_encode(const VarintEncParams& p, hipStream_t stream);

@@ -7,17 +7,11 @@
 // with one FP32 rounding per operation.
 //
 // g is never materialised in HBM.  Each worker's list is sorted by index (the
-// sparsifier writes it in index order), so a block walks the lists alongside
-// its dense tiles: per tile it scatter-adds the entries that fall in the
-// tile into an LDS copy of g -- worker by worker, with a barrier between
-// workers, so every sum is formed in worker order -- and then streams theta and
-// m once, reading g from LDS.  HBM traffic: 8 bytes read and 8 written per
-// element, 8 per list entry.
-//
-// Work unit = kUnit consecutive elements of one tensor.  At the start of a
-// unit a wave finds, for its list, the first entry at or past the unit by a
-// 64-way search (each round one load per lane); after that the lists are
-// consumed in order, tile by tile.
+// sparsifier writes it in index order), so a tile's entries are one run of it:
+// a block finds the runs by search, adds them into an LDS copy of the tile's g
+// -- worker by worker, with a barrier between workers, so every sum is formed
+// in worker order -- and streams theta and m once, reading g from LDS.  HBM
+// traffic: 8 bytes read and 8 written per element, 8 per list entry.
 #include "device_common.hpp"
 #include "launch.hpp"
 
@@ -25,35 +19,63 @@ namespace pulse {
 
 namespace {
 
+// What bounds it: HBM, as four streams (theta and m read and written), which
+// blocks that each do one round of loads and stores carry fastest: 494M
+// elements without lists take 1.30 ms (6.1 TB/s), against 1.59 ms for blocks
+// that walk 262,144 elements each.  The lists add the searches' probes and
+// latency.  Measured on the 218-tensor 0.5B set (ms, 2% density; 1, 4 and 8
+// workers): 262,144-element units 1.66, 1.98-2.04, 2.64; this form 1.41, 1.42,
+// 1.64.  Small sets gain more, since a unit was one block's work: 3M elements
+// in 40 tensors with 8 workers 240 -> 32 us.
 constexpr int kOuterTB = 512;                   // threads per block
-constexpr int kOuterVec = 4;                    // float4 per thread per tile
-constexpr uint32_t kOuterTile = kOuterTB * kOuterVec * 4;  // 8192 elements
-constexpr uint64_t kUnit = 32ull * kOuterTile;  // 262,144 elements per work unit
+constexpr int kOuterWaves = kOuterTB / 64;
+constexpr int kOuterVec = 3;                    // float4 per thread
+constexpr uint32_t kOuterTile = kOuterTB * kOuterVec * 4;  // elements of a block
+// List entries of a tile a wave holds, per lane: kFirst loaded at once (128
+// entries of 6,144 elements: 2% density), the rest only if the tile has more.
+// Tiles of 4,096 or 8,192 elements were within 3% at 2% density and one to
+// four workers; one wave per list needs eight waves for eight workers (four
+// waves of 256-thread blocks: 1.94 ms with 8 workers).
+constexpr int kFirst = 2;
+constexpr int kHeld = 4;
+static_assert(kOuterWaves >= kMaxLists, "one wave per list");
 
-// First position k in [lo, hi) with idx[k] >= target, or hi.  Whole wave.
-__device__ uint64_t wave_lower_bound(const uint32_t* idx, uint64_t lo, uint64_t hi,
-                                     uint32_t target) {
+// First position in [lo, hi) with idx >= target, or hi.  Whole wave.  `x`: the
+// target's place in the tensor, in [0, 1].  Each round reads 16 probes (a probe
+// costs a cache line: 64 of them per round moved more bytes than the tile
+// itself), the first one around where evenly spread entries would put the
+// target (the position's standard deviation is at most sqrt(entries) / 2), the
+// later ones splitting what is left evenly.
+__device__ uint64_t wave_lower_bound(const uint32_t* idx, uint64_t lo, uint64_t hi, uint64_t target,
+                                     float x) {
   const int lane = lane_id();
+  bool guess = true;
   while (hi - lo > 64) {
-    // probes p_l = lo + (hi - lo) * (l + 1) / 65 split [lo, hi) into 65 parts
-    const uint64_t span = hi - lo;
-    const uint64_t p = lo + span * (uint64_t)(lane + 1) / 65u;  // span < 2^58
-    const uint64_t ge = __ballot(idx[p] >= target);
+    const uint64_t span = hi - lo;  // < 2^58
+    uint64_t at = lo + span * (uint64_t)((lane & 15) + 1) / 17u;
+    if (guess) {
+      // 16 distinct ascending positions in [lo, hi)
+      guess = false;
+      const float s = (float)span;
+      const int64_t step = 1 + (int64_t)(__builtin_sqrtf(s) * 0.125f);
+      int64_t q = (int64_t)(s * x) + ((lane & 15) - 8) * step;
+      const int64_t bot = lane & 15, top = (int64_t)span - 16 + (lane & 15);
+      q = q < bot ? bot : q > top ? top : q;
+      at = lo + (uint64_t)q;
+    }
+    const uint32_t ge = (uint32_t)__ballot(lane < 16 && (uint64_t)idx[lane < 16 ? at : lo] >= target);
     if (ge == 0) {
-      lo = __shfl(p, 63, 64) + 1;  // every probe is below target
+      lo = __shfl(at, 15, 64) + 1;  // every probe is below the target
     } else {
-      const int f = __builtin_ctzll(ge);
-      const uint64_t pf = __shfl(p, f, 64);
-      const uint64_t pb = f > 0 ? __shfl(p, f - 1, 64) + 1 : lo;
+      const int q = __builtin_ctz(ge);
+      const uint64_t pb = q > 0 ? __shfl(at, q - 1, 64) + 1 : lo;
+      hi = __shfl(at, q, 64);  // idx[hi] >= target: the answer is at most there
       lo = pb;
-      hi = pf;  // idx[pf] >= target: the answer is at most pf
-      if (lo == hi) return lo;
     }
   }
   const uint64_t k = lo + (uint64_t)lane;
-  const uint64_t ge = __ballot(k < hi && idx[k] >= target);
-  if (ge == 0) return hi;
-  return lo + (uint64_t)__builtin_ctzll(ge);
+  const uint64_t ge = __ballot(k < hi && (uint64_t)idx[k < hi ? k : lo] >= target);
+  return ge == 0 ? hi : lo + (uint64_t)__builtin_ctzll(ge);
 }
 
 __device__ __forceinline__ float4 ld4(const float* p) {
@@ -82,131 +104,173 @@ __device__ __forceinline__ void nesterov(float& th, float& m, float g, float mu,
   th = th - step;
 }
 
+// Tensor of a block-uniform tile: the last tensor whose first tile is <= tile
+// (starts never decrease; an empty tensor shares its start with the next one,
+// which wins).  A binary search with scalar loads of the kernel arguments.
+__device__ __forceinline__ int outer_owner(const OuterParams& p, uint32_t tile) {
+  static_assert(kMaxBatch == 64, "six halvings cover 64 tensors");
+  uint32_t k = 0;
+#pragma unroll
+  for (uint32_t step = 32; step > 0; step >>= 1) {
+    const uint32_t q = k + step;
+    if (q < (uint32_t)p.ntensors && p.tile_begin[q] <= tile) k = q;
+  }
+  return (int)k;
+}
+
 }  // namespace
 
 __global__ __launch_bounds__(kOuterTB) void outer_kernel(OuterParams p) {
   __shared__ float4 s_g[kOuterTile / 4];
-  __shared__ uint64_t s_pos[kMaxLists];
-  __shared__ uint64_t s_hi[kMaxLists];
+  __shared__ uint64_t s_more[kMaxLists];  // entries of the tile past the held ones: from here
+  __shared__ uint32_t s_cnt[kMaxLists];   // how many
   const int tid = threadIdx.x;
   const int wid = tid >> 6;
   const int R = p.nlists;
-  const uint32_t lane_begin = owner_lane_begin(p);
-  for (uint32_t u = blockIdx.x; u < p.nunits; u += gridDim.x) {
-    // the unit's tensor and element range
-    const int k = owner_of(lane_begin, u);
-    const OuterTensorDesc t = p.t[k];
-    const uint64_t u0 = (uint64_t)(u - p.tile_begin[k]) * kUnit;
-    const uint64_t u1 = u0 + kUnit < t.n ? u0 + kUnit : t.n;
-    // each list's entries of this tensor, and the first one at or past u0
-    __syncthreads();  // the previous unit is done with s_pos / s_hi
-    for (int r = wid; r < R; r += kOuterTB / 64) {
-      const OuterListDesc& L = p.l[r];
-      const uint64_t cap = L.capacity;
-      uint64_t lo = L.seg_begin[k];
-      uint64_t hi = k + 1 < p.ntensors ? L.seg_begin[k + 1] : *L.end;
-      lo = lo < cap ? lo : cap;
-      hi = hi < cap ? hi : cap;
-      hi = hi > lo ? hi : lo;
-      const uint64_t first =
-          u0 == 0 ? lo : wave_lower_bound(L.idx, lo, hi, t.index_base + (uint32_t)u0);
-      if (lane_id() == 0) {
-        s_pos[r] = first;
-        s_hi[r] = hi;
+  const int k = outer_owner(p, blockIdx.x);
+  float* const theta = p.t[k].theta;
+  float* const momentum = p.t[k].momentum;
+  const uint64_t n = p.t[k].n;
+  const uint32_t base = p.t[k].index_base;
+  const uint64_t t0 = (uint64_t)(blockIdx.x - p.tile_begin[k]) * kOuterTile;
+  const uint64_t t1 = t0 + kOuterTile < n ? t0 + kOuterTile : n;
+  // this thread's elements: float4 j at t0 + (j * TB + tid) * 4, in flight
+  // during the searches
+  float4 th[kOuterVec], mo[kOuterVec];
+  const bool full = t0 + kOuterTile <= n;
+#pragma unroll
+  for (int j = 0; j < kOuterVec; ++j) {
+    const uint64_t e = t0 + (uint64_t)(j * kOuterTB + tid) * 4;
+    if (full) {
+      th[j] = ld4(theta + e);
+      mo[j] = ld4(momentum + e);
+    } else {
+      float a[4], b[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        a[c] = e + c < t1 ? theta[e + c] : 0.0f;
+        b[c] = e + c < t1 ? momentum[e + c] : 0.0f;
+      }
+      th[j] = make_float4(a[0], a[1], a[2], a[3]);
+      mo[j] = make_float4(b[0], b[1], b[2], b[3]);
+    }
+    s_g[j * kOuterTB + tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  }
+  // Wave r takes list r: it finds the list's first entry in the tile and holds
+  // the entries from there on, kHeld per lane.
+  const uint64_t lo_idx = (uint64_t)base + t0;
+  const uint64_t hi_idx = (uint64_t)base + t1;  // <= index_base + n <= 2^32
+  const int lane = lane_id();
+  uint32_t id[kHeld];
+  float v[kHeld];
+#pragma unroll
+  for (int h = 0; h < kHeld; ++h) {
+    id[h] = 0xFFFFFFFFu;  // with v = 0: no entry
+    v[h] = 0.0f;
+  }
+  if (wid < R) {
+    const OuterListDesc& L = p.l[wid];
+    const uint64_t cap = L.capacity;
+    uint64_t lo = L.seg_begin[k];
+    uint64_t hi = k + 1 < p.ntensors ? L.seg_begin[k + 1] : *L.end;
+    lo = lo < cap ? lo : cap;
+    hi = hi < cap ? hi : cap;
+    hi = hi > lo ? hi : lo;
+    const uint64_t f = wave_lower_bound(L.idx, lo, hi, lo_idx, (float)t0 / (float)n);
+    auto hold = [&](int h) {
+      const uint64_t at = f + (uint64_t)(h * 64 + lane);
+      if (at < hi) {
+        id[h] = L.idx[at];
+        v[h] = L.val[at];
+      }
+    };
+    // whether the list goes on in the tile past the first h entries per lane
+    auto goes_on = [&](int h) {
+      return __ballot(lane == 63 && f + (uint64_t)(h * 64) < hi && (uint64_t)id[h - 1] < hi_idx) != 0;
+    };
+#pragma unroll
+    for (int h = 0; h < kFirst; ++h) hold(h);
+    uint64_t m0 = f + kHeld * 64, m1 = m0;  // entries that are not held: dense lists
+    if (goes_on(kFirst)) {
+#pragma unroll
+      for (int h = kFirst; h < kHeld; ++h) hold(h);
+      if (goes_on(kHeld)) {
+        // ascending distinct indices: at most a tile's elements (which also
+        // bounds the work for a list out of order)
+        const uint64_t top = f + kOuterTile < hi ? f + kOuterTile : hi;
+        m1 = wave_lower_bound(L.idx, m0, top, hi_idx, (float)(t1 - t0) / (float)kOuterTile);
       }
     }
+    if (lane == 0) {
+      s_more[wid] = m0;
+      s_cnt[wid] = (uint32_t)(m1 - m0);
+    }
+  }
+  __syncthreads();  // g is zero everywhere
+  // Scatter-add, worker by worker: the entries of one list are distinct, so
+  // its adds never collide, and a barrier orders the workers.
+  float* g = reinterpret_cast<float*>(s_g);
+  for (int r = 0; r < R; ++r) {
+    if (r == wid) {
+#pragma unroll
+      for (int h = 0; h < kHeld; ++h) {
+        const uint64_t o = (uint64_t)id[h] - lo_idx;
+        if (o < t1 - t0 && (id[h] != 0xFFFFFFFFu || v[h] != 0.0f)) g[o] += v[h];
+      }
+    }
+    const uint32_t more = s_cnt[r];
+    for (uint32_t c = (uint32_t)tid; c < more; c += kOuterTB) {
+      const uint64_t o = (uint64_t)p.l[r].idx[s_more[r] + c] - lo_idx;
+      if (o < t1 - t0) g[o] += p.l[r].val[s_more[r] + c];
+    }
     __syncthreads();
-    for (uint64_t t0 = u0; t0 < u1; t0 += kOuterTile) {
-      const uint64_t t1 = t0 + kOuterTile < u1 ? t0 + kOuterTile : u1;
-      // this thread's elements: float4 j at t0 + (j * TB + tid) * 4
-      float4 th[kOuterVec], mo[kOuterVec];
+  }
+  // R a power of two: the product by 1 / R rounds to the same value as the quotient
+  const float rf = (float)R;
+  const bool pow2 = (R & (R - 1)) == 0;
+  const float inv = R > 0 ? 1.0f / rf : 1.0f;
 #pragma unroll
-      for (int j = 0; j < kOuterVec; ++j) {
-        const uint64_t e = t0 + (uint64_t)(j * kOuterTB + tid) * 4;
-        if (e + 4 <= t1) {
-          th[j] = ld4(t.theta + e);
-          mo[j] = ld4(t.momentum + e);
-        } else {
-          float a[4], b[4];
+  for (int j = 0; j < kOuterVec; ++j) {
+    const uint64_t e = t0 + (uint64_t)(j * kOuterTB + tid) * 4;
+    float4 gv = s_g[j * kOuterTB + tid];
+    if (pow2) {
+      gv.x = gv.x * inv;
+      gv.y = gv.y * inv;
+      gv.z = gv.z * inv;
+      gv.w = gv.w * inv;
+    } else {
+      gv.x = gv.x / rf;
+      gv.y = gv.y / rf;
+      gv.z = gv.z / rf;
+      gv.w = gv.w / rf;
+    }
+    nesterov(th[j].x, mo[j].x, gv.x, p.mu, p.alpha);
+    nesterov(th[j].y, mo[j].y, gv.y, p.mu, p.alpha);
+    nesterov(th[j].z, mo[j].z, gv.z, p.mu, p.alpha);
+    nesterov(th[j].w, mo[j].w, gv.w, p.mu, p.alpha);
+    if (full) {
+      st4(theta + e, th[j]);
+      st4(momentum + e, mo[j]);
+    } else {
+      const float a[4] = {th[j].x, th[j].y, th[j].z, th[j].w};
+      const float b[4] = {mo[j].x, mo[j].y, mo[j].z, mo[j].w};
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            a[c] = e + c < t1 ? t.theta[e + c] : 0.0f;
-            b[c] = e + c < t1 ? t.momentum[e + c] : 0.0f;
-          }
-          th[j] = make_float4(a[0], a[1], a[2], a[3]);
-          mo[j] = make_float4(b[0], b[1], b[2], b[3]);
-        }
-        s_g[j * kOuterTB + tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      }
-      __syncthreads();  // g is zero everywhere
-      // scatter-add the lists, worker by worker; the entries of one list are
-      // distinct, so its adds never collide, and the barrier in the count
-      // orders the workers
-      const uint64_t lo_idx = (uint64_t)t.index_base + t0;
-      const uint64_t hi_idx = (uint64_t)t.index_base + t1;  // <= index_base + n <= 2^32
-      float* g = reinterpret_cast<float*>(s_g);
-      for (int r = 0; r < R; ++r) {
-        const OuterListDesc& L = p.l[r];
-        uint64_t pos = s_pos[r];
-        const uint64_t hi = s_hi[r];
-        for (;;) {
-          const uint64_t kk = pos + (uint64_t)tid;
-          const uint32_t id = kk < hi ? L.idx[kk] : 0xFFFFFFFFu;
-          // entries below the tile (outside the tensor) are consumed, not added
-          const bool consumed = kk < hi && (uint64_t)id < hi_idx;
-          if (consumed && (uint64_t)id >= lo_idx) g[(uint64_t)id - lo_idx] += L.val[kk];
-          const int c = __syncthreads_count(consumed);
-          pos += (uint64_t)c;
-          if (c < kOuterTB) break;
-        }
-        if (tid == 0) s_pos[r] = pos;
-      }
-      const float rf = (float)R;
-#pragma unroll
-      for (int j = 0; j < kOuterVec; ++j) {
-        const uint64_t e = t0 + (uint64_t)(j * kOuterTB + tid) * 4;
-        float4 gv = s_g[j * kOuterTB + tid];
-        if (R > 0) {
-          gv.x = gv.x / rf;
-          gv.y = gv.y / rf;
-          gv.z = gv.z / rf;
-          gv.w = gv.w / rf;
-        }
-        nesterov(th[j].x, mo[j].x, gv.x, p.mu, p.alpha);
-        nesterov(th[j].y, mo[j].y, gv.y, p.mu, p.alpha);
-        nesterov(th[j].z, mo[j].z, gv.z, p.mu, p.alpha);
-        nesterov(th[j].w, mo[j].w, gv.w, p.mu, p.alpha);
-        if (e + 4 <= t1) {
-          st4(t.theta + e, th[j]);
-          st4(t.momentum + e, mo[j]);
-        } else {
-          const float a[4] = {th[j].x, th[j].y, th[j].z, th[j].w};
-          const float b[4] = {mo[j].x, mo[j].y, mo[j].z, mo[j].w};
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            if (e + c < t1) {
-              t.theta[e + c] = a[c];
-              t.momentum[e + c] = b[c];
-            }
-          }
+      for (int c = 0; c < 4; ++c) {
+        if (e + c < t1) {
+          theta[e + c] = a[c];
+          momentum[e + c] = b[c];
         }
       }
-      __syncthreads();  // every read of g and s_pos done before the next tile
     }
   }
 }
 
-uint64_t outer_unit_elems() { return kUnit; }
+uint64_t outer_tile_elems() { return kOuterTile; }
+uint64_t outer_max_tiles() { return 0xFFFFFFFFull / kOuterTB; }
 
 hipError_t launch_outer(const OuterParams& p, hipStream_t stream) {
-  if (p.nunits == 0) return hipSuccess;
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return hipErrorInvalidValue;
-  const uint32_t cap = (uint32_t)(cus > 0 ? cus : 1) * 2u;
-  const uint32_t grid = p.nunits < cap ? p.nunits : cap;
-  hipLaunchKernelGGL(outer_kernel, dim3(grid), dim3(kOuterTB), 0, stream, p);
+  if (p.ntiles == 0) return hipSuccess;
+  hipLaunchKernelGGL(outer_kernel, dim3(p.ntiles), dim3(kOuterTB), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -507,7 +507,7 @@ int pulse_outer_step_batch(const pulse_outer_tensor* tensors, uint32_t ntensors,
       return fail(PULSE_EALIGN, "outer tensor %u: theta/momentum not 16-byte aligned", t);
     if (int rc = check_range(d.n, d.index_base, "outer", t)) return rc;
   }
-  const uint64_t unit = pulse::outer_unit_elems();
+  const uint64_t tile = pulse::outer_tile_elems(), max_tiles = pulse::outer_max_tiles();
   uint32_t t0 = 0;
   while (t0 < ntensors) {
     pulse::OuterParams p;
@@ -515,23 +515,23 @@ int pulse_outer_step_batch(const pulse_outer_tensor* tensors, uint32_t ntensors,
     p.mu = mu;
     p.alpha = alpha;
     p.nlists = (int)nlists;
-    uint64_t units = 0;
+    uint64_t tiles = 0;
     int k = 0;
     while (t0 + k < ntensors && k < pulse::kMaxBatch) {
       const pulse_outer_tensor& d = tensors[t0 + k];
-      const uint64_t nu = (d.n + unit - 1) / unit;
-      if (k > 0 && units + nu > 0xFFFFFFFFull) break;
-      p.tile_begin[k] = (uint32_t)units;
+      const uint64_t nt = (d.n + tile - 1) / tile;
+      if (k > 0 && tiles + nt > max_tiles) break;
+      p.tile_begin[k] = (uint32_t)tiles;
       p.t[k].theta = d.theta;
       p.t[k].momentum = d.momentum;
       p.t[k].n = d.n;
       p.t[k].index_base = d.index_base;
-      units += nu;
+      tiles += nt;
       ++k;
     }
-    p.tile_begin[k] = (uint32_t)units;
+    p.tile_begin[k] = (uint32_t)tiles;
     p.ntensors = k;
-    p.nunits = (uint32_t)units;
+    p.ntiles = (uint32_t)tiles;
     for (uint32_t r = 0; r < nlists; ++r) {
       p.l[r].idx = lists[r].idx;
       p.l[r].val = lists[r].val;

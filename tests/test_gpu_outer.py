@@ -1,8 +1,8 @@
 """GPU parity: PULSELoCo outer step (SparseSync average + outer Nesterov), HIP vs oracle, bit-exact.
 
-Sizes span several 262,144-element work units and 8,192-element tiles with
-ragged tails; lists cover 0..8 workers, densities from a few entries to every
-element (so a tile takes several 512-entry passes per list), indices outside the
+Sizes span many 6,144-element tiles with ragged tails; lists cover 0..8
+workers, densities from a few entries to every element (so a tile takes several
+512-entry passes per list), indices outside the
 tensor, capacity clipping, the largest index base, multi-tensor batches split
 over launches, and a whole round chained from the sparsifier on each side.
 """
@@ -56,6 +56,41 @@ def test_outer_step_single_tensor_rounds(n, R):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(hf32(m_d), m)
         np.testing.assert_array_equal(hf32(th_d), th)
+
+
+TILE = 6144  # elements of a block; a wave holds 128 entries of a list per tile at once, 256 at most
+
+
+@pytest.mark.parametrize("n", [TILE - 1, TILE, TILE + 1, 3 * TILE + 5])
+@pytest.mark.parametrize("per_tile", [63, 64, 65, 127, 128, 129, 255, 256, 257, 6000])
+def test_outer_step_tile_and_held_entry_edges(n, per_tile):
+    """Lists with so many entries in every tile, the same with all of them at the
+    end of each tile or of the tensor (so that the search's first guess is far
+    off), at the top of the index range (the last index is 2^32 - 1)."""
+    rng = np.random.default_rng(n * 7 + per_tile)
+    base = (1 << 32) - n
+    ntiles = -(-n // TILE)
+
+    def pick(t, packed):
+        size = min(TILE, n - t * TILE)
+        k = min(size, per_tile)
+        at = np.arange(size - k, size) if packed else np.sort(rng.choice(size, k, replace=False))
+        return at + t * TILE
+
+    even = np.concatenate([pick(t, False) for t in range(ntiles)])
+    packed = np.concatenate([pick(t, True) for t in range(ntiles)])
+    tail = np.arange(max(0, n - per_tile), n)
+    th = (rng.standard_normal(n) * 0.1).astype(np.float32)
+    m = (rng.standard_normal(n) * 0.01).astype(np.float32)
+    th_d, m_d = dev(th), dev(m)
+    lists = []
+    for at in (even, packed, tail):
+        lists.append(((at + base).astype(np.uint32), rng.standard_normal(at.size).astype(np.float32)))
+    oracle.outer_step(th, m, lists, mu=MU, alpha=ALPHA, index_base=base)
+    pulse.outer_step(th_d, m_d, gpu_lists(lists), mu=MU, alpha=ALPHA, index_base=base)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(hf32(m_d), m)
+    np.testing.assert_array_equal(hf32(th_d), th)
 
 
 def test_outer_step_out_of_range_indices_capacity_and_max_base():
