@@ -1,6 +1,7 @@
 // cast.hip -- the dense BF16 view of an FP32 tensor (Sec. 3 "Sparsity
 // metric"; RNE per App. A.2 / App. D).  Eight elements per lane per step:
-// two 16-byte loads, one 16-byte store.  Also a plain zero fill.
+// two 16-byte loads, one 16-byte store.  Also a plain zero fill and
+// a write of words that come as kernel arguments.
 #include "device_common.hpp"
 #include "launch.hpp"
 
@@ -42,6 +43,17 @@ __global__ __launch_bounds__(kCastTB) void zero_words_kernel(uint64_t* __restric
                                                              uint64_t nwords) {
   const uint64_t stride = (uint64_t)gridDim.x * kCastTB;
   for (uint64_t i = (uint64_t)blockIdx.x * kCastTB + threadIdx.x; i < nwords; i += stride) p[i] = 0;
+}
+
+__global__ __launch_bounds__(512) void put_words_kernel(PutWords p) {
+  if (threadIdx.x < p.n) p.dst[threadIdx.x] = p.w[threadIdx.x];
+}
+
+hipError_t launch_put_words(const PutWords& p, hipStream_t stream) {
+  static_assert(PutWords::kRoom <= 512, "one word per thread");
+  if (p.n == 0) return hipSuccess;
+  hipLaunchKernelGGL(put_words_kernel, dim3(1), dim3(512), 0, stream, p);
+  return hipGetLastError();
 }
 
 hipError_t launch_zero_words(uint64_t* p, uint64_t nwords, hipStream_t stream) {

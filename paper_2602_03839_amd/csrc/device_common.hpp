@@ -48,10 +48,14 @@ constexpr int kWordDone = 32;
 constexpr int kTicketBits = 24;
 constexpr uint64_t kTicketMask = (1ull << kTicketBits) - 1;
 constexpr uint64_t kSeqMask = (1ull << 40) - 1;  // G0 is kept modulo 2^40
-constexpr int kSlotBits = 16;
+// The words after the ring hold the tensor table of a launch of more than
+// kMaxBatch tensors (TileMap below).
+constexpr int kSlotBits = 15;
 constexpr uint64_t kSlots = 1ull << kSlotBits;
 constexpr int kStatusOffsetWords = 64;            // 512-byte header
-constexpr size_t kWorkspaceBytes = (kStatusOffsetWords + kSlots) * sizeof(uint64_t);
+constexpr size_t kTableWords = 1u << 15;
+constexpr size_t kTableOffsetWords = kStatusOffsetWords + kSlots;
+constexpr size_t kWorkspaceBytes = (kTableOffsetWords + kTableWords) * sizeof(uint64_t);
 constexpr uint32_t kMaxTilesPerLaunch = (1u << kTicketBits) - 1;  // < kNoTicket
 // Largest grid of a ticketed launch.
 constexpr uint32_t kMaxGrid = 1u << 16;
@@ -366,25 +370,86 @@ __device__ uint64_t look_back(uint64_t* ws, const Ticket& tk, LookWindow<LK> win
   }
 }
 
-// Owner of a tile.  Lane k of a wave holds tile_begin[k] for k < ntensors
-// (<= 64 tensors per launch) and ~0 elsewhere; the tensor that owns tile t is
-// the highest lane whose begin is <= t (begins never decrease, and an empty
-// tensor shares its begin with the next tensor, which wins).  One compare and
-// one ballot, no memory access on the way.
-template <typename Params>
-__device__ __forceinline__ uint32_t owner_lane_begin(const Params& p) {
-  uint32_t v = ~0u;
-  const int lane = lane_id();
+// ---------------------------------------------------------------- tensors of a launch
+//
+// A launch's tensors come with its kernel arguments (up to kMaxBatch), or
+// (TABLE) as an array in the workspace, written by a small launch before: a
+// launch costs its fill and drain, ~35 us, so a set of 218 tensors in one
+// launch instead of four saves ~100 us.  The array does not change while the
+// kernel runs and is read with scalar loads, as kernel arguments are.
+template <bool TABLE, typename Params>
+__device__ __forceinline__ auto tensor_at(const Params& p, int k) {
+  typename Params::Desc d;
+  if (TABLE) {
+    typedef const __attribute__((address_space(4))) uint64_t* cword;
+    const cword q = (cword)(uintptr_t)(p.table + k);
+    static_assert(sizeof(d) % 8 == 0, "descriptors are read as whole words");
+    uint64_t w[sizeof(d) / 8];
 #pragma unroll
-  for (int k = 0; k < 64; ++k)
-    if (k < p.ntensors && lane == k) v = p.tile_begin[k];
-  return v;
+    for (int i = 0; i < (int)(sizeof(d) / 8); ++i) w[i] = q[i];
+    __builtin_memcpy(&d, w, sizeof d);
+  } else {
+    d = p.t[k];
+  }
+  return d;
 }
 
-__device__ __forceinline__ int owner_of(uint32_t lane_begin, uint32_t t) {
-  const uint64_t b = __ballot(lane_begin <= t);  // lane 0 holds 0 <= t
-  return 63 - __builtin_clzll(b);
-}
+// The tensor that owns tile t: the last one whose first tile is <= t (starts
+// never decrease, and an empty tensor shares its start with the next one,
+// which wins).  In the kernel-argument form lane k of a wave holds tensor k's
+// start (~0 past the last), and one compare and one ballot answer, with no
+// memory access on the way.  In the table form lane l holds the start of
+// tensor l * stride, and a second round covers the stride tensors from LDS.
+// A wave-uniform t gives a wave-uniform answer.
+struct TileOwner {
+  int k;
+  uint32_t begin;  // its first tile
+};
+
+template <bool TABLE, typename Params>
+struct TileMap {
+  uint32_t lane_begin;
+  uint32_t stride;
+  uint32_t n;
+  const uint32_t* s_begin;  // TABLE: every start, in LDS
+
+  // s: LDS with room for kMaxTable starts, filled (fill) and visible before.
+  __device__ __forceinline__ TileMap(const Params& p, const uint32_t* s) : s_begin(s) {
+    const int lane = lane_id();
+    n = (uint32_t)p.ntensors;
+    stride = 1;
+    uint32_t v = ~0u;
+    if (TABLE) {
+      stride = (n + 63) / 64;
+      if ((uint32_t)lane * stride < n) v = s[(uint32_t)lane * stride];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 64; ++k)
+        if (k < p.ntensors && lane == k) v = p.tile_begin[k];
+    }
+    lane_begin = v;
+  }
+
+  // Every thread of the block; the caller's next barrier makes it visible.
+  __device__ static __forceinline__ void fill(const Params& p, uint32_t* s) {
+    if (TABLE)
+      for (uint32_t i = threadIdx.x; i < (uint32_t)p.ntensors; i += blockDim.x) s[i] = p.table_begin[i];
+  }
+
+  __device__ __forceinline__ TileOwner owner(uint32_t t) const {
+    const uint64_t b = __ballot(lane_begin <= t);  // lane 0 holds 0 <= t
+    const int g = 63 - __builtin_clzll(b);
+    if (!TABLE) return TileOwner{g, (uint32_t)__builtin_amdgcn_readlane((int)lane_begin, g)};
+    const uint32_t q = (uint32_t)g * stride + (uint32_t)lane_id();
+    const uint32_t v = (uint32_t)lane_id() < stride && q < n ? s_begin[q] : ~0u;
+    const int f = 63 - __builtin_clzll(__ballot(v <= t));  // lane 0 of the group holds <= t
+    return TileOwner{g * (int)stride + f, (uint32_t)__builtin_amdgcn_readlane((int)v, f)};
+  }
+
+  __device__ __forceinline__ uint32_t begin(const Params& p, int k) const {
+    return TABLE ? s_begin[k] : p.tile_begin[k];
+  }
+};
 
 // ---------------------------------------------------------------- scan wave
 //
@@ -418,6 +483,7 @@ struct ScanState {
   Ticket tk;
   uint64_t agg;
   int k;
+  uint32_t begin;  // first tile of tensor k
   bool valid;
   bool ovf;  // some wave-group of the tile found more than seg_cap entries
 };
@@ -437,8 +503,8 @@ struct KnownPrefix {
 };
 constexpr uint32_t kNoTile = 0xFFFFFFFFu;
 
-template <int U, int NW, int RES, typename Params, int AHEAD = kAhead>
-__device__ void scan_wave_loop(const Params& p, uint64_t* s_tk, uint32_t* s_wtot2,
+template <int U, int NW, int RES, bool TABLE, typename Params, int AHEAD = kAhead>
+__device__ void scan_wave_loop(const Params& p, const uint32_t* s_begin, uint64_t* s_tk, uint32_t* s_wtot2,
                                uint32_t* s_wexcl, uint64_t* s_excl2, uint32_t* s_cnt2,
                                uint32_t* s_ovf2, uint32_t seg_cap, KnownPrefix* s_known) {
   constexpr int kResolve = RES;
@@ -482,7 +548,7 @@ __device__ void scan_wave_loop(const Params& p, uint64_t* s_tk, uint32_t* s_wtot
   // kNoTicket when the block's first chunk lies past the last tile, and the
   // sequence base must never move backwards
   uint64_t count_in = 0;
-  const uint32_t lane_begin = owner_lane_begin(p);
+  const TileMap<TABLE, Params> map(p, s_begin);
   ScanState hist[kDefer];  // hist[d]: T(i - 1 - d)
 #pragma unroll
   for (int d = 0; d < kDefer; ++d) hist[d].valid = false;
@@ -510,7 +576,9 @@ __device__ void scan_wave_loop(const Params& p, uint64_t* s_tk, uint32_t* s_wtot
       now.tk = cur;
       now.agg = __shfl(incl, 63, 64);
       now.ovf = __ballot(lane < U * NW && v > seg_cap) != 0;
-      now.k = owner_of(lane_begin, cur.tile);
+      const TileOwner ow = map.owner(cur.tile);
+      now.k = ow.k;
+      now.begin = ow.begin;
       if (cur.tile == 0) {
         count_in = *p.count;  // append position, written by an earlier call
         if (lane == 0) status_publish(p.ws, cur.seq, kFlagPrefix, count_in + now.agg);
@@ -534,8 +602,8 @@ __device__ void scan_wave_loop(const Params& p, uint64_t* s_tk, uint32_t* s_wtot
         if (res.tk.tile == p.ntiles - 1) *p.count = excl + res.agg;
         if (p.seg_begin) {
           // segment starts of this tensor and of the empty tensors just before it
-          if (p.tile_begin[res.k] == res.tk.tile) {
-            for (int kk = res.k; kk >= 0 && p.tile_begin[kk] == res.tk.tile; --kk)
+          if (res.begin == res.tk.tile) {
+            for (int kk = res.k; kk >= 0 && map.begin(p, kk) == res.tk.tile; --kk)
               p.seg_begin[kk] = excl;
           }
           // empty tensors at the end of the batch start where the patch ends

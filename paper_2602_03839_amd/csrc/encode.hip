@@ -41,18 +41,19 @@ struct TileCtx {
   uint64_t e0;  // first element of the tile in its tensor
   uint64_t n;   // tensor length
   int k;        // tensor index within the launch
-  uint32_t tile_in_tensor;
 };
 
-__device__ __forceinline__ TileCtx locate(const EncodeParams& p, uint32_t lane_begin, uint32_t tile,
-                                          uint32_t tile_elems) {
+template <bool TABLE>
+__device__ __forceinline__ TileCtx locate(const EncodeParams& p, const TileMap<TABLE, EncodeParams>& map,
+                                          uint32_t tile, uint32_t tile_elems) {
   TileCtx c;
-  c.k = owner_of(lane_begin, tile);
-  c.tile_in_tensor = tile - p.tile_begin[c.k];
-  c.e0 = (uint64_t)c.tile_in_tensor * tile_elems;
-  c.n = p.t[c.k].n;
-  c.w = p.t[c.k].w_new;
-  c.s = p.t[c.k].snap;
+  const TileOwner o = map.owner(tile);
+  const EncodeTensorDesc d = tensor_at<TABLE>(p, o.k);
+  c.k = o.k;
+  c.e0 = (uint64_t)(tile - o.begin) * tile_elems;
+  c.n = d.n;
+  c.w = d.w_new;
+  c.s = d.snap;
   return c;
 }
 
@@ -131,7 +132,7 @@ __device__ __forceinline__ uint16_t bf16_slot(uint32_t h0, uint32_t h1, uint32_t
 
 // REFRESH: some tensor of the launch has an inference copy to refresh in the
 // same pass (a separate instantiation, so the plain encode carries no test).
-template <int NW, int U, bool REFRESH>
+template <int NW, int U, bool REFRESH, bool TABLE>
 __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
   constexpr int TBC = NW * 64;
   constexpr uint32_t TILE = TBC * U * 8;
@@ -144,6 +145,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
   __shared__ uint32_t s_wexcl[kWexclRing * NSEG];
   __shared__ uint32_t s_seg[kSegSlots][NSEG][kSegCap];  // (offset in tile << 16) | bf16 value
   __shared__ KnownPrefix s_known[2];
+  __shared__ uint32_t s_begin[TABLE ? kMaxTable : 1];
   static_assert(NSEG <= 64, "block scan runs on one wave");
   static_assert(U <= 4, "masks of all groups are packed into one register");
   static_assert(TILE <= 65536, "offsets within a tile are stored in 16 bits");
@@ -153,8 +155,9 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
   const int lane = lane_id();
   const int wid = tid >> 6;
 
+  TileMap<TABLE, EncodeParams>::fill(p, s_begin);
   if (wid == NW) {
-    scan_wave_loop<U, NW, kResolve>(p, s_tk, s_wtot, s_wexcl, s_excl, s_tcnt, s_tovf, kSegCap,
+    scan_wave_loop<U, NW, kResolve, TABLE>(p, s_begin, s_tk, s_wtot, s_wexcl, s_excl, s_tcnt, s_tovf, kSegCap,
                                      s_known);
     return;
   }
@@ -167,7 +170,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
   // in the previous iteration.
   __syncthreads();  // T(0) .. T(kAhead) are in s_tk
   static_assert(kAhead == 1 || kAhead == 2, "one or two register sets");
-  const uint32_t lane_begin = owner_lane_begin(p);
+  const TileMap<TABLE, EncodeParams> map(p, s_begin);
   TileRegs<TBC, U> r0, r1;
   uint64_t e0_0 = 0, e0_1 = 0;  // first element of the tile in each register set
   int k_0 = 0, k_1 = 0;          // and its tensor
@@ -175,7 +178,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
   for (int q = 0; q < kAhead; ++q) {
     const Ticket t = ticket_at(s_tk, q);
     if (t.tile < p.ntiles) {
-      const TileCtx c = locate(p, lane_begin, t.tile, TILE);
+      const TileCtx c = locate<TABLE>(p, map, t.tile, TILE);
       const bool full = c.e0 + TILE <= c.n;
 #pragma unroll
       for (int u = 0; u < U; ++u) load_group<TBC, U>(q == 0 ? r0 : r1, u, c, tid, full);
@@ -192,7 +195,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
     const Ticket t = ticket_at(s_tk, i + kAhead);
     have_next = t.tile < p.ntiles;
     if (have_next) {
-      cn = locate(p, lane_begin, t.tile, TILE);
+      cn = locate<TABLE>(p, map, t.tile, TILE);
       next_full = cn.e0 + TILE <= cn.n;
     }
   };
@@ -261,20 +264,22 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
       // entry of T(i) will be emitted: its entries lie below the inclusive
       // prefix of the latest tile this block resolved plus TILE for each tile
       // in between (the scan wave's slot from two iterations ago).
-      uint16_t* __restrict__ refresh = REFRESH ? p.t[ck].refresh : nullptr;
+      EncodeTensorDesc cd{};
+      if (REFRESH) cd = tensor_at<TABLE>(p, ck);
+      uint16_t* __restrict__ refresh = cd.refresh;
       const KnownPrefix kp = s_known[it & 1];
       const uint64_t span = kp.tile == kNoTile ? (uint64_t)cur.tile + 1 : (uint64_t)(cur.tile - kp.tile);
       refreshed = REFRESH && refresh != nullptr && kp.incl <= p.capacity &&
                   span <= (p.capacity - kp.incl) / TILE;
       if (refreshed) {
-        const uint64_t tn = p.t[ck].n;
+        const uint64_t tn = cd.n;
         // Whole-run refresh (the inference copy equals the snapshot wherever
         // nothing changed): every lane of a run of kSectorLanes lanes that
         // holds a change stores its eight BF16 values as one 16-byte write,
         // so the run's bytes are rewritten whole -- unchanged values equal the
         // snapshot's -- in one request instead of one partial write per
         // change.  All lanes are active here (have_cur is block-uniform).
-        const bool sector = p.t[ck].mirror != 0u;
+        const bool sector = cd.mirror != 0u;
         const uint32_t run_mask = or_across_lanes<kSectorLanes>(mask_packed);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -301,10 +306,11 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
       const uint32_t tile_cnt = s_tcnt[oi & 1];
       const bool overflowed = s_tovf[oi & 1] != 0u;
       const uint64_t cap = p.capacity;
-      const uint32_t base = p.t[od.k].index_base;
+      const EncodeTensorDesc td = tensor_at<TABLE>(p, od.k);
+      const uint32_t base = td.index_base;
       // refresh not written at compute time: only emitted entries, here
       uint16_t* __restrict__ late_refresh =
-          (REFRESH && !od.refreshed) ? p.t[od.k].refresh : nullptr;
+          (REFRESH && !od.refreshed) ? td.refresh : nullptr;
       const uint32_t* wexcl = s_wexcl + (oi & (kWexclRing - 1)) * NSEG;
       if (!overflowed) {
         // entry j of the tile lies in the last wave-group q whose prefix is <= j
@@ -326,7 +332,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
       } else {
         // a wave-group found more entries than its segment holds: every lane
         // writes its own entries, recovering the values from the FP32 masters
-        const float* w = p.t[od.k].w_new;
+        const float* w = td.w_new;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           uint32_t m = (od.mask >> (8 * u)) & 0xFFu;
@@ -381,27 +387,26 @@ constexpr int kEncodeNW = kEncodeTB / 64;
 
 uint32_t encode_tile_elems() { return kEncodeTB * kEncodeU * 8; }
 
-hipError_t launch_encode(EncodeParams& p, hipStream_t stream) {
+template <bool REFRESH, bool TABLE>
+static hipError_t launch_encode_form(const EncodeParams& p, hipStream_t stream) {
+  const int grid_cap = persistent_grid((const void*)encode_kernel<kEncodeNW, kEncodeU, REFRESH, TABLE>,
+                                       (kEncodeNW + 1) * 64);
+  if (grid_cap <= 0) return hipErrorInvalidConfiguration;
+  const uint32_t grid = p.ntiles < (uint32_t)grid_cap ? p.ntiles : (uint32_t)grid_cap;
+  hipLaunchKernelGGL((encode_kernel<kEncodeNW, kEncodeU, REFRESH, TABLE>), dim3(grid),
+                     dim3((kEncodeNW + 1) * 64), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_encode(EncodeParams& p, bool refresh, hipStream_t stream) {
   if (p.ntiles == 0) {
     if (p.seg_begin == nullptr || p.ntensors == 0) return hipSuccess;
-    hipLaunchKernelGGL(empty_segments_kernel, dim3(1), dim3(64), 0, stream,
+    hipLaunchKernelGGL(empty_segments_kernel, dim3((uint32_t)(p.ntensors + 63) / 64), dim3(64), 0, stream,
                        (const uint64_t*)p.count, p.seg_begin, (uint32_t)p.ntensors);
     return hipGetLastError();
   }
-  bool refresh = false;
-  for (int k = 0; k < p.ntensors; ++k) refresh |= p.t[k].refresh != nullptr;
-  const void* fn = refresh ? (const void*)encode_kernel<kEncodeNW, kEncodeU, true>
-                           : (const void*)encode_kernel<kEncodeNW, kEncodeU, false>;
-  const int grid_cap = persistent_grid(fn, (kEncodeNW + 1) * 64);
-  if (grid_cap <= 0) return hipErrorInvalidConfiguration;
-  const uint32_t grid = p.ntiles < (uint32_t)grid_cap ? p.ntiles : (uint32_t)grid_cap;
-  if (refresh)
-    hipLaunchKernelGGL((encode_kernel<kEncodeNW, kEncodeU, true>), dim3(grid),
-                       dim3((kEncodeNW + 1) * 64), 0, stream, p);
-  else
-    hipLaunchKernelGGL((encode_kernel<kEncodeNW, kEncodeU, false>), dim3(grid),
-                       dim3((kEncodeNW + 1) * 64), 0, stream, p);
-  return hipGetLastError();
+  if (p.table) return refresh ? launch_encode_form<true, true>(p, stream) : launch_encode_form<false, true>(p, stream);
+  return refresh ? launch_encode_form<true, false>(p, stream) : launch_encode_form<false, false>(p, stream);
 }
 
 }  // namespace pulse

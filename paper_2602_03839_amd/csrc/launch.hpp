@@ -9,8 +9,11 @@
 
 namespace pulse {
 
-constexpr int kMaxBatch = 64;  // tensors per launch; larger batches are split
+constexpr int kMaxBatch = 64;  // tensors in a launch's kernel arguments
 static_assert(kMaxBatch <= 64, "the tile -> tensor lookup keeps one tensor per lane");
+// Tensors per launch of the encoders and sparsifiers when they lie in the
+// workspace's table instead (TileMap in device_common.hpp).
+constexpr int kMaxTable = 1024;
 
 // Tile shapes: compute threads per block (a multiple of 64; one more wave is
 // added for the scan) and 8-element groups per thread.  The defaults give
@@ -38,6 +41,9 @@ struct EncodeTensorDesc {
 };
 
 struct EncodeParams {
+  typedef EncodeTensorDesc Desc;
+  const Desc* table;            // ntensors descriptors in the workspace, or null: in t
+  const uint32_t* table_begin;  // and their first tiles
   uint64_t* ws;
   uint32_t* idx;
   uint16_t* val;
@@ -64,6 +70,9 @@ struct LocoTensorDesc {
 };
 
 struct LocoParams {
+  typedef LocoTensorDesc Desc;
+  const Desc* table;            // ntensors descriptors in the workspace, or null: in t
+  const uint32_t* table_begin;  // and their first tiles
   uint64_t* ws;
   uint32_t* idx;
   float* val;
@@ -163,6 +172,9 @@ struct LowpTensorDesc {
 };
 
 struct LowpParams {
+  typedef LowpTensorDesc Desc;
+  const Desc* table;            // ntensors descriptors in the workspace, or null: in t
+  const uint32_t* table_begin;  // and their first tiles
   uint64_t* ws;
   uint32_t* idx;
   void* val;  // FP8: uint8 codes; MXFP4: uint16 (scale << 8) | code
@@ -286,7 +298,17 @@ static_assert(sizeof(ApplyParams) < 4096, "kernel argument block too large");
 
 uint32_t encode_tile_elems();
 uint32_t loco_tile_elems(int gm);
-hipError_t launch_encode(EncodeParams& p, hipStream_t stream);
+// dst[0 .. n) = w[0 .. n), by a kernel that carries the words as arguments.
+struct PutWords {
+  static constexpr uint32_t kRoom = 500;
+  uint64_t* dst;
+  uint32_t n;
+  uint64_t w[kRoom];
+};
+static_assert(sizeof(PutWords) < 4096, "kernel argument block too large");
+hipError_t launch_put_words(const PutWords& p, hipStream_t stream);
+// refresh: some tensor of the launch has a copy to refresh
+hipError_t launch_encode(EncodeParams& p, bool refresh, hipStream_t stream);
 hipError_t launch_loco(LocoParams& p, hipStream_t stream);
 
 // Two-pass form of the threshold sparsifier (loco2.hip): tiles of kL2Tile

@@ -30,19 +30,20 @@ struct LocoCtx {
   uint64_t e0;
   uint64_t n;
   int k;
-  uint32_t tile_in_tensor;
 };
 
-__device__ __forceinline__ LocoCtx locate(const LocoParams& p, uint32_t lane_begin, uint32_t tile,
-                                          uint32_t tile_elems) {
+template <bool TABLE>
+__device__ __forceinline__ LocoCtx locate(const LocoParams& p, const TileMap<TABLE, LocoParams>& map,
+                                          uint32_t tile, uint32_t tile_elems) {
   LocoCtx c;
-  c.k = owner_of(lane_begin, tile);
-  c.tile_in_tensor = tile - p.tile_begin[c.k];
-  c.e0 = (uint64_t)c.tile_in_tensor * tile_elems;
-  c.n = p.t[c.k].n;
-  c.d = p.t[c.k].delta;
-  c.r = p.t[c.k].residual;
-  c.th = p.t[c.k].theta;
+  const TileOwner o = map.owner(tile);
+  const LocoTensorDesc d = tensor_at<TABLE>(p, o.k);
+  c.k = o.k;
+  c.e0 = (uint64_t)(tile - o.begin) * tile_elems;
+  c.n = d.n;
+  c.d = d.delta;
+  c.r = d.residual;
+  c.th = d.theta;
   return c;
 }
 
@@ -150,7 +151,7 @@ constexpr int loco_ahead(int) { return 2; }
 // a back for selected entries beyond capacity.  A wave-group whose entries do
 // not fit its segment writes a everywhere instead; its write-out reads the
 // values back from the residual and zeroes the emitted ones.
-template <int NW, int U, int GM>
+template <int NW, int U, int GM, bool TABLE>
 __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
   constexpr bool GATE = GM != 0;
   constexpr int AH = loco_ahead(GM);
@@ -165,6 +166,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
   __shared__ uint32_t s_wexcl[kWexclRing * NSEG];
   __shared__ uint16_t s_off[kSegSlots][NSEG][kSegCap];  // offset of the entry in its tile
   __shared__ float s_val[kSegSlots][NSEG][kSegCap];     // its value a
+  __shared__ uint32_t s_begin[TABLE ? kMaxTable : 1];
   static_assert(NSEG <= 64, "block scan runs on one wave");
   static_assert(U <= 4, "masks of all groups are packed into one register");
   static_assert(TILE <= 65536, "offsets within a tile are stored in 16 bits");
@@ -175,8 +177,9 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
   const int wid = tid >> 6;
   const float tau = p.tau;
 
+  TileMap<TABLE, LocoParams>::fill(p, s_begin);
   if (wid == NW) {
-    scan_wave_loop<U, NW, kResolve, LocoParams, AH>(p, s_tk, s_wtot, s_wexcl, s_excl, s_tcnt,
+    scan_wave_loop<U, NW, kResolve, TABLE, LocoParams, AH>(p, s_begin, s_tk, s_wtot, s_wexcl, s_excl, s_tcnt,
                                                      s_tovf, kSegCap, nullptr);
     return;
   }
@@ -186,7 +189,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
   // registers with T(i + AH), then write the entries of T(i - kDefer))
   __syncthreads();  // T(0) .. T(AH) are in s_tk
   static_assert(AH == 1 || AH == 2, "one or two register sets");
-  const uint32_t lane_begin = owner_lane_begin(p);
+  const TileMap<TABLE, LocoParams> map(p, s_begin);
   LocoRegs<U, GATE> g0, g1;
   uint64_t e0_0 = 0, e0_1 = 0;
   int k_0 = 0, k_1 = 0;
@@ -194,7 +197,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
   for (int q = 0; q < AH; ++q) {
     const Ticket t = ticket_at(s_tk, q);
     if (t.tile < p.ntiles) {
-      const LocoCtx c = locate(p, lane_begin, t.tile, TILE);
+      const LocoCtx c = locate<TABLE>(p, map, t.tile, TILE);
 #pragma unroll
       for (int u = 0; u < U; ++u) load_group<TBC, U, GATE>(q == 0 ? g0 : g1, u, c, tid, true);
       (q == 0 ? e0_0 : e0_1) = c.e0;
@@ -207,7 +210,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
   auto look_up_next = [&](int i) {
     const Ticket t = ticket_at(s_tk, i + AH);
     have_next = t.tile < p.ntiles;
-    if (have_next) cn = locate(p, lane_begin, t.tile, TILE);
+    if (have_next) cn = locate<TABLE>(p, map, t.tile, TILE);
   };
   look_up_next(0);
   LocoDeferred<U> hist[kDefer];
@@ -223,10 +226,11 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
     if (!pending) return false;
     uint32_t mask_packed = 0, excl_packed[(U + 1) / 2], ovf = 0;
     {
-      float* const cres = p.t[ck].residual;
-      const uint64_t cn_n = p.t[ck].n;
+      const LocoTensorDesc cd = tensor_at<TABLE>(p, ck);
+      float* const cres = cd.residual;
+      const uint64_t cn_n = cd.n;
       const bool full = ce0 + TILE <= cn_n;
-      const bool gate = GATE && p.t[ck].theta != nullptr;
+      const bool gate = GATE && cd.theta != nullptr;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
        if (have_cur) {
@@ -241,7 +245,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
           tv[i] = 0.0f;
           if (GATE) tv[i] = __uint_as_float(get_u32(i < 4 ? g.t0[GATE ? u : 0] : g.t1[GATE ? u : 0], i & 3));
         }
-        if (!vec) element_tail(p.t[ck].delta, cres, gate ? p.t[ck].theta : nullptr, e, cn_n, dv, rv, tv);
+        if (!vec) element_tail(cd.delta, cres, gate ? cd.theta : nullptr, e, cn_n, dv, rv, tv);
         float a[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) a[i] = dv[i] + rv[i];
@@ -265,7 +269,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
           }
           if (GM == 2) {
             // selected iff fp8(theta * s) != fp8((theta - a) * s)
-            const float is = p.t[ck].inv_scale;
+            const float is = cd.inv_scale;
             float y0[8], y1[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -346,8 +350,9 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
       const uint32_t tile_cnt = s_tcnt[oi & 1];
       const bool overflowed = s_tovf[oi & 1] != 0u;
       const uint64_t cap = p.capacity;
-      const uint32_t base = p.t[od.k].index_base;
-      float* const ores = p.t[od.k].residual;
+      const LocoTensorDesc td = tensor_at<TABLE>(p, od.k);
+      const uint32_t base = td.index_base;
+      float* const ores = td.residual;
       const uint32_t* wexcl = s_wexcl + (oi & (kWexclRing - 1)) * NSEG;
       if (!overflowed) {
         // entry j of the tile lies in the last wave-group q whose prefix is <= j
@@ -438,30 +443,35 @@ constexpr int kLocoNW = kLocoTB / 64;
 
 uint32_t loco_tile_elems(int gm) { return kLocoTB * loco_u(gm) * 8; }
 
-template <int GM>
+template <int GM, bool TABLE>
 static hipError_t launch_loco_form(const LocoParams& p, hipStream_t stream) {
-  const void* fn = (const void*)loco_kernel<kLocoNW, loco_u(GM), GM>;
-  const int grid_cap = persistent_grid(fn, (kLocoNW + 1) * 64);
+  const int grid_cap =
+      persistent_grid((const void*)loco_kernel<kLocoNW, loco_u(GM), GM, TABLE>, (kLocoNW + 1) * 64);
   if (grid_cap <= 0) return hipErrorInvalidConfiguration;
   const uint32_t grid = p.ntiles < (uint32_t)grid_cap ? p.ntiles : (uint32_t)grid_cap;
-  hipLaunchKernelGGL((loco_kernel<kLocoNW, loco_u(GM), GM>), dim3(grid), dim3((kLocoNW + 1) * 64),
-                     0, stream, p);
+  hipLaunchKernelGGL((loco_kernel<kLocoNW, loco_u(GM), GM, TABLE>), dim3(grid),
+                     dim3((kLocoNW + 1) * 64), 0, stream, p);
   return hipGetLastError();
+}
+
+template <bool TABLE>
+static hipError_t launch_loco_gm(const LocoParams& p, hipStream_t stream) {
+  switch (p.gm) {
+    case 0: return launch_loco_form<0, TABLE>(p, stream);
+    case 1: return launch_loco_form<1, TABLE>(p, stream);
+    case 2: return launch_loco_form<2, TABLE>(p, stream);
+    default: return launch_loco_form<3, TABLE>(p, stream);
+  }
 }
 
 hipError_t launch_loco(LocoParams& p, hipStream_t stream) {
   if (p.ntiles == 0) {
     if (p.seg_begin == nullptr || p.ntensors == 0) return hipSuccess;
-    hipLaunchKernelGGL(loco_empty_segments_kernel, dim3(1), dim3(64), 0, stream,
+    hipLaunchKernelGGL(loco_empty_segments_kernel, dim3((uint32_t)(p.ntensors + 63) / 64), dim3(64), 0, stream,
                        (const uint64_t*)p.count, p.seg_begin, (uint32_t)p.ntensors);
     return hipGetLastError();
   }
-  switch (p.gm) {
-    case 0: return launch_loco_form<0>(p, stream);
-    case 1: return launch_loco_form<1>(p, stream);
-    case 2: return launch_loco_form<2>(p, stream);
-    default: return launch_loco_form<3>(p, stream);
-  }
+  return p.table ? launch_loco_gm<true>(p, stream) : launch_loco_gm<false>(p, stream);
 }
 
 }  // namespace pulse

@@ -87,15 +87,18 @@ struct LowpCtx {
   int k;
 };
 
-__device__ __forceinline__ LowpCtx lowp_locate(const LowpParams& p, uint32_t lane_begin,
+template <bool TABLE>
+__device__ __forceinline__ LowpCtx lowp_locate(const LowpParams& p, const TileMap<TABLE, LowpParams>& map,
                                                uint32_t tile, uint32_t tile_elems) {
   LowpCtx c;
-  c.k = owner_of(lane_begin, tile);
-  c.e0 = (uint64_t)(tile - p.tile_begin[c.k]) * tile_elems;
-  c.n = p.t[c.k].n;
-  c.w = p.t[c.k].w_new;
-  c.snap = p.t[c.k].snap;
-  c.sscale = p.t[c.k].snap_scales;
+  const TileOwner o = map.owner(tile);
+  const LowpTensorDesc d = tensor_at<TABLE>(p, o.k);
+  c.k = o.k;
+  c.e0 = (uint64_t)(tile - o.begin) * tile_elems;
+  c.n = d.n;
+  c.w = d.w_new;
+  c.snap = d.snap;
+  c.sscale = d.snap_scales;
   return c;
 }
 
@@ -163,7 +166,7 @@ struct LowpDeferred {
 // e0 + (u * TBC + tid) * 8 ...  The new D values of a group are staged in LDS
 // as 8 bytes (FP8: the codes; MXFP4: the packed codes and the scale byte)
 // until the tile's write-out, kDefer iterations later.
-template <int NW, int U, int DT>
+template <int NW, int U, int DT, bool TABLE>
 __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p) {
   constexpr int TBC = NW * 64;
   constexpr uint32_t TILE = TBC * U * 8;
@@ -172,6 +175,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
   __shared__ uint32_t s_wtot[2 * U * NW];
   __shared__ uint32_t s_wexcl[kLowpWexclRing * U * NW];
   __shared__ uint2 s_vals[kLowpValBufs][U * TBC];
+  __shared__ uint32_t s_begin[TABLE ? kMaxTable : 1];
   static_assert(U * NW <= 64, "block scan runs on one wave");
   static_assert(U <= 4, "masks of all groups are packed into one register");
 
@@ -179,15 +183,16 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
   const int lane = lane_id();
   const int wid = tid >> 6;
 
+  TileMap<TABLE, LowpParams>::fill(p, s_begin);
   if (wid == NW) {
-    scan_wave_loop<U, NW, kLowpResolve>(p, s_tk, s_wtot, s_wexcl, s_excl, nullptr, nullptr, 0u,
+    scan_wave_loop<U, NW, kLowpResolve, TABLE>(p, s_begin, s_tk, s_wtot, s_wexcl, s_excl, nullptr, nullptr, 0u,
                                         nullptr);
     return;
   }
 
   __syncthreads();  // T(0) .. T(kAhead) are in s_tk
   static_assert(kAhead == 1 || kAhead == 2, "one or two register sets");
-  const uint32_t lane_begin = owner_lane_begin(p);
+  const TileMap<TABLE, LowpParams> map(p, s_begin);
   LowpRegs g0[U], g1[U];
   uint64_t e0_0 = 0, e0_1 = 0;
   int k_0 = 0, k_1 = 0;
@@ -195,7 +200,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
   for (int q = 0; q < kAhead; ++q) {
     const Ticket t = ticket_at(s_tk, q);
     if (t.tile < p.ntiles) {
-      const LowpCtx c = lowp_locate(p, lane_begin, t.tile, TILE);
+      const LowpCtx c = lowp_locate<TABLE>(p, map, t.tile, TILE);
       const bool full = c.e0 + TILE <= c.n;
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -210,7 +215,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
     const Ticket t = ticket_at(s_tk, i + kAhead);
     have_next = t.tile < p.ntiles;
     if (have_next) {
-      cn = lowp_locate(p, lane_begin, t.tile, TILE);
+      cn = lowp_locate<TABLE>(p, map, t.tile, TILE);
       next_full = cn.e0 + TILE <= cn.n;
     }
   };
@@ -229,7 +234,8 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
     uint32_t mask_packed = 0, excl_packed[(U + 1) / 2];
     uint2 staged[U];
     if (have_cur) {
-      const uint64_t cn_n = p.t[ck].n;
+      const LowpTensorDesc cd = tensor_at<TABLE>(p, ck);
+      const uint64_t cn_n = cd.n;
       const bool full = ce0 + TILE <= cn_n;
       uint32_t cnt[U];
 #pragma unroll
@@ -243,7 +249,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
         }
         uint32_t m = 0;
         if (DT == kDtypeFp8) {
-          const float is = p.t[ck].inv_scale;
+          const float is = cd.inv_scale;
           float y[8];
 #pragma unroll
           for (int i = 0; i < 8; ++i) y[i] = x[i] * is;
@@ -286,7 +292,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
       const uint64_t tile_excl = s_excl[oi & 1];
       const uint32_t* wexcl = s_wexcl + (oi & (kLowpWexclRing - 1)) * U * NW;
       const uint64_t cap = p.capacity;
-      const uint32_t base = p.t[od.k].index_base;
+      const uint32_t base = tensor_at<TABLE>(p, od.k).index_base;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         uint32_t mm = (od.mask >> (8 * u)) & 0xFFu;
@@ -409,25 +415,29 @@ __global__ void lowp_empty_segments_kernel(const uint64_t* count, uint64_t* seg_
 
 uint32_t lowp_tile_elems() { return kLowpNW * 64 * kLowpU * 8; }
 
+template <int DT, bool TABLE>
+static hipError_t launch_lowp_form(const LowpParams& p, hipStream_t stream) {
+  const int grid_cap = persistent_grid((const void*)encode_lowp_kernel<kLowpNW, kLowpU, DT, TABLE>,
+                                       (kLowpNW + 1) * 64);
+  if (grid_cap <= 0) return hipErrorInvalidConfiguration;
+  const uint32_t grid = p.ntiles < (uint32_t)grid_cap ? p.ntiles : (uint32_t)grid_cap;
+  hipLaunchKernelGGL((encode_lowp_kernel<kLowpNW, kLowpU, DT, TABLE>), dim3(grid),
+                     dim3((kLowpNW + 1) * 64), 0, stream, p);
+  return hipGetLastError();
+}
+
 hipError_t launch_encode_lowp(int dtype, LowpParams& p, hipStream_t stream) {
   if (p.ntiles == 0) {
     if (p.seg_begin == nullptr || p.ntensors == 0) return hipSuccess;
-    hipLaunchKernelGGL(lowp_empty_segments_kernel, dim3(1), dim3(64), 0, stream,
+    hipLaunchKernelGGL(lowp_empty_segments_kernel, dim3((uint32_t)(p.ntensors + 63) / 64), dim3(64), 0, stream,
                        (const uint64_t*)p.count, p.seg_begin, (uint32_t)p.ntensors);
     return hipGetLastError();
   }
-  const void* fn = dtype == kDtypeFp8 ? (const void*)encode_lowp_kernel<kLowpNW, kLowpU, kDtypeFp8>
-                                      : (const void*)encode_lowp_kernel<kLowpNW, kLowpU, kDtypeMxfp4>;
-  const int grid_cap = persistent_grid(fn, (kLowpNW + 1) * 64);
-  if (grid_cap <= 0) return hipErrorInvalidConfiguration;
-  const uint32_t grid = p.ntiles < (uint32_t)grid_cap ? p.ntiles : (uint32_t)grid_cap;
-  if (dtype == kDtypeFp8)
-    hipLaunchKernelGGL((encode_lowp_kernel<kLowpNW, kLowpU, kDtypeFp8>), dim3(grid),
-                       dim3((kLowpNW + 1) * 64), 0, stream, p);
-  else
-    hipLaunchKernelGGL((encode_lowp_kernel<kLowpNW, kLowpU, kDtypeMxfp4>), dim3(grid),
-                       dim3((kLowpNW + 1) * 64), 0, stream, p);
-  return hipGetLastError();
+  if (p.table)
+    return dtype == kDtypeFp8 ? launch_lowp_form<kDtypeFp8, true>(p, stream)
+                              : launch_lowp_form<kDtypeMxfp4, true>(p, stream);
+  return dtype == kDtypeFp8 ? launch_lowp_form<kDtypeFp8, false>(p, stream)
+                            : launch_lowp_form<kDtypeMxfp4, false>(p, stream);
 }
 
 hipError_t launch_apply_lowp(const LowpApplyParams& p, hipStream_t stream) {

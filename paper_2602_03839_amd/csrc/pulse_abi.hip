@@ -62,6 +62,75 @@ bool refresh_mirrors(const pulse_encode_tensor& d) {
 
 uint32_t tiles_for(uint64_t n, uint32_t tile) { return (uint32_t)((n + tile - 1) / tile); }
 
+// The next launch's tensors, from tensors[0 .. left): their first tiles and
+// descriptors (fill(i, desc) writes tensor i's) go to p.t where all that are
+// left fit there, else up to kMaxTable of them to the workspace's table, by
+// launches on the stream.  *taken receives their number.
+template <typename Params, typename Tensor, typename Fill>
+int gather_launch(Params& p, const Tensor* tensors, uint32_t left, uint32_t tile, uint32_t max_tiles,
+                  Fill fill, void* workspace, hipStream_t stream, uint32_t* taken) {
+  const bool table = left > (uint32_t)pulse::kMaxBatch;
+  const uint32_t room = table ? (uint32_t)pulse::kMaxTable : (uint32_t)pulse::kMaxBatch;
+  uint32_t tiles = 0, k = 0;
+  while (k < left && k < room) {
+    const uint64_t nt = tiles_for(tensors[k].n, tile);
+    if (k > 0 && (uint64_t)tiles + nt > max_tiles) break;
+    if (!table) {
+      p.tile_begin[k] = tiles;
+      fill(k, p.t[k]);
+    }
+    tiles += (uint32_t)nt;
+    ++k;
+  }
+  *taken = k;
+  p.ntensors = (int)k;
+  p.ntiles = tiles;
+  if (!table) {
+    p.tile_begin[k] = tiles;
+    return PULSE_OK;
+  }
+  // the table: the first tiles (two per word), then the descriptors
+  typedef typename Params::Desc Desc;
+  static_assert(sizeof(Desc) % 8 == 0, "descriptors are whole words");
+  static_assert(((size_t)pulse::kMaxTable + 1) / 2 + pulse::kMaxTable * (sizeof(Desc) / 8) <= pulse::kTableWords,
+                "the table holds every tensor of a launch");
+  uint64_t* const at = (uint64_t*)workspace + pulse::kTableOffsetWords;
+  const uint32_t nb = (k + 1) / 2;
+  p.table_begin = (const uint32_t*)at;
+  p.table = (const Desc*)(at + nb);
+  pulse::PutWords w;
+  w.dst = at;
+  w.n = 0;
+  int rc = PULSE_OK;
+  auto put = [&](uint64_t x) {
+    w.w[w.n++] = x;
+    if (w.n == pulse::PutWords::kRoom) {
+      rc = hip_status(pulse::launch_put_words(w, stream), "tensor table launch");
+      w.dst += w.n;
+      w.n = 0;
+    }
+    return rc;
+  };
+  uint32_t begin = 0;
+  for (uint32_t i = 0; i < nb; ++i) {
+    uint64_t x = 0;
+    for (uint32_t j = 2 * i; j < 2 * i + 2 && j < k; ++j) {
+      x |= (uint64_t)begin << (32 * (j & 1));
+      begin += tiles_for(tensors[j].n, tile);
+    }
+    if (put(x)) return rc;
+  }
+  for (uint32_t i = 0; i < k; ++i) {
+    Desc d{};
+    fill(i, d);
+    uint64_t x[sizeof(Desc) / 8];
+    memcpy(x, &d, sizeof d);
+    for (uint64_t v : x)
+      if (put(v)) return rc;
+  }
+  return hip_status(pulse::launch_put_words(w, stream), "tensor table launch");
+}
+
 // Largest two-pass launch (in kL2Tile-element tiles) whose staging area fits a
 // workspace of `bytes` bytes; 0 if none does.  Capped so that a launch's grid
 // stays below 2^31 blocks.
@@ -236,26 +305,23 @@ int encode_batch(const pulse_encode_tensor* tensors, uint32_t ntensors, uint32_t
     p.capacity = capacity;
     p.count = count;
     p.seg_begin = seg_begin ? seg_begin + t0 : nullptr;
-    uint32_t tiles = 0;
-    int k = 0;
-    while (t0 + k < ntensors && k < pulse::kMaxBatch) {
-      const pulse_encode_tensor& d = tensors[t0 + k];
-      const uint32_t nt = tiles_for(d.n, tile);
-      if (k > 0 && (uint64_t)tiles + nt > pulse::kMaxTilesPerLaunch) break;
-      p.tile_begin[k] = tiles;
-      p.t[k].w_new = d.w_new;
-      p.t[k].snap = d.snap;
-      p.t[k].refresh = d.refresh;
-      p.t[k].n = d.n;
-      p.t[k].index_base = d.index_base;
-      p.t[k].mirror = d.refresh && refresh_mirrors(d) ? 1u : 0u;
-      tiles += nt;
-      ++k;
-    }
-    p.tile_begin[k] = tiles;
-    p.ntensors = k;
-    p.ntiles = tiles;
-    if (int rc = hip_status(pulse::launch_encode(p, (hipStream_t)stream), "encode launch")) return rc;
+    bool refresh = false;
+    uint32_t k = 0;
+    if (int rc = gather_launch(p, tensors + t0, ntensors - t0, tile, pulse::kMaxTilesPerLaunch,
+                               [&](uint32_t i, pulse::EncodeTensorDesc& e) {
+                                 const pulse_encode_tensor& d = tensors[t0 + i];
+                                 e.w_new = d.w_new;
+                                 e.snap = d.snap;
+                                 e.refresh = d.refresh;
+                                 e.n = d.n;
+                                 e.index_base = d.index_base;
+                                 e.mirror = d.refresh && refresh_mirrors(d) ? 1u : 0u;
+                                 refresh |= d.refresh != nullptr;
+                               },
+                               workspace, (hipStream_t)stream, &k))
+      return rc;
+    if (int rc = hip_status(pulse::launch_encode(p, refresh, (hipStream_t)stream), "encode launch"))
+      return rc;
     t0 += k;
   }
   return ok();
@@ -420,25 +486,21 @@ int loco_batch(const pulse_loco_tensor* tensors, const float* inv_scales, uint32
         continue;
       }
     }
-    while (t0 + k < ntensors && k < pulse::kMaxBatch) {
-      const pulse_loco_tensor& d = tensors[t0 + k];
-      const uint32_t nt = tiles_for(d.n, tile);
-      if (k > 0 && (uint64_t)tiles + nt > pulse::kMaxTilesPerLaunch) break;
-      p.tile_begin[k] = tiles;
-      p.t[k].delta = d.delta;
-      p.t[k].residual = d.residual;
-      p.t[k].theta = d.theta;
-      p.t[k].n = d.n;
-      p.t[k].index_base = d.index_base;
-      p.t[k].inv_scale = inv_scales ? inv_scales[t0 + k] : 1.0f;
-      tiles += nt;
-      ++k;
-    }
-    p.tile_begin[k] = tiles;
-    p.ntensors = k;
-    p.ntiles = tiles;
+    uint32_t taken = 0;
+    if (int rc = gather_launch(p, tensors + t0, ntensors - t0, tile, pulse::kMaxTilesPerLaunch,
+                               [&](uint32_t i, pulse::LocoTensorDesc& e) {
+                                 const pulse_loco_tensor& d = tensors[t0 + i];
+                                 e.delta = d.delta;
+                                 e.residual = d.residual;
+                                 e.theta = d.theta;
+                                 e.n = d.n;
+                                 e.index_base = d.index_base;
+                                 e.inv_scale = inv_scales ? inv_scales[t0 + i] : 1.0f;
+                               },
+                               workspace, (hipStream_t)stream, &taken))
+      return rc;
     if (int rc = hip_status(pulse::launch_loco(p, (hipStream_t)stream), "loco launch")) return rc;
-    t0 += k;
+    t0 += taken;
   }
   return ok();
 }
@@ -739,25 +801,19 @@ int pulse_encode_lowp_batch(int dtype, const pulse_lowp_tensor* tensors, uint32_
     p.capacity = capacity;
     p.count = count;
     p.seg_begin = seg_begin ? seg_begin + t0 : nullptr;
-    uint32_t tiles = 0;
-    int k = 0;
-    while (t0 + k < ntensors && k < pulse::kMaxBatch) {
-      const pulse_lowp_tensor& d = tensors[t0 + k];
-      const uint32_t nt = tiles_for(d.n, tile);
-      if (k > 0 && (uint64_t)tiles + nt > pulse::kMaxTilesPerLaunch) break;
-      p.tile_begin[k] = tiles;
-      p.t[k].w_new = d.w_new;
-      p.t[k].snap = d.snap;
-      p.t[k].snap_scales = d.snap_scales;
-      p.t[k].n = d.n;
-      p.t[k].index_base = d.index_base;
-      p.t[k].inv_scale = d.inv_scale;
-      tiles += nt;
-      ++k;
-    }
-    p.tile_begin[k] = tiles;
-    p.ntensors = k;
-    p.ntiles = tiles;
+    uint32_t k = 0;
+    if (int rc = gather_launch(p, tensors + t0, ntensors - t0, tile, pulse::kMaxTilesPerLaunch,
+                               [&](uint32_t i, pulse::LowpTensorDesc& e) {
+                                 const pulse_lowp_tensor& d = tensors[t0 + i];
+                                 e.w_new = d.w_new;
+                                 e.snap = d.snap;
+                                 e.snap_scales = d.snap_scales;
+                                 e.n = d.n;
+                                 e.index_base = d.index_base;
+                                 e.inv_scale = d.inv_scale;
+                               },
+                               workspace, (hipStream_t)stream, &k))
+      return rc;
     if (int rc = hip_status(pulse::launch_encode_lowp(dtype, p, (hipStream_t)stream),
                             "encode_lowp launch"))
       return rc;

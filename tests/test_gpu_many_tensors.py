@@ -1,0 +1,162 @@
+"""GPU parity of batches with more tensors than a launch's kernel arguments hold
+(64): their descriptors go through the workspace's table, up to 1,024 tensors a
+launch.  Encode (plain, mirrored, with the patch overflowing), the gate
+sparsifier and the FP8/MXFP4 encodes against the oracle tensor by tensor, bit
+for bit; the numbers of tensors sit at the table's edges."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2602_03839_amd import pulse
+from tests.gpu_helpers import counter, dev, h16, h32, hf32, read_count
+
+pytestmark = pytest.mark.gpu
+
+COUNTS = [64, 65, 129, 1024, 1025, 1100]
+
+
+def make_sizes(rng, T, big):
+    """Mostly tiny and some empty tensors, a few of `big` elements and more, empty ones at both ends."""
+    sizes = rng.integers(0, 60, T)
+    sizes[rng.random(T) < 0.2] = 0
+    for at in (T // 3, T // 2, T - 2):
+        sizes[at] = big + int(rng.integers(0, 100))
+    sizes[0] = sizes[-1] = 0
+    return [int(x) for x in sizes]
+
+
+def f32(a):
+    return dev(a) if a.size else torch.empty(0, dtype=torch.float32, device="cuda")
+
+
+def i16(a):
+    return dev(a) if a.size else torch.empty(0, dtype=torch.int16, device="cuda")
+
+
+@pytest.fixture(scope="module")
+def ws():
+    return pulse.workspace()
+
+
+def buffers(cap, T, val_dtype):
+    return (torch.zeros(max(cap, 1), dtype=torch.int32, device="cuda"),
+            torch.zeros(max(cap, 1), dtype=val_dtype, device="cuda"), counter(0),
+            torch.full((T,), -1, dtype=torch.int64, device="cuda"))
+
+
+@pytest.mark.parametrize("cap_frac", [None, 1.0, 0.5])
+@pytest.mark.parametrize("T", COUNTS)
+def test_encode_many_tensors(ws, T, cap_frac):
+    """cap_frac None: no refresh; else mirrored refresh with that share of the patch's room."""
+    rng = np.random.default_rng(T)
+    sizes = make_sizes(rng, T, 40_000)
+    host, descs, refs, base = [], [], [], 0
+    for n in sizes:
+        w = rng.normal(0, 0.1, n).astype(np.float32)
+        s = oracle.cast(w) ^ (rng.random(n) < 0.03).astype(np.uint16)
+        s_d = i16(s)
+        r_d = s_d.clone() if cap_frac is not None else None
+        host.append((w, s, base))
+        refs.append(r_d)
+        descs.append(pulse.EncodeTensor(f32(w), s_d, r_d, base, mirrors_snap=r_d is not None))
+        base += n
+    nnz = sum(int((oracle.cast(w) != s).sum()) for w, s, _ in host)
+    cap = nnz if cap_frac is None else int(nnz * cap_frac)
+    o_idx, o_val, o_seg, cnt = np.zeros(cap, np.uint32), np.zeros(cap, np.uint16), [], 0
+    o_refs = []
+    for w, s, b in host:
+        o_seg.append(cnt)
+        r = s.copy()
+        cnt, _, _ = oracle.encode(w, s, index_base=b, capacity=cap, count_in=cnt, idx_out=o_idx,
+                                  val_out=o_val, refresh=r)
+        o_refs.append(r)
+    idx, val, count, seg = buffers(cap, T, torch.int16)
+    pulse.EncodeBatch(descs)(idx, val, count, ws, seg_begin=seg, capacity=cap)
+    torch.cuda.synchronize()
+    assert read_count(count) == cnt == nnz
+    np.testing.assert_array_equal(seg.cpu().numpy(), np.array(o_seg))
+    np.testing.assert_array_equal(h32(idx)[:cap], o_idx)
+    np.testing.assert_array_equal(h16(val)[:cap], o_val)
+    for t, (r_d, r) in enumerate(zip(refs, o_refs)):
+        if r_d is not None and r.size:
+            np.testing.assert_array_equal(h16(r_d), r, err_msg=str(t))
+    pulse.check_workspace(ws)
+
+
+@pytest.mark.parametrize("T", COUNTS)
+def test_gate_many_tensors(ws, T):
+    rng = np.random.default_rng(T + 1)
+    sizes = make_sizes(rng, T, 20_000)
+    descs, res, want, o_seg, cnt = [], [], [], [], 0
+    cap = sum(sizes)
+    o_idx, o_val = np.zeros(cap, np.uint32), np.zeros(cap, np.float32)
+    for n in sizes:
+        th = rng.normal(0, 0.1, n).astype(np.float32)
+        d = rng.normal(0, 2e-4, n).astype(np.float32)
+        e = rng.normal(0, 5e-5, n).astype(np.float32)
+        e_d = f32(e)
+        descs.append(pulse.LocoTensor(f32(d), e_d, f32(th), 0))
+        o_seg.append(cnt)
+        if n:
+            k, oi, ov = oracle.loco(d, e, 0.0, theta=th)
+            o_idx[cnt:cnt + k], o_val[cnt:cnt + k] = oi[:k], ov[:k]
+            cnt += k
+        res.append(e_d)
+        want.append(e)
+    idx, val, count, seg = buffers(cap, T, torch.float32)
+    pulse.LocoBatch(descs)(0.0, idx, val, count, ws, seg_begin=seg)
+    torch.cuda.synchronize()
+    assert read_count(count) == cnt
+    np.testing.assert_array_equal(seg.cpu().numpy(), np.array(o_seg))
+    np.testing.assert_array_equal(h32(idx)[:cnt], o_idx[:cnt])
+    np.testing.assert_array_equal(hf32(val)[:cnt].view(np.uint32), o_val[:cnt].view(np.uint32))
+    for t, (r_d, r) in enumerate(zip(res, want)):
+        np.testing.assert_array_equal(hf32(r_d).view(np.uint32), r.view(np.uint32), err_msg=str(t))
+
+
+@pytest.mark.parametrize("dtype", [pulse.FP8_E4M3, pulse.MXFP4])
+@pytest.mark.parametrize("T", COUNTS)
+def test_lowp_many_tensors(ws, T, dtype):
+    rng = np.random.default_rng(T + 2)
+    fp8 = dtype == pulse.FP8_E4M3
+    sizes = make_sizes(rng, T, 50_000)
+    descs, o_seg, cnt = [], [], 0
+    cap = sum(sizes)
+    o_idx, o_val = np.zeros(cap, np.uint32), np.zeros(cap, np.uint8 if fp8 else np.uint16)
+    for t, n in enumerate(sizes):
+        w = rng.normal(0, 0.1, n).astype(np.float32)
+        w2 = (w + rng.normal(0, 1e-3, n)).astype(np.float32)
+        scale = 100.0 + t
+        o_seg.append(cnt)
+        if fp8:
+            snap, sc = oracle.cast_fp8(w, scale), None
+            k, oi, ov = oracle.encode_fp8(w2, snap, scale) if n else (0, o_idx, o_val)
+        else:
+            snap, sc = oracle.cast_mxfp4(w) if n else (np.zeros(0, np.uint8), np.zeros(0, np.uint8))
+            k, oi, ov = oracle.encode_mxfp4(w2, snap, sc) if n else (0, o_idx, o_val)
+        o_idx[cnt:cnt + k], o_val[cnt:cnt + k] = oi[:k], ov[:k]
+        cnt += k
+        u8 = lambda a: dev(a) if a.size else torch.empty(0, dtype=torch.uint8, device="cuda")  # noqa: E731
+        descs.append(pulse.LowpTensor(f32(w2), u8(snap), None if fp8 else u8(sc), 0, scale))
+    idx, val, count, seg = buffers(cap, T, torch.uint8 if fp8 else torch.int16)
+    pulse.EncodeLowpBatch(dtype, descs)(idx, val, count, ws, seg_begin=seg)
+    torch.cuda.synchronize()
+    assert read_count(count) == cnt
+    np.testing.assert_array_equal(seg.cpu().numpy(), np.array(o_seg))
+    np.testing.assert_array_equal(h32(idx)[:cnt], o_idx[:cnt])
+    got = val.cpu().numpy() if fp8 else h16(val)
+    np.testing.assert_array_equal(got[:cnt], o_val[:cnt])
+
+
+@pytest.mark.parametrize("T", [130, 1030])
+def test_all_empty_many_tensors(ws, T):
+    """No elements at all: every segment starts at the append position."""
+    e = torch.empty(0, dtype=torch.float32, device="cuda")
+    s = torch.empty(0, dtype=torch.int16, device="cuda")
+    idx, val, count, seg = buffers(4, T, torch.int16)
+    count.fill_(3)
+    pulse.EncodeBatch([pulse.EncodeTensor(e, s)] * T)(idx, val, count, ws, seg_begin=seg)
+    torch.cuda.synchronize()
+    assert read_count(count) == 3
+    assert bool((seg == 3).all())
