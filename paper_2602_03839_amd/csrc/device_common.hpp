@@ -190,7 +190,13 @@ constexpr uint64_t kNoTicket = kTicketMask;
 // Tiles per ticket.  A chunk's tiles are processed in consecutive iterations,
 // so the chunk's last aggregate appears kChunk - 1 iterations after its first;
 // with kChunk <= RES + 1 later tiles never wait for it at resolution time.
-constexpr uint32_t kChunk = 4;
+// Two, measured against four, three and one (us; the encode with RES 2, the
+// lower-precision encode with RES 4): 0.5B set in place 645 / 693 / 685 / 671,
+// mirrored 7B set 9,274 / 9,556 / 9,452 / 9,847, FP8 0.5B set 468 / 508 / - / -.
+// Fewer tiles per ticket keep the chip's reads closer to address order and the
+// last wave of tiles shorter, until the one ticket counter (70-88M draws a
+// second) becomes the bound.
+constexpr uint32_t kChunk = 2;
 
 // Tiles whose loads a block keeps in flight: while a block computes tile T(i),
 // the loads of T(i + 1) .. T(i + kAhead) are outstanding.  A tile is 90 KiB

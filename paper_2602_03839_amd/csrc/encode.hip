@@ -103,8 +103,11 @@ __device__ __forceinline__ void load_group(TileRegs<TBC, U>& r, int u, const Til
 // computing iteration i + kDefer + 1 at different times, so the slot may be
 // refilled only from iteration i + kDefer + 2 on, after the next barrier.
 constexpr uint32_t kSegCap = 64;
-// Iterations from a tile's compute to its resolution and to its write-out.
-constexpr int kResolve = 4;
+// Iterations from a tile's compute to its resolution and to its write-out.  Two
+// iterations find the predecessors published with two tiles per ticket, and a
+// launch drains in three: the 0.5B set in place took 645 us (4: 678, 3: 663),
+// the mirrored 7B set the same within 0.4%.
+constexpr int kResolve = 2;
 constexpr int kDefer = kResolve + 1;
 constexpr int kWexclRing = wexcl_ring(kResolve);
 constexpr int kSegSlots = kDefer + 2;
