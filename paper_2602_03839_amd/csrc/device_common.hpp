@@ -171,12 +171,17 @@ __device__ __forceinline__ uint64_t draw_ticket(uint64_t* ws) {
                                 __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Called by one thread per block after its last draw.  The acquire-release
-// increment orders every block's draws before the reset done by the last one.
+// Called by one thread per block after its last draw, by the thread that drew
+// or after a barrier that followed the draw's return.  Every draw has returned
+// before the increment is issued (the wait), and the last block resets the
+// counter only after its own increment has returned, so all draws precede the
+// reset.  No ordering of other memory is needed, so the increment is relaxed:
+// a release at device scope would write back the XCD's whole L2 per block.
 __device__ __forceinline__ void finish_launch(uint64_t* ws, uint64_t g0, uint32_t ntiles,
                                               uint32_t nblocks) {
+  __builtin_amdgcn_s_waitcnt(0);  // every counter at zero
   const uint64_t d =
-      __hip_atomic_fetch_add(ws + kWordDone, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_add(ws + kWordDone, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (d == nblocks - 1) {
     __hip_atomic_store(ws + kWordDone, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(ws + kWordTicket, ((g0 + ntiles) & kSeqMask) << kTicketBits,
@@ -625,6 +630,93 @@ __device__ void scan_wave_loop(const Params& p, const uint32_t* s_begin, uint64_
     hist[0] = now;
   }
   if (lane == 0) finish_launch(p.ws, g0, p.ntiles, gridDim.x);
+}
+
+// ---------------------------------------------------------------- one tile per block
+//
+// Small calls.  The persistent kernels' pipeline needs tens of tiles per block
+// to pay for its fill and drain, and a small call has less than one: there a
+// block draws one ticket, computes its one tile with every wave and resolves
+// it at once.  Tickets still number the tiles, so a block waits only for
+// blocks that are running.
+constexpr int kOneNW = 16;  // waves per block
+constexpr int kOneLK = 4;   // look-back window: 256 predecessors read at once
+
+// Tile and owner of this block.  Every thread calls it; s_c is LDS.
+__device__ __forceinline__ Ticket one_ticket(uint64_t* ws, uint64_t* s_c) {
+  if (threadIdx.x == 0) *s_c = draw_ticket(ws);
+  __syncthreads();
+  return ticket_at(s_c, 0);
+}
+
+template <bool TABLE, typename Params>
+__device__ __forceinline__ TileOwner one_owner(const Params& p, uint32_t tile) {
+  if (!TABLE) {
+    const TileMap<false, Params> map(p, nullptr);
+    return map.owner(tile);
+  }
+  // the search of TileMap in memory: a block looks up one tile only
+  const uint32_t n = (uint32_t)p.ntensors, stride = (n + 63) / 64;
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t c = lane * stride < n ? p.table_begin[lane * stride] : ~0u;
+  const uint32_t g = 63u - (uint32_t)__builtin_clzll(__ballot(c <= tile));
+  const uint32_t q = g * stride + lane;
+  const uint32_t v = lane < stride && q < n ? p.table_begin[q] : ~0u;
+  const int f = 63 - __builtin_clzll(__ballot(v <= tile));
+  return TileOwner{(int)(g * stride) + f, (uint32_t)__builtin_amdgcn_readlane((int)v, f)};
+}
+
+// Positions of a tile whose wave-groups (U groups x NW waves, group-major) hold
+// s_wtot[] entries (written before; this call starts with a barrier).  Every
+// thread calls it; the tile's exclusive patch position is returned, wexcl[u]
+// receives the entries of the tile before this wave's group u, *total the
+// tile's count.  Wave 0 publishes and looks back, and writes *count and the
+// segment starts as scan_wave_loop does; the last wave counts the block out.
+template <int U, bool TABLE, typename Params>
+__device__ __forceinline__ uint64_t one_resolve(const Params& p, const Ticket& tk, const TileOwner& own,
+                                                const uint32_t* s_wtot, uint64_t* s_excl,
+                                                uint32_t (&wexcl)[U], uint32_t* total) {
+  static_assert(U * kOneNW <= 64, "one lane per wave-group");
+  const int lane = lane_id();
+  const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  __syncthreads();
+  const uint32_t v = lane < U * kOneNW ? s_wtot[lane] : 0u;
+  const uint32_t incl = wave_incl_scan(v);
+#pragma unroll
+  for (int u = 0; u < U; ++u) wexcl[u] = __builtin_amdgcn_readlane((int)(incl - v), u * kOneNW + wid);
+  const uint32_t agg = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+  *total = agg;
+  if (wid == 0) {
+    uint64_t excl;
+    if (tk.tile == 0) {
+      excl = *p.count;  // append position, written by an earlier call
+      if (lane == 0) status_publish(p.ws, tk.seq, kFlagPrefix, excl + agg);
+    } else {
+      if (lane == 0) status_publish(p.ws, tk.seq, kFlagAggregate, agg);
+      LookWindow<kOneLK> win;
+      look_back_issue<kOneLK>(p.ws, tk, (int64_t)tk.tile - 1, win);
+      excl = look_back<kOneLK>(p.ws, tk, win);
+      if (lane == 0) status_publish(p.ws, tk.seq, kFlagPrefix, excl + agg);
+    }
+    if (lane == 0) {
+      *s_excl = excl;
+      if (tk.tile == p.ntiles - 1) *p.count = excl + agg;
+      if (p.seg_begin) {
+        const uint32_t* const begins = TABLE ? p.table_begin : nullptr;
+        auto begin = [&](int k) { return TABLE ? begins[k] : p.tile_begin[k]; };
+        if (own.begin == tk.tile) {
+          for (int kk = own.k; kk >= 0 && begin(kk) == tk.tile; --kk) p.seg_begin[kk] = excl;
+        }
+        if (tk.tile == p.ntiles - 1) {
+          for (int kk = own.k + 1; kk < p.ntensors; ++kk) p.seg_begin[kk] = excl + agg;
+        }
+      }
+    }
+  } else if (wid == kOneNW - 1 && lane == 0) {
+    finish_launch(p.ws, (tk.seq - tk.tile) & kSeqMask, p.ntiles, gridDim.x);
+  }
+  __syncthreads();
+  return *s_excl;
 }
 
 // ---------------------------------------------------------------- loads

@@ -380,6 +380,67 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
   }
 }
 
+// One tile per block (device_common.hpp): U groups of 8 elements per lane.
+template <int U, bool REFRESH, bool TABLE>
+__global__ __launch_bounds__(kOneNW * 64) void encode_one_kernel(EncodeParams p) {
+  constexpr int TBC = kOneNW * 64;
+  constexpr uint32_t TILE = TBC * U * 8;
+  __shared__ uint64_t s_c, s_excl;
+  __shared__ uint32_t s_wtot[U * kOneNW];
+  const int tid = threadIdx.x;
+  const Ticket tk = one_ticket(p.ws, &s_c);
+  const TileOwner own = one_owner<TABLE>(p, tk.tile);
+  const EncodeTensorDesc d = tensor_at<TABLE>(p, own.k);
+  TileCtx c;
+  c.e0 = (uint64_t)(tk.tile - own.begin) * TILE;
+  c.n = d.n;
+  c.w = d.w_new;
+  c.s = d.snap;
+  const bool full = c.e0 + TILE <= c.n;
+  TileRegs<TBC, U> r;
+#pragma unroll
+  for (int u = 0; u < U; ++u) load_group<TBC, U>(r, u, c, tid, full);
+  uint32_t hb[U][4], mask[U], excl[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    hb[u][0] = bf16x2_rne(r.a[u].x, r.a[u].y);
+    hb[u][1] = bf16x2_rne(r.a[u].z, r.a[u].w);
+    hb[u][2] = bf16x2_rne(r.b[u].x, r.b[u].y);
+    hb[u][3] = bf16x2_rne(r.b[u].z, r.b[u].w);
+    mask[u] = diff2(hb[u][0], r.c[u].x) | (diff2(hb[u][1], r.c[u].y) << 2) |
+              (diff2(hb[u][2], r.c[u].z) << 4) | (diff2(hb[u][3], r.c[u].w) << 6);
+    const uint32_t cnt = (uint32_t)__builtin_popcount(mask[u]);
+    const uint32_t incl = wave_incl_scan(cnt);
+    excl[u] = incl - cnt;
+    if (lane_id() == 63) s_wtot[u * kOneNW + (tid >> 6)] = incl;
+  }
+  uint32_t wexcl[U], total;
+  const uint64_t tile_excl = one_resolve<U, TABLE>(p, tk, own, s_wtot, &s_excl, wexcl, &total);
+  const uint64_t cap = p.capacity;
+  // whole-run refresh, as in encode_kernel, where every entry is emitted
+  const bool sector = REFRESH && d.refresh != nullptr && d.mirror != 0u && tile_excl + total <= cap;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint64_t e = c.e0 + (uint64_t)(u * TBC + tid) * 8;
+    const uint32_t run = REFRESH ? or_across_lanes<kSectorLanes>(mask[u]) : 0u;
+    const bool whole = sector && run != 0u && e + 8 <= c.n;
+    if (whole) store16_stream(d.refresh + e, make_uint4(hb[u][0], hb[u][1], hb[u][2], hb[u][3]));
+    uint64_t pos = tile_excl + wexcl[u] + excl[u];
+    uint32_t m = mask[u];
+    while (m) {
+      const int i = __builtin_ctz(m);
+      m &= m - 1;
+      if (pos < cap) {
+        const uint16_t v = bf16_slot(hb[u][0], hb[u][1], hb[u][2], hb[u][3], i);
+        store_nt(p.idx + pos, d.index_base + (uint32_t)(e + i));
+        store_nt(p.val + pos, v);
+        if (REFRESH && !whole && d.refresh) store_nt(d.refresh + e + i, v);
+      }
+      ++pos;
+    }
+  }
+}
+
 // A batch whose tensors are all empty still has to report segment starts.
 __global__ void empty_segments_kernel(const uint64_t* count, uint64_t* seg_begin, uint32_t nseg) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -401,13 +462,28 @@ static hipError_t launch_encode_form(const EncodeParams& p, hipStream_t stream) 
   return hipGetLastError();
 }
 
-hipError_t launch_encode(EncodeParams& p, bool refresh, hipStream_t stream) {
+template <int U, bool REFRESH>
+static hipError_t launch_encode_one_form(const EncodeParams& p, hipStream_t stream) {
+  if (p.table)
+    hipLaunchKernelGGL((encode_one_kernel<U, REFRESH, true>), dim3(p.ntiles), dim3(kOneNW * 64), 0, stream, p);
+  else
+    hipLaunchKernelGGL((encode_one_kernel<U, REFRESH, false>), dim3(p.ntiles), dim3(kOneNW * 64), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_encode(EncodeParams& p, bool refresh, int one, hipStream_t stream) {
   if (p.ntiles == 0) {
     if (p.seg_begin == nullptr || p.ntensors == 0) return hipSuccess;
     hipLaunchKernelGGL(empty_segments_kernel, dim3((uint32_t)(p.ntensors + 63) / 64), dim3(64), 0, stream,
                        (const uint64_t*)p.count, p.seg_begin, (uint32_t)p.ntensors);
     return hipGetLastError();
   }
+  if (one == 1)
+    return refresh ? launch_encode_one_form<1, true>(p, stream) : launch_encode_one_form<1, false>(p, stream);
+  if (one == 2)
+    return refresh ? launch_encode_one_form<2, true>(p, stream) : launch_encode_one_form<2, false>(p, stream);
+  if (one == 4)
+    return refresh ? launch_encode_one_form<4, true>(p, stream) : launch_encode_one_form<4, false>(p, stream);
   if (p.table) return refresh ? launch_encode_form<true, true>(p, stream) : launch_encode_form<false, true>(p, stream);
   return refresh ? launch_encode_form<true, false>(p, stream) : launch_encode_form<false, false>(p, stream);
 }

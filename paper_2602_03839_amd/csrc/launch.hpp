@@ -296,6 +296,8 @@ static_assert(sizeof(OuterParams) < 4096, "kernel argument block too large");
 static_assert(sizeof(LocoParams) < 4096, "kernel argument block too large");
 static_assert(sizeof(ApplyParams) < 4096, "kernel argument block too large");
 
+// Tiles of the one-tile-per-block forms: 1,024 lanes x 8 elements x `groups`.
+constexpr uint32_t one_tile_elems(int groups) { return 1024u * 8u * (uint32_t)groups; }
 uint32_t encode_tile_elems();
 uint32_t loco_tile_elems(int gm);
 // dst[0 .. n) = w[0 .. n), by a kernel that carries the words as arguments.
@@ -307,9 +309,12 @@ struct PutWords {
 };
 static_assert(sizeof(PutWords) < 4096, "kernel argument block too large");
 hipError_t launch_put_words(const PutWords& p, hipStream_t stream);
-// refresh: some tensor of the launch has a copy to refresh
-hipError_t launch_encode(EncodeParams& p, bool refresh, hipStream_t stream);
-hipError_t launch_loco(LocoParams& p, hipStream_t stream);
+// refresh: some tensor of the launch has a copy to refresh.  one: 0 = the
+// persistent kernel (encode_tile_elems()), 1 or 2 = one tile per block, of
+// one_tile_elems(one) elements
+hipError_t launch_encode(EncodeParams& p, bool refresh, int one, hipStream_t stream);
+// one: one tile of one_tile_elems(1) elements per block, else the persistent kernel
+hipError_t launch_loco(LocoParams& p, bool one, hipStream_t stream);
 
 // Two-pass form of the threshold sparsifier (loco2.hip): tiles of kL2Tile
 // elements, each staging up to kL2Cap selected entries; the ordering passes
@@ -335,7 +340,8 @@ hipError_t launch_coo_encode(const CooEncParams& p, hipStream_t stream);
 hipError_t launch_coo_decode(const CooDecParams& p, hipStream_t stream);
 hipError_t launch_outer(const OuterParams& p, hipStream_t stream);
 uint32_t lowp_tile_elems();
-hipError_t launch_encode_lowp(int dtype, LowpParams& p, hipStream_t stream);
+// one: as for launch_encode
+hipError_t launch_encode_lowp(int dtype, LowpParams& p, int one, hipStream_t stream);
 hipError_t launch_apply_lowp(const LowpApplyParams& p, hipStream_t stream);
 hipError_t launch_cast_lowp(int dtype, const float* src, uint64_t n, float inv_scale,
                             uint8_t* codes, uint8_t* scales, hipStream_t stream);

@@ -105,6 +105,56 @@ __device__ __forceinline__ void element_tail(const float* d, const float* r, con
   __builtin_amdgcn_s_waitcnt(0);  // every counter at zero
 }
 
+// Selection mask of a lane's eight sums a: by the gate GM against theta tv, or
+// (GM 0, or a tensor without theta) by |a| >= tau.  For MXFP4 the four lanes of
+// a block take part together: every lane of the wave must call it.
+template <int GM>
+__device__ __forceinline__ uint32_t loco_select(const float (&a)[8], const float (&tv)[8], bool gate,
+                                                float tau, float inv_scale) {
+  uint32_t m = 0;
+  if (gate && GM == 1) {
+    // selected iff bf16(theta) != bf16(theta - a), pairwise on the cvt unit
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t t_lo = __float_as_uint(tv[2 * j]), t_hi = __float_as_uint(tv[2 * j + 1]);
+      const float after_lo = __uint_as_float(t_lo) - a[2 * j];
+      const float after_hi = __uint_as_float(t_hi) - a[2 * j + 1];
+      m |= diff2(bf16x2_rne(t_lo, t_hi),
+                 bf16x2_rne(__float_as_uint(after_lo), __float_as_uint(after_hi)))
+           << (2 * j);
+    }
+  } else if (gate && GM != 0) {
+    float th[8], af[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      th[i] = tv[i];
+      af[i] = th[i] - a[i];
+    }
+    if (GM == 2) {
+      // selected iff fp8(theta * s) != fp8((theta - a) * s)
+      float y0[8], y1[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        y0[i] = th[i] * inv_scale;
+        y1[i] = af[i] * inv_scale;
+      }
+      uint32_t lo0, hi0, lo1, hi1;
+      fp8_codes8(y0, lo0, hi0);
+      fp8_codes8(y1, lo1, hi1);
+      m = fp8_change_mask(lo0, hi0, lo1, hi1);
+    } else {
+      // selected iff (scale, code) of theta's block != that of theta - a
+      uint32_t c0, c1;
+      const uint32_t s0 = mx_view8(th, c0), s1 = mx_view8(af, c1);
+      m = s0 != s1 ? 0xFFu : nibble_change_mask(c0, c1);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m |= (uint32_t)(fabsf(a[i]) >= tau) << i;
+  }
+  return m;
+}
+
 }  // namespace
 
 // Iterations from a tile's compute to its resolution and to its write-out.
@@ -236,7 +286,6 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
        if (have_cur) {
         const uint64_t e = ce0 + (uint64_t)(u * TBC + tid) * 8;
         const bool vec = full || e + 8 <= cn_n;
-        uint32_t m = 0;
         float dv[8], rv[8], tv[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -249,47 +298,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
         float a[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) a[i] = dv[i] + rv[i];
-        if (gate && GM == 1) {
-          // selected iff bf16(theta) != bf16(theta - a), pairwise on the cvt unit
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint32_t t_lo = __float_as_uint(tv[2 * j]), t_hi = __float_as_uint(tv[2 * j + 1]);
-            const float after_lo = __uint_as_float(t_lo) - a[2 * j];
-            const float after_hi = __uint_as_float(t_hi) - a[2 * j + 1];
-            m |= diff2(bf16x2_rne(t_lo, t_hi),
-                       bf16x2_rne(__float_as_uint(after_lo), __float_as_uint(after_hi)))
-                 << (2 * j);
-          }
-        } else if (gate) {
-          float th[8], af[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            th[i] = tv[i];
-            af[i] = th[i] - a[i];
-          }
-          if (GM == 2) {
-            // selected iff fp8(theta * s) != fp8((theta - a) * s)
-            const float is = cd.inv_scale;
-            float y0[8], y1[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-              y0[i] = th[i] * is;
-              y1[i] = af[i] * is;
-            }
-            uint32_t lo0, hi0, lo1, hi1;
-            fp8_codes8(y0, lo0, hi0);
-            fp8_codes8(y1, lo1, hi1);
-            m = fp8_change_mask(lo0, hi0, lo1, hi1);
-          } else {
-            // selected iff (scale, code) of theta's block != that of theta - a
-            uint32_t c0, c1;
-            const uint32_t s0 = mx_view8(th, c0), s1 = mx_view8(af, c1);
-            m = s0 != s1 ? 0xFFu : nibble_change_mask(c0, c1);
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) m |= (uint32_t)(fabsf(a[i]) >= tau) << i;
-        }
+        uint32_t m = loco_select<GM>(a, tv, gate, tau, cd.inv_scale);
         if (!vec) {
 #pragma unroll
           for (int i = 0; i < 8; ++i)
@@ -433,6 +442,82 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
   }
 }
 
+// One tile per block (device_common.hpp), one group of 8 elements per lane.
+// The residual is stored once the entries' positions are known.
+template <int GM, bool TABLE>
+__global__ __launch_bounds__(kOneNW * 64) void loco_one_kernel(LocoParams p) {
+  constexpr bool GATE = GM != 0;
+  constexpr int TBC = kOneNW * 64;
+  constexpr uint32_t TILE = TBC * 8;
+  __shared__ uint64_t s_c, s_excl;
+  __shared__ uint32_t s_wtot[kOneNW];
+  const int tid = threadIdx.x;
+  const Ticket tk = one_ticket(p.ws, &s_c);
+  const TileOwner own = one_owner<TABLE>(p, tk.tile);
+  const LocoTensorDesc d = tensor_at<TABLE>(p, own.k);
+  const bool gate = GATE && d.theta != nullptr;
+  const uint64_t e = (uint64_t)(tk.tile - own.begin) * TILE + (uint64_t)tid * 8;
+  const bool vec = e + 8 <= d.n;
+  float dv[8], rv[8], tv[8];
+  if (vec) {
+    const uint4 d0 = load16(d.delta + e), d1 = load16(d.delta + e + 4);
+    const uint4 r0 = load16(d.residual + e), r1 = load16(d.residual + e + 4);
+    uint4 t0 = make_uint4(0, 0, 0, 0), t1 = t0;
+    if (gate) {
+      t0 = load16(d.theta + e);
+      t1 = load16(d.theta + e + 4);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      dv[i] = __uint_as_float(get_u32(i < 4 ? d0 : d1, i & 3));
+      rv[i] = __uint_as_float(get_u32(i < 4 ? r0 : r1, i & 3));
+      tv[i] = __uint_as_float(get_u32(i < 4 ? t0 : t1, i & 3));
+    }
+  } else {
+    element_tail(d.delta, d.residual, gate ? d.theta : nullptr, e, d.n, dv, rv, tv);
+  }
+  float a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = dv[i] + rv[i];
+  uint32_t m = loco_select<GM>(a, tv, gate, p.tau, d.inv_scale);
+  if (!vec) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (!(e + i < d.n)) m &= ~(1u << i);
+  }
+  const uint32_t cnt = (uint32_t)__builtin_popcount(m);
+  const uint32_t incl = wave_incl_scan(cnt);
+  if (lane_id() == 63) s_wtot[tid >> 6] = incl;
+  uint32_t wexcl[1], total;
+  const uint64_t excl =
+      one_resolve<1, TABLE>(p, tk, own, s_wtot, &s_excl, wexcl, &total) + wexcl[0] + (incl - cnt);
+  const uint64_t cap = p.capacity;
+  uint64_t pos = excl;
+  float nr[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    nr[i] = a[i];
+    if ((m >> i) & 1u) {
+      if (pos < cap) {
+        p.idx[pos] = d.index_base + (uint32_t)(e + i);
+        p.val[pos] = a[i];
+        nr[i] = 0.0f;
+      }
+      ++pos;
+    }
+  }
+  if (vec) {
+    store16(d.residual + e, make_uint4(__float_as_uint(nr[0]), __float_as_uint(nr[1]),
+                                       __float_as_uint(nr[2]), __float_as_uint(nr[3])));
+    store16(d.residual + e + 4, make_uint4(__float_as_uint(nr[4]), __float_as_uint(nr[5]),
+                                           __float_as_uint(nr[6]), __float_as_uint(nr[7])));
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (e + i < d.n) d.residual[e + i] = nr[i];
+  }
+}
+
 __global__ void loco_empty_segments_kernel(const uint64_t* count, uint64_t* seg_begin,
                                            uint32_t nseg) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -454,6 +539,15 @@ static hipError_t launch_loco_form(const LocoParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <int GM>
+static hipError_t launch_loco_one_form(const LocoParams& p, hipStream_t stream) {
+  if (p.table)
+    hipLaunchKernelGGL((loco_one_kernel<GM, true>), dim3(p.ntiles), dim3(kOneNW * 64), 0, stream, p);
+  else
+    hipLaunchKernelGGL((loco_one_kernel<GM, false>), dim3(p.ntiles), dim3(kOneNW * 64), 0, stream, p);
+  return hipGetLastError();
+}
+
 template <bool TABLE>
 static hipError_t launch_loco_gm(const LocoParams& p, hipStream_t stream) {
   switch (p.gm) {
@@ -464,12 +558,20 @@ static hipError_t launch_loco_gm(const LocoParams& p, hipStream_t stream) {
   }
 }
 
-hipError_t launch_loco(LocoParams& p, hipStream_t stream) {
+hipError_t launch_loco(LocoParams& p, bool one, hipStream_t stream) {
   if (p.ntiles == 0) {
     if (p.seg_begin == nullptr || p.ntensors == 0) return hipSuccess;
     hipLaunchKernelGGL(loco_empty_segments_kernel, dim3((uint32_t)(p.ntensors + 63) / 64), dim3(64), 0, stream,
                        (const uint64_t*)p.count, p.seg_begin, (uint32_t)p.ntensors);
     return hipGetLastError();
+  }
+  if (one) {
+    switch (p.gm) {
+      case 0: return launch_loco_one_form<0>(p, stream);
+      case 1: return launch_loco_one_form<1>(p, stream);
+      case 2: return launch_loco_one_form<2>(p, stream);
+      default: return launch_loco_one_form<3>(p, stream);
+    }
   }
   return p.table ? launch_loco_gm<true>(p, stream) : launch_loco_gm<false>(p, stream);
 }

@@ -367,7 +367,7 @@ size_t loco2_scratch_bytes(uint32_t ntiles) {
 }
 
 hipError_t launch_loco2(LocoParams& p, void* scratch, hipStream_t stream) {
-  if (p.ntiles == 0) return launch_loco(p, stream);
+  if (p.ntiles == 0) return launch_loco(p, false, stream);
   const Scratch sc = scratch_at(scratch, p.ntiles);
   const uint32_t units = (p.ntiles + kL2Unit - 1) / kL2Unit;
   hipLaunchKernelGGL(loco_stage_kernel, dim3(p.ntiles), dim3(kL2Threads), 0, stream, p, sc);

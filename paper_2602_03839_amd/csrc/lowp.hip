@@ -144,6 +144,36 @@ __device__ __forceinline__ void lowp_load(LowpRegs& g, const LowpCtx& c, uint64_
   }
 }
 
+// Change mask of a lane's eight masters x against the snapshot's view `snap`;
+// `view` receives the new D values (FP8: the codes; MXFP4: the packed codes and
+// the scale byte).  Every lane of the wave must call it.
+template <int DT>
+__device__ __forceinline__ uint32_t lowp_changes(const float (&x)[8], const uint2& snap, float inv_scale,
+                                                 uint2& view) {
+  if (DT == kDtypeFp8) {
+    float y[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) y[i] = x[i] * inv_scale;
+    uint32_t lo, hi;
+    fp8_codes8(y, lo, hi);
+    view = make_uint2(lo, hi);
+    return fp8_change_mask(lo, hi, snap.x, snap.y);
+  }
+  uint32_t packed;
+  const uint32_t sc = mx_view8(x, packed);
+  view = make_uint2(packed, sc);
+  return sc != snap.y ? 0xFFu : nibble_change_mask(packed, snap.x);
+}
+
+// Value i of a view, as a patch entry's value.
+template <int DT>
+__device__ __forceinline__ void lowp_put(void* val, uint64_t pos, const uint2& view, int i) {
+  if (DT == kDtypeFp8)
+    ((uint8_t*)val)[pos] = (uint8_t)(((i < 4 ? view.x : view.y) >> (8 * (i & 3))) & 0xFFu);
+  else
+    ((uint16_t*)val)[pos] = (uint16_t)((view.y << 8) | ((view.x >> (4 * i)) & 0xFu));
+}
+
 }  // namespace
 
 constexpr int kLowpNW = 15;
@@ -247,22 +277,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
           x[i] = __uint_as_float(get_u32(g[u].w0, i));
           x[i + 4] = __uint_as_float(get_u32(g[u].w1, i));
         }
-        uint32_t m = 0;
-        if (DT == kDtypeFp8) {
-          const float is = cd.inv_scale;
-          float y[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) y[i] = x[i] * is;
-          uint32_t lo, hi;
-          fp8_codes8(y, lo, hi);
-          m = fp8_change_mask(lo, hi, g[u].s.x, g[u].s.y);
-          staged[u] = make_uint2(lo, hi);
-        } else {
-          uint32_t packed;
-          const uint32_t sc = mx_view8(x, packed);
-          m = sc != g[u].s.y ? 0xFFu : nibble_change_mask(packed, g[u].s.x);
-          staged[u] = make_uint2(packed, sc);
-        }
+        uint32_t m = lowp_changes<DT>(x, g[u].s, cd.inv_scale, staged[u]);
         if (!full && !(e + 8 <= cn_n)) {
 #pragma unroll
           for (int i = 0; i < 8; ++i)
@@ -306,10 +321,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
           mm &= mm - 1;
           if (pos < cap) {
             p.idx[pos] = base + (uint32_t)(e + i);
-            if (DT == kDtypeFp8)
-              ((uint8_t*)p.val)[pos] = (uint8_t)(((i < 4 ? sv.x : sv.y) >> (8 * (i & 3))) & 0xFFu);
-            else
-              ((uint16_t*)p.val)[pos] = (uint16_t)((sv.y << 8) | ((sv.x >> (4 * i)) & 0xFu));
+            lowp_put<DT>(p.val, pos, sv, i);
           }
           ++pos;
         }
@@ -338,6 +350,69 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_lowp_kernel(LowpParams p
   for (int it = 0;; it += kAhead) {
     if (!step(it, g0, e0_0, k_0)) return;
     if (kAhead == 2 && !step(it + 1, g1, e0_1, k_1)) return;
+  }
+}
+
+// One tile per block (device_common.hpp): U groups of 8 values per lane.
+template <int U, int DT, bool TABLE>
+__global__ __launch_bounds__(kOneNW * 64) void encode_lowp_one_kernel(LowpParams p) {
+  constexpr int TBC = kOneNW * 64;
+  constexpr uint32_t TILE = TBC * U * 8;
+  __shared__ uint64_t s_c, s_excl;
+  __shared__ uint32_t s_wtot[U * kOneNW];
+  const int tid = threadIdx.x;
+  const Ticket tk = one_ticket(p.ws, &s_c);
+  const TileOwner own = one_owner<TABLE>(p, tk.tile);
+  const LowpTensorDesc d = tensor_at<TABLE>(p, own.k);
+  LowpCtx c;
+  c.e0 = (uint64_t)(tk.tile - own.begin) * TILE;
+  c.n = d.n;
+  c.w = d.w_new;
+  c.snap = d.snap;
+  c.sscale = d.snap_scales;
+  const bool full = c.e0 + TILE <= c.n;
+  LowpRegs g[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) lowp_load<DT>(g[u], c, c.e0 + (uint64_t)(u * TBC + tid) * 8, full);
+  uint32_t mask[U], excl[U];
+  uint2 view[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = __uint_as_float(get_u32(g[u].w0, i));
+      x[i + 4] = __uint_as_float(get_u32(g[u].w1, i));
+    }
+    mask[u] = lowp_changes<DT>(x, g[u].s, d.inv_scale, view[u]);
+    if (!full) {
+      const uint64_t e = c.e0 + (uint64_t)(u * TBC + tid) * 8;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (!(e + i < c.n)) mask[u] &= ~(1u << i);
+    }
+    const uint32_t cnt = (uint32_t)__builtin_popcount(mask[u]);
+    const uint32_t incl = wave_incl_scan(cnt);
+    excl[u] = incl - cnt;
+    if (lane_id() == 63) s_wtot[u * kOneNW + (tid >> 6)] = incl;
+  }
+  uint32_t wexcl[U], total;
+  const uint64_t tile_excl = one_resolve<U, TABLE>(p, tk, own, s_wtot, &s_excl, wexcl, &total);
+  const uint64_t cap = p.capacity;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    uint64_t pos = tile_excl + wexcl[u] + excl[u];
+    const uint64_t e = c.e0 + (uint64_t)(u * TBC + tid) * 8;
+    uint32_t m = mask[u];
+    while (m) {
+      const int i = __builtin_ctz(m);
+      m &= m - 1;
+      if (pos < cap) {
+        p.idx[pos] = d.index_base + (uint32_t)(e + i);
+        lowp_put<DT>(p.val, pos, view[u], i);
+      }
+      ++pos;
+    }
   }
 }
 
@@ -426,13 +501,32 @@ static hipError_t launch_lowp_form(const LowpParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_encode_lowp(int dtype, LowpParams& p, hipStream_t stream) {
+template <int U, int DT>
+static hipError_t launch_lowp_one_form(const LowpParams& p, hipStream_t stream) {
+  if (p.table)
+    hipLaunchKernelGGL((encode_lowp_one_kernel<U, DT, true>), dim3(p.ntiles), dim3(kOneNW * 64), 0, stream, p);
+  else
+    hipLaunchKernelGGL((encode_lowp_one_kernel<U, DT, false>), dim3(p.ntiles), dim3(kOneNW * 64), 0, stream, p);
+  return hipGetLastError();
+}
+
+template <int DT>
+static hipError_t launch_lowp_one(const LowpParams& p, int one, hipStream_t stream) {
+  return one == 1   ? launch_lowp_one_form<1, DT>(p, stream)
+         : one == 2 ? launch_lowp_one_form<2, DT>(p, stream)
+                    : launch_lowp_one_form<4, DT>(p, stream);
+}
+
+hipError_t launch_encode_lowp(int dtype, LowpParams& p, int one, hipStream_t stream) {
   if (p.ntiles == 0) {
     if (p.seg_begin == nullptr || p.ntensors == 0) return hipSuccess;
     hipLaunchKernelGGL(lowp_empty_segments_kernel, dim3((uint32_t)(p.ntensors + 63) / 64), dim3(64), 0, stream,
                        (const uint64_t*)p.count, p.seg_begin, (uint32_t)p.ntensors);
     return hipGetLastError();
   }
+  if (one)
+    return dtype == kDtypeFp8 ? launch_lowp_one<kDtypeFp8>(p, one, stream)
+                              : launch_lowp_one<kDtypeMxfp4>(p, one, stream);
   if (p.table)
     return dtype == kDtypeFp8 ? launch_lowp_form<kDtypeFp8, true>(p, stream)
                               : launch_lowp_form<kDtypeMxfp4, true>(p, stream);

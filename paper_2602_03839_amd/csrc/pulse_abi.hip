@@ -62,6 +62,43 @@ bool refresh_mirrors(const pulse_encode_tensor& d) {
 
 uint32_t tiles_for(uint64_t n, uint32_t tile) { return (uint32_t)((n + tile - 1) / tile); }
 
+// Which form a call takes: 0 = persistent blocks, else one tile of that many
+// groups of 8,192 elements per block.  Kernel times in us, n elements in one
+// tensor, plain encode, 1 / 2 / 4 groups / persistent:
+//   n = 1M   9.2 /  9.0 / 10.7 / 18.9     n = 8M   29.8 / 23.9 / 17.6 / 28.8
+//   n = 2M  11.6 / 11.0 / 12.2 / 20.8     n = 16M  49.6 / 39.5 / 32.3 / 36.7
+//   n = 4M  17.6 / 12.9 / 13.6 / 23.4     n = 32M     - / 72.2 / 56.4 / 51.3
+// A block costs ~30 ns of the ticket and done counters and of the look-back
+// chain, so a form is left where it passes 128, 256 and 512 blocks.  The FP8
+// and MXFP4 encodes cross at the same places (4M in three tensors, with the
+// apply: 31 against 38; 16M: 45 both).  The sparsifier holds one group (three
+// FP32 streams and the values until the positions are known) and crosses later:
+// 4M gate 25.5 against 30.9, threshold in two passes 31.2; 8M 42.5 against
+// 39.7, threshold 38.2 against 41.5.
+constexpr uint64_t kOneTileBlocks[3] = {128, 256, 512};
+constexpr uint64_t kOneTileBlocksLoco = 768;
+
+uint64_t total_tiles(uint64_t tiles, uint64_t n, uint64_t tile) { return tiles + (n + tile - 1) / tile; }
+
+template <typename Tensor>
+int one_tile_form(const Tensor* tensors, uint32_t ntensors) {
+  if (ntensors > (uint32_t)pulse::kMaxTable) return 0;
+  for (int i = 0; i < 3; ++i) {
+    const uint64_t tile = pulse::one_tile_elems(1 << i);
+    uint64_t tiles = 0;
+    for (uint32_t t = 0; t < ntensors; ++t) tiles = total_tiles(tiles, tensors[t].n, tile);
+    if (tiles <= kOneTileBlocks[i]) return 1 << i;
+  }
+  return 0;
+}
+
+bool one_tile_loco(const pulse_loco_tensor* tensors, uint32_t ntensors) {
+  if (ntensors > (uint32_t)pulse::kMaxTable) return false;
+  uint64_t tiles = 0;
+  for (uint32_t t = 0; t < ntensors; ++t) tiles = total_tiles(tiles, tensors[t].n, pulse::one_tile_elems(1));
+  return tiles <= kOneTileBlocksLoco;
+}
+
 // The next launch's tensors, from tensors[0 .. left): their first tiles and
 // descriptors (fill(i, desc) writes tensor i's) go to p.t where all that are
 // left fit there, else up to kMaxTable of them to the workspace's table, by
@@ -294,7 +331,8 @@ int encode_batch(const pulse_encode_tensor* tensors, uint32_t ntensors, uint32_t
                             "scratch fill launch"))
       return rc;
   }
-  const uint32_t tile = pulse::encode_tile_elems();
+  const int one = one_tile_form(tensors, ntensors);
+  const uint32_t tile = one ? pulse::one_tile_elems(one) : pulse::encode_tile_elems();
   uint32_t t0 = 0;
   while (t0 < ntensors) {
     pulse::EncodeParams p;
@@ -320,7 +358,7 @@ int encode_batch(const pulse_encode_tensor* tensors, uint32_t ntensors, uint32_t
                                },
                                workspace, (hipStream_t)stream, &k))
       return rc;
-    if (int rc = hip_status(pulse::launch_encode(p, refresh, (hipStream_t)stream), "encode launch"))
+    if (int rc = hip_status(pulse::launch_encode(p, refresh, one, (hipStream_t)stream), "encode launch"))
       return rc;
     t0 += k;
   }
@@ -439,11 +477,12 @@ int loco_batch(const pulse_loco_tensor* tensors, const float* inv_scales, uint32
   for (uint32_t t = 0; t < ntensors; ++t) any_theta |= tensors[t].n > 0 && tensors[t].theta != nullptr;
   const int gm = !any_theta ? 0 : gate_dtype == pulse::kDtypeFp8 ? 2
                                  : gate_dtype == pulse::kDtypeMxfp4 ? 3 : 1;
-  const uint32_t tile = pulse::loco_tile_elems(gm);
+  const bool one = one_tile_loco(tensors, ntensors);
+  const uint32_t tile = one ? pulse::one_tile_elems(1) : pulse::loco_tile_elems(gm);
   // The threshold form runs in two passes when the workspace has room past
   // its fixed part for a launch's staging area; a tensor too large for it on
   // its own takes the one-pass kernel.
-  const uint32_t max2 = gm == 0 ? loco2_max_tiles(workspace_bytes) : 0;
+  const uint32_t max2 = gm == 0 && !one ? loco2_max_tiles(workspace_bytes) : 0;
   void* const scratch = static_cast<uint8_t*>(workspace) + pulse::kWorkspaceBytes;
   uint32_t t0 = 0;
   while (t0 < ntensors) {
@@ -499,7 +538,7 @@ int loco_batch(const pulse_loco_tensor* tensors, const float* inv_scales, uint32
                                },
                                workspace, (hipStream_t)stream, &taken))
       return rc;
-    if (int rc = hip_status(pulse::launch_loco(p, (hipStream_t)stream), "loco launch")) return rc;
+    if (int rc = hip_status(pulse::launch_loco(p, one, (hipStream_t)stream), "loco launch")) return rc;
     t0 += taken;
   }
   return ok();
@@ -790,7 +829,8 @@ int pulse_encode_lowp_batch(int dtype, const pulse_lowp_tensor* tensors, uint32_
       return fail(PULSE_EALIGN, "encode_lowp tensor %u: w_new/snap misaligned", t);
     if (int rc = check_range(d.n, d.index_base, "encode_lowp", t)) return rc;
   }
-  const uint32_t tile = pulse::lowp_tile_elems();
+  const int one = one_tile_form(tensors, ntensors);
+  const uint32_t tile = one ? pulse::one_tile_elems(one) : pulse::lowp_tile_elems();
   uint32_t t0 = 0;
   while (t0 < ntensors) {
     pulse::LowpParams p;
@@ -814,7 +854,7 @@ int pulse_encode_lowp_batch(int dtype, const pulse_lowp_tensor* tensors, uint32_
                                },
                                workspace, (hipStream_t)stream, &k))
       return rc;
-    if (int rc = hip_status(pulse::launch_encode_lowp(dtype, p, (hipStream_t)stream),
+    if (int rc = hip_status(pulse::launch_encode_lowp(dtype, p, one, (hipStream_t)stream),
                             "encode_lowp launch"))
       return rc;
     t0 += k;
