@@ -375,11 +375,10 @@ int pulse_varint_encode(const uint32_t *idx, uint64_t capacity, const uint64_t *
  *               capacity are not written.
  *   count       device uint64: the number of entries in the stream.
  *   workspace   as for encode.  The decode keeps its per-tile sums in the
- *               workspace's status ring and leaves them zero, so the workspace
- *               stays valid for the other ordered kernels on the same stream.
- * Five launches (count, offsets, segment-start tiles, carries, write): the
- * stream is read twice and the indices written once; no block waits on
- * another.
+ *               workspace and leaves them zero, so the workspace stays valid
+ *               for the other ordered kernels on the same stream.
+ * Three launches (count, carries, write): the stream is read twice and the
+ * indices written once; no block waits on another.
  */
 int pulse_varint_decode(const uint8_t *in, uint64_t in_capacity, const uint64_t *nbytes,
                         const uint64_t *seg_begin, uint32_t nseg,
@@ -432,7 +431,7 @@ int pulse_coo_encode(const uint32_t *idx, uint64_t capacity, const uint64_t *end
  * the tile folds, write) give every pair its row, column and escape count since
  * its segment's start, and its entry lands at seg_begin[s] + 1 + (pairs of s
  * before it) - (escapes of s before it).  The library allocates nothing: the
- * per-tile folds live in the workspace's status ring and are left zero.  A
+ * per-tile folds live in the workspace and are left zero.  A
  * stream that encode did not write decodes to unspecified indices but no
  * access leaves the buffers.
  */

@@ -9,20 +9,19 @@
 //
 // Both decodes are running sums: an entry's index sums the differences since
 // its segment's start, and its place counts the numbers (or non-escape pairs)
-// before it.  Each is computed reduce-then-scan over tiles of the stream
+// before it.  Each is computed reduce-then-write over tiles of the stream
 // (stream_common.hpp), so that no block ever waits on another:
 //   * COO: a reduce pass folds each tile's pairs into one map on (row,
 //     column, escapes), one block composes the maps, and a write pass gives
-//     every pair its entry's index and place -- the pairs are read twice;
+//     every pair its entry's index and place;
 //   * delta-varint: a count pass (terminating bytes, plain sum of the
-//     numbers), one block numbering the tiles' first entries, a pass over
-//     only the tiles that hold a segment start (their sum since it), one
-//     block carrying the segmented sums, and a write pass -- the bytes are
-//     read twice, plus once more for the tiles with segment starts.
+//     numbers); a pass with one block per segment that gives the tiles whose
+//     first entry lies in it that entry and the sum carried into it (the plain
+//     sum before the tile less the one before the segment); and a write pass.
 // The indices are written once, staged in LDS so that consecutive lanes store
 // consecutive entries.  (The single-pass form with a decoupled look-back per
 // tile was bound by the look-back latency: 3.3 and 5.7 ms on a 306M-entry
-// patch, against 0.7 and 1.1 ms here.)
+// patch.)
 #include "launch.hpp"
 #include "stream_common.hpp"
 
@@ -90,29 +89,38 @@ struct Bytes16 {
   uint32_t w[4];   // bytes pos .. pos + 15
 };
 
-__device__ __forceinline__ Bytes16 load_bytes16(const uint8_t* in, uint64_t pos, uint64_t n) {
+// This thread's sixteen bytes of the unit starting at u0 (none past u1; see
+// "Prefetches" in stream_common.hpp).
+__device__ __forceinline__ Bytes16 unit_bytes(const uint8_t* in, uint64_t u0, uint64_t u1) {
+  const uint64_t pos = u0 + 16ull * threadIdx.x;
+  const uint8_t* const zero = reinterpret_cast<const uint8_t*>(kStreamZero);
+  const uint4 v = load16(pos + 16 <= u1 ? in + pos : zero);
   Bytes16 b;
-  b.h = pos >= 4 ? *reinterpret_cast<const uint32_t*>(in + pos - 4) : 0u;
-  if (pos + 16 <= n) {
-    const uint4 v = load16_stream(in + pos);
-    b.w[0] = v.x;
-    b.w[1] = v.y;
-    b.w[2] = v.z;
-    b.w[3] = v.w;
-  } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      uint32_t x = 0;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const uint64_t at = pos + (uint64_t)(4 * q + c);
-        const uint32_t byte = at < n ? (uint32_t)in[at] : 0x80u;
-        x |= byte << (8 * c);
-      }
-      b.w[q] = x;
-    }
-  }
+  b.h = *reinterpret_cast<const uint32_t*>(pos >= 4 && pos < u1 ? in + pos - 4 : zero);
+  b.w[0] = v.x;
+  b.w[1] = v.y;
+  b.w[2] = v.z;
+  b.w[3] = v.w;
   return b;
+}
+
+// Sets the bytes of [u0, u1) that unit_bytes did not load: the ragged sixteen at
+// the stream's end, and continuations (no terminators) past it.
+__device__ __forceinline__ void finish_bytes(Bytes16& b, const uint8_t* in, uint64_t u0, uint64_t u1) {
+  if (u0 + kDUnit <= u1) return;  // block-uniform
+  const uint64_t pos = u0 + 16ull * threadIdx.x;
+  if (pos + 16 <= u1) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t x = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint64_t at = pos + (uint64_t)(4 * q + c);
+      const uint32_t byte = at < u1 ? (uint32_t)in[at] : 0x80u;
+      x |= byte << (8 * c);
+    }
+    b.w[q] = x;
+  }
 }
 
 __device__ __forceinline__ uint32_t terminators(const Bytes16& b) {
@@ -147,69 +155,42 @@ __device__ __forceinline__ void walk_numbers(const Bytes16& b, Emit emit) {
   }
 }
 
-struct VarintLds {
-  uint32_t val[padded(kDUnit)];  // the unit's indices, in entry order (entry i at pad(i))
-  uint32_t bits[kDUnit / 32];    // segment starts among the unit's entries
-  uint32_t range[2];
-  uint32_t w[kDWaves];
-  SegSum ws[kDWaves];
-  SegCache seg;                  // the segments starting among the tile's entries
-};
-
-// This thread's sixteen bytes of the unit starting at u0 (none past u1).
-__device__ __forceinline__ Bytes16 unit_bytes(const VarintDecParams& p, uint64_t u0, uint64_t u1,
-                                              uint64_t n) {
-  const uint64_t pos = u0 + 16ull * threadIdx.x;
-  Bytes16 b;
-  b.h = 0;
-  b.w[0] = b.w[1] = b.w[2] = b.w[3] = 0x80808080u;  // no bytes: no terminators
-  if (pos < u1) b = load_bytes16(p.in, pos, n);
-  return b;
+// Sum of the numbers that end in the sixteen bytes.  Where a wave holds numbers
+// of one and two bytes only, four bytes at a time: first bytes weigh 1, second
+// bytes 128.  A byte 15 that continues belongs to the next thread; a byte 0
+// that continues a number brings that number's first byte (h's last) with it.
+__device__ __forceinline__ uint32_t sum_numbers(const Bytes16& b) {
+  uint32_t s0 = 0, s1 = 0, prev = b.h, later_prev = (b.h << 8) & 0x80000000u;
+  // deep: some number has a third byte (a byte and its predecessor both
+  // continue a number), here or just past byte 15
+  uint32_t deep = 0, first_later = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t later = __builtin_amdgcn_alignbit(b.w[q], prev, 24) & 0x80808080u;
+    if (q == 0) first_later = later & 0x80u;
+    deep |= later & __builtin_amdgcn_alignbit(later, later_prev, 24);
+    prev = b.w[q];
+    later_prev = later;
+    const uint32_t m = (later << 1) - (later >> 7);  // 0xFF in later bytes
+    const uint32_t v = b.w[q] & 0x7F7F7F7Fu;
+    s0 = __builtin_amdgcn_sad_u8(v & ~m, 0u, s0);
+    s1 = __builtin_amdgcn_sad_u8(v & m, 0u, s1);
+  }
+  deep |= later_prev & b.w[3] & 0x80000000u;
+  uint32_t s = 0;
+  if (__ballot(deep != 0u) == 0) {
+    s = s0 + 128u * s1;
+    if (b.w[3] >> 31) s -= (b.w[3] >> 24) & 0x7Fu;
+    if (first_later) s += (b.h >> 24) & 0x7Fu;
+  } else {
+    walk_numbers(b, [&](uint32_t v) { s += v; });
+  }
+  return s;
 }
 
-// One unit of the stream (this thread's bytes b), whose first entry is entry
-// e0.  Returns `carry` (the running sum before the unit) combined with the
-// unit's entries; *cnt receives the unit's entry count.  WRITE: the indices
-// are written.  Every thread of the block calls it.
-template <bool WRITE>
-__device__ SegSum varint_unit(const VarintDecParams& p, const Bytes16& b, uint64_t e0, SegSum carry,
-                              uint32_t* cnt, VarintLds& L) {
-  const int tid = (int)threadIdx.x;
-  for (uint32_t i = (uint32_t)tid; i < kDUnit / 32; i += kDT) L.bits[i] = 0;
-  uint32_t ucnt;
-  const uint32_t rank = block_count_excl(terminators(b), L.w, &ucnt);  // syncs
-  mark_unit_starts(p.seg_begin, L.seg, e0, e0 + ucnt, L.bits, L.range);
-  // this thread's running sum since its last restart
-  SegSum mine = SegSum::id();
-  uint32_t k = rank;
-  walk_numbers(b, [&](uint32_t v) {
-    if (bit_at(L.bits, k)) {
-      mine.f = 1u;
-      mine.s = v;
-    } else {
-      mine.s += v;
-    }
-    ++k;
-  });
-  SegSum total;
-  const SegSum before = block_scan_excl<kDT>(mine, carry, L.ws, &total);
-  if (WRITE) {
-    uint32_t acc = before.s;
-    k = rank;
-    walk_numbers(b, [&](uint32_t v) {
-      acc = bit_at(L.bits, k) ? v : acc + v;
-      L.val[pad(k)] = acc;
-      ++k;
-    });
-    __syncthreads();
-    for (uint32_t i = (uint32_t)tid; i < ucnt; i += kDT) {
-      const uint64_t e = e0 + i;
-      if (e < p.capacity) p.idx[e] = L.val[pad(i)];
-    }
-  }
-  __syncthreads();  // bits, range and val are rewritten by the next unit
-  *cnt = ucnt;
-  return total;
+__device__ __forceinline__ uint64_t stream_length(const uint64_t* n, uint64_t capacity) {
+  const uint64_t x = *n;
+  return x < capacity ? x : capacity;
 }
 
 // ---------------------------------------------------------------- COO pairs
@@ -221,30 +202,34 @@ struct Pairs16 {
   uint32_t c[8];   // column fields, 2 per word
 };
 
-__device__ __forceinline__ Pairs16 load_pairs16(const uint8_t* drow, const uint16_t* dcol, uint64_t q,
-                                                uint64_t n) {
+// This thread's sixteen pairs of the unit starting at q0 (none past q1; see
+// "Prefetches" in stream_common.hpp).
+__device__ __forceinline__ Pairs16 unit_pairs(const CooDecParams& p, uint64_t q0, uint64_t q1) {
+  const uint64_t q = q0 + 16ull * threadIdx.x;
+  const uint8_t* const zero = reinterpret_cast<const uint8_t*>(kStreamZero);
+  const bool ok = q + 16 <= q1;
+  const uint4 r = load16(ok ? p.drow + q : zero);
+  const uint4 c0 = load16(ok ? reinterpret_cast<const uint8_t*>(p.dcol + q) : zero);
+  const uint4 c1 = load16(ok ? reinterpret_cast<const uint8_t*>(p.dcol + q + 8) : zero);
   Pairs16 x;
-  if (q + 16 <= n) {
-    const uint4 r = load16_stream(drow + q);
-    const uint4 c0 = load16_stream(dcol + q);
-    const uint4 c1 = load16_stream(dcol + q + 8);
-    x.r[0] = r.x; x.r[1] = r.y; x.r[2] = r.z; x.r[3] = r.w;
-    x.c[0] = c0.x; x.c[1] = c0.y; x.c[2] = c0.z; x.c[3] = c0.w;
-    x.c[4] = c1.x; x.c[5] = c1.y; x.c[6] = c1.z; x.c[7] = c1.w;
-  } else {
+  x.r[0] = r.x; x.r[1] = r.y; x.r[2] = r.z; x.r[3] = r.w;
+  x.c[0] = c0.x; x.c[1] = c0.y; x.c[2] = c0.z; x.c[3] = c0.w;
+  x.c[4] = c1.x; x.c[5] = c1.y; x.c[6] = c1.z; x.c[7] = c1.w;
+  return x;
+}
+
+// The ragged sixteen of a unit [q0, q1) that ends the stream.
+__device__ __forceinline__ void finish_pairs(Pairs16& x, const CooDecParams& p, uint64_t q0, uint64_t q1) {
+  if (q1 - q0 == kDUnit) return;  // block-uniform
+  const uint64_t q = q0 + 16ull * threadIdx.x;
+  if (q >= q1 || q + 16 <= q1) return;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) x.r[w] = 0;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) x.c[w] = 0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      if (q + (uint64_t)j < n) {
-        x.r[j >> 2] |= (uint32_t)drow[q + j] << (8 * (j & 3));
-        x.c[j >> 1] |= (uint32_t)dcol[q + j] << (16 * (j & 1));
-      }
+  for (int j = 0; j < 16; ++j) {
+    if (q + (uint64_t)j < q1) {
+      x.r[j >> 2] |= (uint32_t)p.drow[q + j] << (8 * (j & 3));
+      x.c[j >> 1] |= (uint32_t)p.dcol[q + j] << (16 * (j & 1));
     }
   }
-  return x;
 }
 
 __device__ __forceinline__ uint32_t pair_row(const Pairs16& x, int j) {
@@ -273,7 +258,6 @@ __device__ __forceinline__ CooEl segment_state(const CooDecParams& p, uint32_t s
 struct CooLds {
   uint32_t seg[kDUnit / 32];     // segment starts among the unit's pairs
   uint32_t esc[kDUnit / 32];     // escape pairs
-  uint32_t range[2];
   uint64_t ref;                  // the position of the unit's first pair
   CooEl ws[kDWaves];
   SegCache cache;                // the segments whose pairs start in the tile
@@ -284,21 +268,6 @@ struct CooStage {
   uint32_t val[padded(kDUnit)];  // flat index of each pair's entry (pair i at pad(i))
   uint32_t pos[padded(kDUnit)];  // low 32 bits of its position
 };
-
-// This thread's sixteen pairs of the unit starting at q0 (none past q1).
-__device__ __forceinline__ Pairs16 unit_pairs(const CooDecParams& p, uint64_t q0, uint64_t q1, uint64_t n) {
-  const uint64_t q = q0 + 16ull * threadIdx.x;
-  Pairs16 x;
-  if (q < q1) {
-    x = load_pairs16(p.drow, p.dcol, q, n);
-  } else {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) x.r[w] = 0;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) x.c[w] = 0;
-  }
-  return x;
-}
 
 // Writes segment s's first index at its first entry (if it has entries).
 __device__ __forceinline__ void put_first(const CooDecParams& p, uint64_t nent, uint32_t s) {
@@ -316,13 +285,10 @@ __device__ CooEl coo_unit(const CooDecParams& p, const Pairs16& x, uint64_t q0, 
                           uint64_t nent, CooEl carry, bool last_unit, CooLds& L, CooStage* S) {
   const int tid = (int)threadIdx.x;
   const uint64_t q = q0 + 16ull * (uint64_t)tid;
-  for (uint32_t i = (uint32_t)tid; i < kDUnit / 32; i += kDT) {
-    L.seg[i] = 0;
-    L.esc[i] = 0;
-  }
-  __syncthreads();
-  mark_unit_starts(p.seg_pairs, L.cache, q0, q1, L.seg, L.range);
-  const uint32_t lo = L.range[0], hi = L.range[1];
+  mark_unit(p.seg_pairs, L.cache, q0, q1, L.seg);
+  uint32_t marks = run_marks(L.cache, L.seg);
+  if (q == 0) marks |= 1u;  // the stream's first pair always starts a segment
+  const uint32_t lo = L.cache.lo, hi = L.cache.lo + L.cache.n;
   const uint32_t m = q < q1 ? (uint32_t)(q1 - q < 16 ? q1 - q : 16) : 0u;  // this thread's pairs
   const uint32_t i0 = (uint32_t)tid * 16u;
   // this thread's map (absolute from its last segment start on)
@@ -331,7 +297,7 @@ __device__ CooEl coo_unit(const CooDecParams& p, const Pairs16& x, uint64_t q0, 
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     if ((uint32_t)j < m) {
-      if (bit_at(L.seg, i0 + j))
+      if ((marks >> j) & 1u)
         mine = segment_state(p, segment_of(p.seg_pairs, L.cache, lo, hi, q + j), &C);
       mine = comb(mine, pair_map(pair_row(x, j), pair_col(x, j)));
     }
@@ -359,7 +325,7 @@ __device__ CooEl coo_unit(const CooDecParams& p, const Pairs16& x, uint64_t q0, 
     for (int j = 0; j < 16; ++j) {
       if ((uint32_t)j < m) {
         const uint64_t qj = q + (uint64_t)j;
-        if (bit_at(L.seg, i0 + j)) {
+        if ((marks >> j) & 1u) {
           s = segment_of(p.seg_pairs, L.cache, lo, hi, qj);
           st = segment_state(p, s, &C);
           sp = p.seg_pairs[s];
@@ -374,7 +340,8 @@ __device__ CooEl coo_unit(const CooDecParams& p, const Pairs16& x, uint64_t q0, 
         if (qj == q0) L.ref = at;
       }
     }
-    if (m > 0) atomicOr(&L.esc[i0 >> 5], escb << (i0 & 31));
+    // two threads share a word: the even one holds its low half
+    reinterpret_cast<uint16_t*>(L.esc)[tid] = (uint16_t)escb;
     __syncthreads();
     const uint64_t ref = L.ref;
     const uint32_t cnt = (uint32_t)(q1 - q0);
@@ -384,7 +351,10 @@ __device__ CooEl coo_unit(const CooDecParams& p, const Pairs16& x, uint64_t q0, 
       if (at < p.capacity) p.idx[at] = S->val[pad(i)];
     }
     if (tid < 64) {
-      for (uint32_t t = lo + (uint32_t)lane_id(); t < hi; t += 64) put_first(p, nent, t);
+      for (uint32_t t = lo + (uint32_t)lane_id(); t < hi; t += 64) {
+        const uint64_t v = start_of(p.seg_pairs, L.cache, t);
+        if (v >= q0 && v < q1) put_first(p, nent, t);
+      }
       if (last_unit) {
         const uint32_t from = lower_bound_wave(p.seg_pairs, p.nseg, n);
         for (uint32_t t = from + (uint32_t)lane_id(); t < p.nseg; t += 64) put_first(p, nent, t);
@@ -409,23 +379,33 @@ __device__ __forceinline__ CooEl load_el(const uint64_t* w) {
 
 // ---------------------------------------------------------------- varint
 //
-// Ring layout: word b holds tile b's (entries | sum << 32), word kMaxStreamTiles + 1 + b
-// its first entry (| 1 << 63 once a segment start is known to lie in it).
+// Table words, for tile b: word b its (entries | sum << 32); in the next two
+// regions its first entry, and the running sum carried into it.
+
+constexpr uint32_t kFirstWords = kMaxStreamTiles + 1;
+constexpr uint32_t kCarryWords = 2 * (kMaxStreamTiles + 1);
+static_assert(3 * (uint64_t)(kMaxStreamTiles + 1) <= kTableWords, "three words per tile");
 
 __global__ __launch_bounds__(kDT) void varint_count_kernel(VarintDecParams p) {
   __shared__ uint32_t s_w[kDWaves];
   __shared__ uint32_t s_w2[kDWaves];
-  const uint64_t n0 = *p.nbytes;
-  const uint64_t n = n0 < p.in_capacity ? n0 : p.in_capacity;
+  const uint64_t n = stream_length(p.nbytes, p.in_capacity);
   const Geo g = stream_geometry(n);
   if (blockIdx.x >= g.ntiles) return;
   const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
   const uint64_t t1 = t0 + g.tile < n ? t0 + g.tile : n;
   uint32_t cnt = 0, sum = 0;
-  for (uint64_t pos = t0 + 16ull * threadIdx.x; pos < t1; pos += 16ull * kDT) {
-    const Bytes16 b = load_bytes16(p.in, pos, n);
-    cnt += terminators(b);
-    walk_numbers(b, [&](uint32_t v) { sum += v; });
+  for (uint64_t u0 = t0; u0 < t1; u0 += 4 * kDUnit) {
+    // four units' loads in flight
+    Bytes16 b[4];
+#pragma unroll
+    for (uint64_t q = 0; q < 4; ++q) b[q] = unit_bytes(p.in, u0 + q * kDUnit, t1);
+#pragma unroll
+    for (uint64_t q = 0; q < 4; ++q) {
+      finish_bytes(b[q], p.in, u0 + q * kDUnit, t1);
+      cnt += terminators(b[q]);
+      sum += sum_numbers(b[q]);
+    }
   }
   // block sums of both
   const int lane = lane_id(), wid = (int)threadIdx.x >> 6;
@@ -442,193 +422,271 @@ __global__ __launch_bounds__(kDT) void varint_count_kernel(VarintDecParams p) {
       C += s_w[w];
       S += s_w2[w];
     }
-    stream_ring(p.ws)[blockIdx.x] = (uint64_t)C | ((uint64_t)S << 32);
+    stream_words(p.ws)[blockIdx.x] = (uint64_t)C | ((uint64_t)S << 32);
   }
 }
 
-// One block: each tile's first entry, and the entry count.
-__global__ __launch_bounds__(kST) void varint_offsets_kernel(VarintDecParams p) {
-  __shared__ uint64_t s_w[kST / 64];
-  const uint64_t n0 = *p.nbytes;
-  const uint64_t n = n0 < p.in_capacity ? n0 : p.in_capacity;
+// Entries and plain sum (modulo 2^32) before a tile.
+struct Before {
+  uint64_t cnt;
+  uint32_t sum;
+  __device__ static Before id() { return Before{0ull, 0u}; }
+};
+__device__ __forceinline__ Before comb(Before x, Before y) { return Before{x.cnt + y.cnt, x.sum + y.sum}; }
+__device__ __forceinline__ Before shfl_up(Before x, int d) {
+  return Before{(uint64_t)__shfl_up(x.cnt, d, 64), (uint32_t)__shfl_up((int)x.sum, d, 64)};
+}
+
+// Block s, s + grid, ...: segment s (and block 0 the entries before the first
+// segment).  The tiles whose first entry lies past its start, up to its end,
+// carry in the plain sum before them less the one before the segment: the
+// block folds the tile words, sums the numbers of the start's tile up to it,
+// and writes those tiles' first entries and carries.  Every tile's first entry
+// lies in exactly one segment's range.
+__global__ __launch_bounds__(kDT) void varint_carry_kernel(VarintDecParams p) {
+  __shared__ Before s_wb[kDWaves];
+  __shared__ uint32_t s_w[kDWaves];
+  __shared__ Before s_at;  // before the tile that holds the segment's start
+  __shared__ uint32_t s_tile;
+  const uint64_t n = stream_length(p.nbytes, p.in_capacity);
   const Geo g = stream_geometry(n);
-  uint64_t* ring = stream_ring(p.ws);
-  const uint32_t per = (g.ntiles + kST - 1) / kST;
-  const uint32_t a = (uint32_t)threadIdx.x * per;
-  const uint32_t b = a + per < g.ntiles ? a + per : g.ntiles;
-  uint64_t run = 0;
-  for (uint32_t i = a; i < b; ++i) run += (uint32_t)ring[i];
-  // block exclusive sum of the runs (64-bit)
-  const int lane = lane_id(), wid = (int)threadIdx.x >> 6;
-  uint64_t inc = run;
+  uint64_t* words = stream_words(p.ws);
+  Before run = Before::id(), total;
+  uint64_t x[kFoldPer];
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t o = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += o;
+  for (uint32_t q = 0; q < kFoldPer; ++q) {
+    const uint32_t i = threadIdx.x * kFoldPer + q;
+    x[q] = i < g.ntiles ? words[i] : 0ull;
+    run = comb(run, Before{(uint32_t)x[q], (uint32_t)(x[q] >> 32)});
   }
-  if (lane == 63) s_w[wid] = inc;
-  __syncthreads();
-  uint64_t pre = inc - run, all = 0;
-  for (int w = 0; w < kST / 64; ++w) {
-    if (w < wid) pre += s_w[w];
-    all += s_w[w];
-  }
-  for (uint32_t i = a; i < b; ++i) {
-    ring[kMaxStreamTiles + 1 + i] = pre;
-    pre += (uint32_t)ring[i];
-  }
-  if (threadIdx.x == 0) *p.count = all;
-}
-
-// Tiles that hold a segment start: their sum since the last start in them.
-__global__ __launch_bounds__(kDT) void varint_restarts_kernel(VarintDecParams p) {
-  __shared__ VarintLds L;
-  __shared__ int s_has;
-  const uint64_t n0 = *p.nbytes;
-  const uint64_t n = n0 < p.in_capacity ? n0 : p.in_capacity;
-  const Geo g = stream_geometry(n);
-  if (blockIdx.x >= g.ntiles) return;
-  uint64_t* ring = stream_ring(p.ws);
-  const uint64_t e0 = ring[kMaxStreamTiles + 1 + blockIdx.x];
-  const uint64_t w0 = ring[blockIdx.x];
-  const uint64_t ecnt = (uint32_t)w0;
-  if (threadIdx.x < 64) {
-    bool has = e0 == 0 && ecnt > 0;
-    if (!has && p.seg_begin && p.nseg > 0) {
-      const uint32_t s = lower_bound_wave(p.seg_begin, p.nseg, e0);
-      has = s < p.nseg && p.seg_begin[s] < e0 + ecnt;
+  const Before mine = block_scan_excl<kDT>(run, Before::id(), s_wb, &total);
+  // f(tile, entries and sum before it, entries before the next) for this thread's tiles
+  auto tiles = [&](auto f) {
+    Before at = mine;
+#pragma unroll
+    for (uint32_t q = 0; q < kFoldPer; ++q) {
+      const uint32_t i = threadIdx.x * kFoldPer + q;
+      const Before next = comb(at, Before{(uint32_t)x[q], (uint32_t)(x[q] >> 32)});
+      if (i < g.ntiles) f(i, at, next.cnt);
+      at = next;
     }
-    if (threadIdx.x == 0) s_has = has ? 1 : 0;
-  }
-  __syncthreads();
-  if (!s_has) return;  // block-uniform
-  const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
-  const uint64_t t1 = t0 + g.tile < n ? t0 + g.tile : n;
-  cache_tile_segments(p.seg_begin, p.nseg, e0, e0 + ecnt, L.seg);
-  SegSum run = SegSum::id();
-  uint64_t e = e0;
-  Bytes16 b = unit_bytes(p, t0, t1, n);
-  for (uint64_t u0 = t0; u0 < t1; u0 += kDUnit) {
-    const uint64_t u1 = u0 + kDUnit < t1 ? u0 + kDUnit : t1;
-    const Bytes16 cur = b;
-    if (u1 < t1) b = unit_bytes(p, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1, n);  // the next unit's, in flight
-    uint32_t c;
-    run = varint_unit<false>(p, cur, e, run, &c, L);
-    e += c;
-  }
-  if (threadIdx.x == 0) {
-    ring[blockIdx.x] = (uint64_t)(uint32_t)w0 | ((uint64_t)run.s << 32);
-    ring[kMaxStreamTiles + 1 + blockIdx.x] = e0 | (1ull << 63);
-  }
-}
-
-// One block: the running sum carried into each tile.
-__global__ __launch_bounds__(kST) void varint_carry_kernel(VarintDecParams p) {
-  __shared__ SegSum s_w[kST / 64];
-  const uint64_t n0 = *p.nbytes;
-  const uint64_t n = n0 < p.in_capacity ? n0 : p.in_capacity;
-  const Geo g = stream_geometry(n);
-  uint64_t* ring = stream_ring(p.ws);
-  auto ld = [&](uint32_t i) {
-    return SegSum{(uint32_t)(ring[kMaxStreamTiles + 1 + i] >> 63), (uint32_t)(ring[i] >> 32)};
   };
-  auto st = [&](uint32_t i, SegSum c) { ring[i] = (ring[i] & 0xFFFFFFFFull) | ((uint64_t)c.s << 32); };
-  SegSum all;
-  single_block_scan<SegSum>(g.ntiles, ld, st, s_w, &all);
+  auto segment = [&](uint64_t e, uint64_t next) {  // block-uniform
+    bool any = false;
+    __syncthreads();  // the last segment's shared words are read
+    tiles([&](uint32_t i, Before at, uint64_t end) {
+      any |= (at.cnt > e || e == 0) && at.cnt <= next;
+      if (at.cnt <= e && e < end) {
+        s_at = at;
+        s_tile = i;
+      }
+    });
+    if (!__syncthreads_or(any)) return;
+    uint32_t before = 0;  // the sum of all numbers before entry e
+    if (e > 0) {
+      const uint32_t want = (uint32_t)(e - s_at.cnt);  // the tile's entries before e
+      const uint64_t t0 = (uint64_t)s_tile * g.tile;
+      const uint64_t t1 = t0 + g.tile < n ? t0 + g.tile : n;
+      uint32_t seen = 0, sum = 0;
+      for (uint64_t u0 = t0; u0 < t1 && seen < want; u0 += kDUnit) {  // block-uniform
+        Bytes16 b = unit_bytes(p.in, u0, t1);
+        finish_bytes(b, p.in, u0, t1);
+        uint32_t c;
+        uint32_t k = seen + block_count_excl(terminators(b), s_w, &c);
+        walk_numbers(b, [&](uint32_t v) {
+          if (k < want) sum += v;
+          ++k;
+        });
+        seen += c;
+      }
+      uint32_t all;
+      (void)block_count_excl(sum, s_w, &all);
+      before = s_at.sum + all;
+    }
+    tiles([&](uint32_t i, Before at, uint64_t) {
+      if ((at.cnt > e || e == 0) && at.cnt <= next) {
+        words[kFirstWords + i] = at.cnt;
+        words[kCarryWords + i] = (uint64_t)(at.sum - before);
+      }
+    });
+  };
+  const uint32_t nseg = p.seg_begin ? p.nseg : 0u;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) *p.count = total.cnt;
+    const uint64_t first = nseg ? p.seg_begin[0] : ~0ull;
+    if (first > 0) segment(0, first);
+  }
+  for (uint32_t s = blockIdx.x; s < nseg; s += gridDim.x) {
+    const uint64_t e = p.seg_begin[s];
+    const uint64_t next = s + 1 < nseg ? p.seg_begin[s + 1] : ~0ull;
+    if (next <= e || (e > 0 && e >= total.cnt)) continue;  // empty, or past the last entry
+    segment(e, next);
+  }
 }
 
 __global__ __launch_bounds__(kDT) void varint_write_kernel(VarintDecParams p) {
-  __shared__ VarintLds L;
-  const uint64_t n0 = *p.nbytes;
-  const uint64_t n = n0 < p.in_capacity ? n0 : p.in_capacity;
+  __shared__ uint32_t s_val[padded(kDUnit)];  // the unit's indices, in entry order (entry i at pad(i))
+  __shared__ uint32_t s_bits[kDUnit / 32];
+  __shared__ uint32_t s_range[2];
+  __shared__ uint32_t s_w[kDWaves];
+  __shared__ Sum64 s_wu[kDWaves];
+  __shared__ SegSum s_ws[kDWaves];
+  __shared__ SegCache s_seg;
+  const int tid = (int)threadIdx.x;
+  const uint64_t n = stream_length(p.nbytes, p.in_capacity);
   const Geo g = stream_geometry(n);
   if (blockIdx.x >= g.ntiles) return;
-  uint64_t* ring = stream_ring(p.ws);
-  const uint64_t e0 = ring[kMaxStreamTiles + 1 + blockIdx.x] & ~(1ull << 63);
-  const uint64_t w0 = ring[blockIdx.x];
-  SegSum run = SegSum{0u, (uint32_t)(w0 >> 32)};
+  uint64_t* words = stream_words(p.ws);
   const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
   const uint64_t t1 = t0 + g.tile < n ? t0 + g.tile : n;
-  Bytes16 b = unit_bytes(p, t0, t1, n);
-  cache_tile_segments(p.seg_begin, p.nseg, e0, e0 + (uint32_t)w0, L.seg);  // ends with a barrier:
-  if (threadIdx.x == 0) {                                                  // every thread has read
-    ring[blockIdx.x] = 0;                                                  // the tile's words
-    ring[kMaxStreamTiles + 1 + blockIdx.x] = 0;
+  Bytes16 b = unit_bytes(p.in, t0, t1);
+  const uint32_t ecnt = (uint32_t)words[blockIdx.x];
+  const uint64_t e0 = words[kFirstWords + blockIdx.x];
+  uint32_t carry = (uint32_t)words[kCarryWords + blockIdx.x];
+  cache_tile_segments(p.seg_begin, p.nseg, e0, e0 + ecnt, s_seg);  // ends with a barrier: every
+  if (tid == 0) {                                                  // thread has read the tile's words
+    words[blockIdx.x] = 0;
+    words[kFirstWords + blockIdx.x] = 0;
+    words[kCarryWords + blockIdx.x] = 0;
   }
   uint64_t e = e0;
   for (uint64_t u0 = t0; u0 < t1; u0 += kDUnit) {
     const uint64_t u1 = u0 + kDUnit < t1 ? u0 + kDUnit : t1;
-    const Bytes16 cur = b;
-    if (u1 < t1) b = unit_bytes(p, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1, n);  // the next unit's, in flight
-    uint32_t c;
-    run = varint_unit<true>(p, cur, e, run, &c, L);
-    e += c;
+    Bytes16 cur = b;
+    b = unit_bytes(p.in, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1);  // the next unit's, in flight
+    finish_bytes(cur, p.in, u0, u1);
+    // one walk: a number at the byte that ends it
+    uint32_t v[16], ends = 0, sum = 0;
+    {
+      uint32_t cv = 0, sh = 0;
+      bool begin = true;
+#pragma unroll
+      for (int j = -4; j < 16; ++j) {
+        const uint32_t byte = j < 0 ? (cur.h >> (8 * (j + 4))) & 0xFFu : (cur.w[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+        const uint32_t v7 = byte & 0x7Fu;
+        cv = begin ? v7 : cv | (sh < 32 ? v7 << sh : 0u);
+        sh = begin ? 7 : sh + 7;
+        begin = (byte & 0x80u) == 0;
+        if (j >= 0) {
+          v[j] = cv;
+          ends |= begin ? 1u << j : 0u;
+          sum += begin ? cv : 0u;
+        }
+      }
+    }
+    // this thread's rank among the unit's entries, and the sum before it
+    const uint32_t mine = (uint32_t)__builtin_popcount(ends);
+    uint32_t k, ucnt, acc, marks = 0;
+    if (s_seg.n == 0) {
+      // no segment starts in the tile: one scan of (sum, count); sums wrap out
+      // of the top, and a unit's count never reaches bit 32
+      Sum64 all;
+      const uint64_t ex =
+          block_scan_excl<kDT>(Sum64{((uint64_t)sum << 32) | mine}, Sum64::id(), s_wu, &all).v;
+      k = (uint32_t)ex;
+      ucnt = (uint32_t)all.v;
+      acc = carry + (uint32_t)(ex >> 32);
+      carry += (uint32_t)(all.v >> 32);
+    } else {
+      for (uint32_t i = (uint32_t)tid; i < kDUnit / 32; i += kDT) s_bits[i] = 0;
+      k = block_count_excl(mine, s_w, &ucnt);  // its barriers order the clearing
+      mark_unit_starts(p.seg_begin, s_seg, e, e + ucnt, s_bits, s_range);
+      SegSum own = SegSum::id();
+      uint32_t r = k;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        if ((ends >> j) & 1u) {
+          const bool at_start = bit_at(s_bits, r);
+          marks |= at_start ? 1u << j : 0u;
+          own = comb(own, SegSum{at_start ? 1u : 0u, v[j]});
+          ++r;
+        }
+      }
+      SegSum all;
+      acc = block_scan_excl<kDT>(own, SegSum{0u, carry}, s_ws, &all).s;
+      carry = all.s;
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      if ((ends >> j) & 1u) {
+        acc = (marks >> j) & 1u ? v[j] : acc + v[j];
+        s_val[pad(k)] = acc;
+        ++k;
+      }
+    }
+    __syncthreads();
+    for (uint32_t i = (uint32_t)tid; i < ucnt; i += kDT) {
+      const uint64_t at = e + i;
+      if (at < p.capacity) p.idx[at] = s_val[pad(i)];
+    }
+    e += ucnt;
+    // no barrier here: the next unit writes s_val after its scan's barriers
   }
 }
 
 // ---------------------------------------------------------------- COO
 //
-// Ring layout: words 2b, 2b + 1 hold tile b's map, then its exclusive prefix.
+// Table words 2b, 2b + 1: tile b's map, then its exclusive prefix.
 
 __global__ __launch_bounds__(kDT) void coo_reduce_kernel(CooDecParams p) {
   __shared__ CooLds L;
-  const uint64_t n0 = *p.npairs;
-  const uint64_t n = n0 < p.pair_capacity ? n0 : p.pair_capacity;
+  const uint64_t n = stream_length(p.npairs, p.pair_capacity);
   const uint64_t nent = *p.nent;
   const Geo g = stream_geometry(n);
   if (blockIdx.x >= g.ntiles) return;
   const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
   const uint64_t t1 = t0 + g.tile < n ? t0 + g.tile : n;
+  Pairs16 x = unit_pairs(p, t0, t1);
   cache_tile_segments(p.seg_pairs, p.nseg, t0, t1, L.cache);
   CooEl run = CooEl::id();
-  Pairs16 x = unit_pairs(p, t0, t1, n);
   for (uint64_t u0 = t0; u0 < t1; u0 += kDUnit) {
     const uint64_t u1 = u0 + kDUnit < t1 ? u0 + kDUnit : t1;
-    const Pairs16 cur = x;
-    if (u1 < t1) x = unit_pairs(p, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1, n);  // the next unit's, in flight
+    Pairs16 cur = x;
+    x = unit_pairs(p, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1);  // the next unit's, in flight
+    finish_pairs(cur, p, u0, u1);
     run = coo_unit<false>(p, cur, u0, u1, n, nent, run, false, L, nullptr);
   }
-  if (threadIdx.x == 0) store_el(stream_ring(p.ws) + 2ull * blockIdx.x, run);
+  if (threadIdx.x == 0) store_el(stream_words(p.ws) + 2ull * blockIdx.x, run);
 }
 
+// One block: the map before each tile.  (Folding the maps before its tile in
+// every block of the write pass cost that pass 13 us on 1,128 tiles; this
+// launch takes 5.)
 __global__ __launch_bounds__(kST) void coo_scan_kernel(CooDecParams p) {
   __shared__ CooEl s_w[kST / 64];
-  const uint64_t n0 = *p.npairs;
-  const uint64_t n = n0 < p.pair_capacity ? n0 : p.pair_capacity;
+  const uint64_t n = stream_length(p.npairs, p.pair_capacity);
   const Geo g = stream_geometry(n);
-  uint64_t* ring = stream_ring(p.ws);
-  auto ld = [&](uint32_t i) { return load_el(ring + 2ull * i); };
-  auto st = [&](uint32_t i, CooEl x) { store_el(ring + 2ull * i, x); };
-  CooEl all;
-  single_block_scan<CooEl>(g.ntiles, ld, st, s_w, &all);
+  uint64_t* w = stream_words(p.ws);
+  auto ld = [&](uint32_t i) { return load_el(w + 2ull * i); };
+  auto st = [&](uint32_t i, CooEl x) { store_el(w + 2ull * i, x); };
+  single_block_scan<CooEl>(g.ntiles, ld, st, s_w);
 }
 
 __global__ __launch_bounds__(kDT) void coo_write_kernel(CooDecParams p) {
   __shared__ CooLds L;
   __shared__ CooStage S;
-  const uint64_t n0 = *p.npairs;
-  const uint64_t n = n0 < p.pair_capacity ? n0 : p.pair_capacity;
+  const uint64_t n = stream_length(p.npairs, p.pair_capacity);
   const uint64_t nent = *p.nent;
   const Geo g = stream_geometry(n);
   if (blockIdx.x >= g.ntiles) return;
-  uint64_t* ring = stream_ring(p.ws) + 2ull * blockIdx.x;
-  CooEl run = load_el(ring);
   const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
   const uint64_t t1 = t0 + g.tile < n ? t0 + g.tile : n;
-  Pairs16 x = unit_pairs(p, t0, t1, n);
+  Pairs16 x = unit_pairs(p, t0, t1);
+  uint64_t* const words = stream_words(p.ws) + 2ull * blockIdx.x;
+  CooEl run = load_el(words);
   cache_tile_segments(p.seg_pairs, p.nseg, t0, t1, L.cache);  // ends with a barrier: every
   if (threadIdx.x == 0) {                                     // thread has read the tile's words
-    ring[0] = 0;
-    ring[1] = 0;
+    words[0] = 0;
+    words[1] = 0;
   }
   if (t0 >= t1) {  // the empty stream: only the segments' first indices
     run = coo_unit<true>(p, x, 0, 0, n, nent, run, true, L, &S);
-    return;
   }
   for (uint64_t u0 = t0; u0 < t1; u0 += kDUnit) {
     const uint64_t u1 = u0 + kDUnit < t1 ? u0 + kDUnit : t1;
-    const Pairs16 cur = x;
-    if (u1 < t1) x = unit_pairs(p, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1, n);  // the next unit's, in flight
+    Pairs16 cur = x;
+    x = unit_pairs(p, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1);  // the next unit's, in flight
+    finish_pairs(cur, p, u0, u1);
     run = coo_unit<true>(p, cur, u0, u1, n, nent, run, u1 == n, L, &S);
   }
 }
@@ -641,11 +699,8 @@ hipError_t launch_varint_decode(const VarintDecParams& p, hipStream_t stream) {
   const uint32_t grid = tile_grid(p.in_capacity);
   hipLaunchKernelGGL(varint_count_kernel, dim3(grid), dim3(kDT), 0, stream, p);
   if (hipError_t e = hipGetLastError()) return e;
-  hipLaunchKernelGGL(varint_offsets_kernel, dim3(1), dim3(kST), 0, stream, p);
-  if (hipError_t e = hipGetLastError()) return e;
-  hipLaunchKernelGGL(varint_restarts_kernel, dim3(grid), dim3(kDT), 0, stream, p);
-  if (hipError_t e = hipGetLastError()) return e;
-  hipLaunchKernelGGL(varint_carry_kernel, dim3(1), dim3(kST), 0, stream, p);
+  const uint32_t nseg = p.nseg < 1u ? 1u : p.nseg < 512u ? p.nseg : 512u;
+  hipLaunchKernelGGL(varint_carry_kernel, dim3(nseg), dim3(kDT), 0, stream, p);
   if (hipError_t e = hipGetLastError()) return e;
   hipLaunchKernelGGL(varint_write_kernel, dim3(grid), dim3(kDT), 0, stream, p);
   return hipGetLastError();

@@ -18,7 +18,7 @@ namespace pulse {
 
 // ---------------------------------------------------------------- workspace
 //
-// The header holds three words, each on its own 128-byte cache line so that
+// The header holds four words, each on its own 128-byte cache line so that
 // polls of one never contend with the atomics on another:
 // word kWordTicket: ticket counter = (G0 << 24) | c, where c counts the chunks
 //         of kChunk consecutive tiles drawn in the current launch and G0 is the
@@ -32,6 +32,8 @@ namespace pulse {
 //         it counted itself out) stores ((G0 + ntiles) << 24) into the ticket
 //         counter and 0 here, so the next launch starts at c = 0 with no reset
 //         kernel.
+// word kWordStream: blocks of the current index-stream launch that have read
+//         their tile aggregates (stream_common.hpp); zero between launches.
 // words kStatusOffsetWords ..: a ring of kSlots status words.  Tile with global
 //         sequence g uses slot g mod kSlots and tags its word with (g / kSlots)
 //         mod 256.  Every sequence number is published exactly once, in order
@@ -45,6 +47,7 @@ namespace pulse {
 constexpr int kWordTicket = 0;
 constexpr int kWordGaveUp = 16;
 constexpr int kWordDone = 32;
+constexpr int kWordStream = 48;
 constexpr int kTicketBits = 24;
 constexpr uint64_t kTicketMask = (1ull << kTicketBits) - 1;
 constexpr uint64_t kSeqMask = (1ull << 40) - 1;  // G0 is kept modulo 2^40

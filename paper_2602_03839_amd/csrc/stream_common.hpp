@@ -3,14 +3,13 @@
 // of a stream whose length is read from the device.
 //
 //   1. reduce  one block per tile folds its part of the stream into an
-//              aggregate, kept in the workspace's status ring;
-//   2. scan    one block turns the tile aggregates into exclusive prefixes;
-//   3. write   one block per tile reads its part again, starts from its prefix
-//              and writes its output, staged in LDS so that consecutive lanes
-//              store consecutive items; it clears its ring words to zero.
-// The ring's other users (encode, sparsify) read a zero word as "not published
-// yet", so a workspace stays shareable with them on one stream.  No block
-// waits on another.
+//              aggregate, kept in the workspace's table words;
+//   2. write   one block per tile starts from the fold of the aggregates
+//              before its own, reads its part again and writes its output.
+// The encoders' blocks fold plain sums themselves (a few words per thread cost
+// less than a launch); the decoders have a small launch in between.  The words
+// are left zero, so a zero-filled workspace stays so.  No block waits on
+// another.
 #pragma once
 
 #include "device_common.hpp"
@@ -21,11 +20,17 @@ namespace stream {
 constexpr int kDT = 256;                     // threads per block of the tile kernels
 constexpr int kDWaves = kDT / 64;
 constexpr uint32_t kDUnit = kDT * 16;        // bytes (varint) or pairs (COO) per unit
-constexpr uint32_t kMaxStreamTiles = 8191;   // tiles per launch: two ring words each
-constexpr int kST = 1024;                    // threads of the single-block scans
-static_assert(2 * (uint64_t)(kMaxStreamTiles + 1) <= kSlots, "tile aggregates exceed the ring");
+// Tiles per launch, up to three table words each.  More cost the fold of the
+// tile words in every block, fewer leave the last wave of tiles longer: 2,047 /
+// 4,095 / 8,191 took 370 / 355 / 365 us on the 7B set's varint stream (encode
+// and decode) and 89 / 90 / 92 us on the 0.5B set's COO stream.
+constexpr uint32_t kMaxStreamTiles = 4095;
+constexpr int kST = 1024;                    // threads of the single-block scan
+static_assert(3 * (uint64_t)(kMaxStreamTiles + 1) <= kTableWords, "tile aggregates exceed the table");
+// Tile aggregates a thread folds for its block's prefix.
+constexpr uint32_t kFoldPer = (kMaxStreamTiles + kDT) / kDT;
 
-__device__ __forceinline__ uint64_t* stream_ring(uint64_t* ws) { return ws + kStatusOffsetWords; }
+__device__ __forceinline__ uint64_t* stream_words(uint64_t* ws) { return ws + kTableOffsetWords; }
 
 // LDS arrays that threads fill sixteen consecutive items each (thread t at
 // 16 t + j) get one spare word per sixteen: item i lives at pad(i), so the 64
@@ -221,11 +226,19 @@ __device__ __forceinline__ uint32_t segment_of(const uint64_t* starts, const Seg
   return lo > 0 ? lo - 1 : 0;
 }
 
+// Sum of 64-bit values, for block_scan_excl.
+struct Sum64 {
+  uint64_t v;
+  __device__ static Sum64 id() { return Sum64{0ull}; }
+};
+__device__ __forceinline__ Sum64 comb(Sum64 x, Sum64 y) { return Sum64{x.v + y.v}; }
+__device__ __forceinline__ Sum64 shfl_up(Sum64 x, int d) { return Sum64{__shfl_up(x.v, d, 64)}; }
+
 // Exclusive scan of n elements in place by one block of kST threads: each
 // thread folds a run of consecutive elements, the runs are scanned, and each
-// thread writes its run's prefixes.  *total (thread 0) receives the fold of all.
+// thread writes its run's prefixes.
 template <typename T, typename Load, typename Store>
-__device__ void single_block_scan(uint32_t n, Load ld, Store st, T* s_w, T* total) {
+__device__ void single_block_scan(uint32_t n, Load ld, Store st, T* s_w) {
   const uint32_t per = (n + kST - 1) / kST;
   const uint32_t a = (uint32_t)threadIdx.x * per;
   const uint32_t b = a + per < n ? a + per : n;
@@ -238,16 +251,169 @@ __device__ void single_block_scan(uint32_t n, Load ld, Store st, T* s_w, T* tota
     st(i, pre);
     pre = comb(pre, x);
   }
-  *total = all;
 }
 
-// Sum of 64-bit values, for block_scan_excl / single_block_scan.
-struct Sum64 {
-  uint64_t v;
-  __device__ static Sum64 id() { return Sum64{0ull}; }
+// Sum of w[0 .. n), n <= kMaxStreamTiles; every thread of the block gets it.
+// s_w holds one value per wave; contains one barrier, and s_w may be reused
+// after the next.
+__device__ __forceinline__ uint64_t fold_before(const uint64_t* w, uint32_t n, uint64_t* s_w) {
+  uint64_t v = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < kFoldPer; ++q) {
+    const uint32_t i = q * kDT + threadIdx.x;
+    if (i < n) v += w[i];
+  }
+  v = wave_sum_u64(v);
+  if (lane_id() == 0) s_w[threadIdx.x >> 6] = v;
+  __syncthreads();
+  uint64_t all = 0;
+#pragma unroll
+  for (int q = 0; q < kDWaves; ++q) all += s_w[q];
+  return all;
+}
+
+// Called by every block of a write pass at its end, by all threads: counts the
+// block out, and the last one out -- every block has read its aggregates --
+// clears words [0, n0).  Relaxed: a block's reads have
+// returned (the wait) before it counts itself out, and nothing else is ordered.
+__device__ __forceinline__ void stream_finish(uint64_t* ws, uint32_t ntiles, uint32_t n0) {
+  if (threadIdx.x >= 64) return;
+  uint32_t last = 0;
+  if (threadIdx.x == 0) {
+    __builtin_amdgcn_s_waitcnt(0);  // every counter at zero
+    last = __hip_atomic_fetch_add(ws + kWordStream, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           ntiles - 1;
+    if (last) __hip_atomic_store(ws + kWordStream, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (!__builtin_amdgcn_readfirstlane((int)last)) return;
+  uint64_t* w = stream_words(ws);
+  for (uint32_t i = threadIdx.x; i < n0; i += 64) w[i] = 0;
+}
+
+// Prefetches.  A load that one of two paths issues, or that a branch skips, has
+// its registers merged where the paths join, and the compiler waits for it
+// there -- right after issuing it.  Every prefetch below is therefore one
+// unconditional load per register, from the stream or (for lanes without a
+// whole piece in range) from a zero block; the one ragged piece at a list's
+// end is read again, item by item, when its unit is computed.
+__device__ __align__(16) const uint32_t kStreamZero[4] = {0u, 0u, 0u, 0u};
+
+// A unit's entries as its threads hold them: four quads of four consecutive
+// entries, quad q of thread t the entries 4 (q kDT + t) .. + 3 of the unit, so
+// that each load instruction reads whole lines.  Entries at or past u1 read as
+// 0.  The 16-byte loads need the list's own 4-byte alignment only.
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+struct Quads {
+  uint32_t v[16];   // quad q's entries at 4 q ..
+  uint32_t edge[4]; // lane 0: the entry before quad q (0 before the list)
 };
-__device__ __forceinline__ Sum64 comb(Sum64 x, Sum64 y) { return Sum64{x.v + y.v}; }
-__device__ __forceinline__ Sum64 shfl_up(Sum64 x, int d) { return Sum64{__shfl_up(x.v, d, 64)}; }
+
+__device__ __forceinline__ Quads load_quads(const uint32_t* idx, uint64_t u0, uint64_t u1) {
+  Quads x;
+  const uint32_t* const zero = kStreamZero;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint64_t k = u0 + 4ull * ((uint32_t)q * kDT + threadIdx.x);
+    const u32x4_a4 w = *reinterpret_cast<const u32x4_a4*>(k + 4 <= u1 ? idx + k : zero);
+    x.v[4 * q] = w.x;
+    x.v[4 * q + 1] = w.y;
+    x.v[4 * q + 2] = w.z;
+    x.v[4 * q + 3] = w.w;
+    x.edge[q] = *(lane_id() == 0 && k > 0 && k < u1 ? idx + k - 1 : zero);
+  }
+  return x;
+}
+
+// The ragged quad of a unit [u0, u1) that ends the list.
+__device__ __forceinline__ void finish_quads(Quads& x, const uint32_t* idx, uint64_t u0, uint64_t u1) {
+  if (u1 - u0 == kDUnit) return;  // block-uniform
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint64_t k = u0 + 4ull * ((uint32_t)q * kDT + threadIdx.x);
+    if (k < u1 && k + 4 > u1) {
+#pragma unroll
+      for (int j = 0; j < 3; ++j) x.v[4 * q + j] = k + j < u1 ? idx[k + j] : 0u;
+    }
+  }
+}
+
+// The entry before quad q: the previous lane's last, or the edge (wave_shr:1
+// keeps lane 0's own value).
+__device__ __forceinline__ uint32_t before_quad(const Quads& x, int q) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)x.edge[q], (int)x.v[4 * q + 3], 0x138, 0xF, 0xF, false);
+}
+
+// Entries of quad q below u1 (0 to 4).
+__device__ __forceinline__ uint32_t quad_len(uint64_t u0, uint64_t u1, int q) {
+  const uint64_t k = u0 + 4ull * ((uint32_t)q * kDT + threadIdx.x);
+  return k < u1 ? (uint32_t)(u1 - k < 4 ? u1 - k : 4) : 0u;
+}
+
+// Clears the bitmap and marks the items of [u0, u1) at which a segment starts,
+// from the tile's cached starts; nothing for a tile without any.  Every thread
+// calls it.  With starts in the tile it contains two barriers, the first after
+// the bitmap's clearing.  (Item 0 of the list needs no mark of its own: the
+// item before it reads as 0.)
+__device__ __forceinline__ void mark_unit(const uint64_t* starts, const SegCache& C, uint64_t u0, uint64_t u1,
+                                          uint32_t* bits) {
+  if (C.n == 0) return;  // block-uniform
+  for (uint32_t i = threadIdx.x; i < kDUnit / 32; i += kDT) bits[i] = 0;
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < C.n; i += kDT) {
+    const uint64_t v = start_of(starts, C, C.lo + i);
+    if (v >= u0 && v < u1) {
+      const uint32_t b = (uint32_t)(v - u0);
+      atomicOr(&bits[b >> 5], 1u << (b & 31));
+    }
+  }
+  __syncthreads();
+}
+
+// Marks of this thread's quads (bit 4 q + j), and of its sixteen consecutive items.
+__device__ __forceinline__ uint32_t quad_marks(const SegCache& C, const uint32_t* bits) {
+  if (C.n == 0) return 0u;
+  uint32_t m = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t i = 4u * ((uint32_t)q * kDT + threadIdx.x);
+    m |= ((bits[i >> 5] >> (i & 31)) & 0xFu) << (4 * q);
+  }
+  return m;
+}
+
+__device__ __forceinline__ uint32_t run_marks(const SegCache& C, const uint32_t* bits) {
+  if (C.n == 0) return 0u;
+  return (bits[threadIdx.x >> 1] >> (16 * (threadIdx.x & 1))) & 0xFFFFu;
+}
+
+// Exclusive positions of a unit's quads in list order (quad 0 of every thread,
+// then quad 1, ...) from their sizes (at most 2^16 / kDT each); *total receives
+// the unit's.  One barrier; s_w is rewritten by the next call but one.
+__device__ __forceinline__ void scan_quads(const uint32_t (&size)[4], uint2 (*s_w)[kDWaves], int parity,
+                                           uint32_t (&at)[4], uint32_t* total) {
+  const uint32_t a = size[0] | (size[1] << 16), b = size[2] | (size[3] << 16);
+  const uint32_t ia = wave_incl_scan(a), ib = wave_incl_scan(b);
+  const int wid = (int)threadIdx.x >> 6;
+  if (lane_id() == 63) s_w[parity][wid] = make_uint2(ia, ib);
+  __syncthreads();
+  uint32_t ba = 0, bb = 0, ta = 0, tb = 0;
+#pragma unroll
+  for (int w = 0; w < kDWaves; ++w) {
+    const uint2 x = s_w[parity][w];
+    ba += w < wid ? x.x : 0u;
+    bb += w < wid ? x.y : 0u;
+    ta += x.x;
+    tb += x.y;
+  }
+  const uint32_t ea = ba + ia - a, eb = bb + ib - b;
+  const uint32_t t0 = ta & 0xFFFFu, t1 = t0 + (ta >> 16), t2 = t1 + (tb & 0xFFFFu);
+  at[0] = ea & 0xFFFFu;
+  at[1] = t0 + (ea >> 16);
+  at[2] = t1 + (eb & 0xFFFFu);
+  at[3] = t2 + (eb >> 16);
+  *total = t2 + (tb >> 16);
+}
 
 // Grid of a tile kernel over a stream of at most `capacity` items.
 inline uint32_t tile_grid(uint64_t capacity) {

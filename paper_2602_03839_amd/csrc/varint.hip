@@ -14,10 +14,20 @@
 //
 // Both place each entry's output by an exclusive sum of per-entry sizes (its
 // varint length, or its pair count: 1 + its escapes, 0 for a segment's first
-// entry), computed reduce-then-scan over tiles of entries (stream_common.hpp):
-// a size pass per tile, one scan block, and an emit pass that recomputes the
-// sizes, stages the unit's output in LDS and writes it as one contiguous run.
-// The decoders are in decode.hip.
+// entry), computed reduce-then-write over tiles of entries (stream_common.hpp):
+// a size pass per tile, and an emit pass that recomputes the sizes and writes
+// the unit's output as one contiguous run.  The decoders are in decode.hip.
+//
+// A thread takes four quads of consecutive entries straight from memory; the
+// entry before a quad comes from the lane before.  A unit without a segment
+// start (nearly all of a large patch's) passes two barriers in the varint emit
+// pass and one in the COO's, whose pairs then lie where their entries do.
+// Measured against staging every entry in LDS and writing single bytes: 7B
+// set's patch (71M entries, 255 segments), varint size and emit 92 + 223 ->
+// 85 + 120 us; 0.5B set's (4.6M, 218), COO 20 + 44 -> 10 + 33 us, and no
+// launch between the passes (8 and 5 us).  The size pass is bound by reading
+// the list (285 MB at 3.3 TB/s while the caches write back what the call
+// before wrote); the emit passes by instruction issue and occupancy.
 #include "launch.hpp"
 #include "stream_common.hpp"
 
@@ -33,80 +43,25 @@ __device__ __forceinline__ uint32_t varint_len(uint32_t d) {
   return d < (1u << 7) ? 1u : d < (1u << 14) ? 2u : d < (1u << 21) ? 3u : d < (1u << 28) ? 4u : 5u;
 }
 
-// A unit of entries [u0, u1) staged in LDS (consecutive lanes load consecutive
-// entries) with the entry before it, and the segment starts among them.
-struct EntryLds {
-  uint32_t idx[padded(kDUnit + 1)];  // at pad(0) the entry before the unit, at pad(1 + i) entry u0 + i
-  uint32_t bits[kDUnit / 32];    // segment starts
-  uint32_t range[2];             // the segments starting in the unit
-  uint32_t w[kDWaves];
-  uint32_t tail[kDWaves * 16];   // size pass: each wave's last lane's entries
-  SegCache seg;                  // the segments starting in the tile
+struct Tile {
+  uint64_t nent, t0, t1;
+  bool some;  // this block has a tile
+  bool last;
+  uint32_t ntiles;
 };
 
-// A unit's entries as this thread loads them: entry u0 + tid + kDT * j in v[j]
-// (consecutive lanes, consecutive entries), and the entry before the unit.
-struct UnitEntries {
-  uint32_t v[16];
-  uint32_t before;
-};
-
-__device__ __forceinline__ UnitEntries load_unit(const uint32_t* idx, uint64_t u0, uint64_t u1) {
-  UnitEntries x;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const uint64_t k = u0 + threadIdx.x + (uint64_t)kDT * j;
-    x.v[j] = k < u1 ? idx[k] : 0u;
-  }
-  x.before = u0 > 0 ? idx[u0 - 1] : 0u;
-  return x;
-}
-
-// Stages the unit's entries in L.idx and marks its segment starts.  Every
-// thread calls it; it ends with a barrier.
-__device__ void stage_unit(const UnitEntries& x, const uint64_t* seg_begin, uint64_t u0, uint64_t u1,
-                           EntryLds& L) {
-  const uint32_t tid = threadIdx.x;
-  const uint32_t cnt = (uint32_t)(u1 - u0);
-  for (uint32_t i = tid; i < kDUnit / 32; i += kDT) L.bits[i] = 0;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const uint32_t i = tid + (uint32_t)kDT * j;
-    if (i < cnt) L.idx[pad(1 + i)] = x.v[j];
-  }
-  if (tid == 0) L.idx[pad(0)] = x.before;
-  __syncthreads();
-  mark_unit_starts(seg_begin, L.seg, u0, u1, L.bits, L.range);
-}
-
-// Size pass: the unit's entries stay where each thread loaded them (entry
-// u0 + tid + kDT * j in v[j]).  Publishes what lane 0 of each wave needs for
-// the entry before its own: the last lane's entries.  Every thread calls it
-// before the barrier that precedes the marking of the unit.
-__device__ __forceinline__ void publish_tail(const UnitEntries& x, EntryLds& L) {
-  if (lane_id() == 63) {
-    const uint32_t w = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) L.tail[w * 16 + j] = x.v[j];
-  }
-}
-
-// The entry before entry u0 + tid + kDT * j: the lane before holds it; lane 0
-// takes it from the wave before (or, in wave 0, from the last wave's entry of
-// round j - 1, or the entry before the unit).  Every lane calls it.
-__device__ __forceinline__ uint32_t entry_before(const UnitEntries& x, const EntryLds& L, int j) {
-  const uint32_t up = (uint32_t)__shfl_up((int)x.v[j], 1, 64);
-  if (lane_id() > 0) return up;
-  const uint32_t w = threadIdx.x >> 6;
-  if (w > 0) return L.tail[(w - 1) * 16 + j];
-  return j > 0 ? L.tail[(kDWaves - 1) * 16 + j - 1] : x.before;
-}
-
-// Staged entry i's number: its difference from the entry before (a segment's
-// first entry: the index itself).
-__device__ __forceinline__ uint32_t staged_diff(const EntryLds& L, uint32_t i) {
-  const uint32_t cur = L.idx[pad(1 + i)];
-  return bit_at(L.bits, i) ? cur : cur - L.idx[pad(i)];
+// This block's tile of the entries below min(*end, capacity).
+__device__ __forceinline__ Tile entry_tile(const uint64_t* end, uint64_t capacity) {
+  Tile t;
+  const uint64_t e = *end;
+  t.nent = e < capacity ? e : capacity;
+  const Geo g = stream_geometry(t.nent);
+  t.some = blockIdx.x < g.ntiles;
+  t.last = blockIdx.x + 1 == g.ntiles;
+  t.ntiles = g.ntiles;
+  t.t0 = (uint64_t)blockIdx.x * g.tile;
+  t.t1 = t.t0 + g.tile < t.nent ? t.t0 + g.tile : t.nent;
+  return t;
 }
 
 // A tensor's column count C with its reciprocal, for row = index / C.
@@ -134,376 +89,460 @@ __device__ __forceinline__ uint32_t div_cols(uint32_t x, const Cols& k) {
   return q;
 }
 
-// The 2-D COO pairs of one entry: cur its index, prev the entry before it, k
-// its tensor's column count.  *last receives its last pair (row field << 16 |
-// column field); returns its pair count.
-__device__ __forceinline__ uint32_t coo_pairs(bool start, uint32_t cur, uint32_t prev, const Cols& k,
-                                              uint32_t* last) {
-  if (start) {
-    *last = 0;
-    return 0;
+// A walk over a thread's entries of one tensor: the row and column of the last.
+struct CooAt {
+  uint32_t prev, col;
+};
+
+// The 2-D COO pairs of entry cur after the walk's last entry: the last pair (row
+// field << 16 | column field) in *last, and their number.  The columns between
+// two entries decide: less than a row apart, the next row is at most one away,
+// and no division is needed.
+__device__ __forceinline__ uint32_t coo_step(CooAt& at, uint32_t cur, const Cols& k, uint32_t* last) {
+  const uint32_t gap = cur - at.prev;
+  uint32_t np = 1;
+  if (gap < k.C) {
+    const uint32_t c = at.col + gap;
+    const bool next = c >= k.C;
+    *last = next ? (1u << 16) | (c - k.C + 1) : gap;
+    at.col = next ? c - k.C : c;
+  } else {
+    const uint32_t r = div_cols(cur, k), pr = div_cols(at.prev, k);
+    at.col = cur - r * k.C;
+    const uint32_t dr = r - pr;
+    if (cur < at.prev) {  // not ascending (outside the contract): one pair, no escapes
+      *last = 0;
+    } else {
+      const uint32_t esc = (dr - 1) / 255u;
+      *last = ((dr - 255u * esc) << 16) | (at.col + 1);
+      np += esc;
+    }
   }
-  const uint32_t C = k.C;
-  const uint32_t r = div_cols(cur, k), c = cur - r * C;
-  const uint32_t pr = div_cols(prev, k), pc = prev - pr * C;
-  if (r < pr) {  // not ascending (outside the contract): one pair, no escapes
-    *last = 0;
-    return 1;
-  }
-  const uint32_t dr = r - pr;
-  if (dr == 0) {
-    *last = c - pc;
-    return 1;
-  }
-  const uint32_t esc = (dr - 1) / 255u;
-  *last = ((dr - 255u * esc) << 16) | (c + 1);
-  return 1 + esc;
+  at.prev = cur;
+  return np;
 }
 
-
-// Block sum of one value per thread (every thread gets it).
-__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* s_w) {
-  uint32_t total;
-  (void)block_count_excl(v, s_w, &total);
-  return total;
+// The segment of entry k of a tile (its cached starts C): the last one starting
+// at or before it (0 if none).
+__device__ __forceinline__ uint32_t segment_at(const uint64_t* starts, const SegCache& C, uint64_t k) {
+  return segment_of(starts, C, C.lo, C.lo + C.n, k);
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------- delta-varint
 //
-// Ring word b: tile b's byte count, then its first byte.
+// Table word b: tile b's byte count.
 
 __global__ __launch_bounds__(kDT) void varint_size_kernel(VarintEncParams p) {
-  __shared__ EntryLds L;
-  const uint64_t e0 = *p.end;
-  const uint64_t nent = e0 < p.capacity ? e0 : p.capacity;
-  const Geo g = stream_geometry(nent);
-  if (blockIdx.x >= g.ntiles) return;
-  const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
-  const uint64_t t1 = t0 + g.tile < nent ? t0 + g.tile : nent;
-  cache_tile_segments(p.seg_begin, p.nseg, t0, t1, L.seg);
+  __shared__ uint32_t s_bits[kDUnit / 32];
+  __shared__ uint32_t s_w[kDWaves];
+  __shared__ SegCache s_seg;
+  const Tile t = entry_tile(p.end, p.capacity);
+  if (!t.some) return;
+  Quads x = load_quads(p.idx, t.t0, t.t1);
+  cache_tile_segments(p.seg_begin, p.nseg, t.t0, t.t1, s_seg);
   uint32_t bytes = 0;  // < 5 * tile
-  UnitEntries x = load_unit(p.idx, t0, t1);
-  for (uint64_t u0 = t0; u0 < t1; u0 += kDUnit) {
-    const uint64_t u1 = u0 + kDUnit < t1 ? u0 + kDUnit : t1;
-    const UnitEntries cur = x;
-    if (u1 < t1) x = load_unit(p.idx, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1);  // in flight
-    for (uint32_t i = threadIdx.x; i < kDUnit / 32; i += kDT) L.bits[i] = 0;
-    publish_tail(cur, L);
-    __syncthreads();
-    mark_unit_starts(p.seg_begin, L.seg, u0, u1, L.bits, L.range);
+  for (uint64_t u0 = t.t0; u0 < t.t1; u0 += kDUnit) {
+    const uint64_t u1 = u0 + kDUnit < t.t1 ? u0 + kDUnit : t.t1;
+    Quads cur = x;
+    x = load_quads(p.idx, u1, u1 + kDUnit < t.t1 ? u1 + kDUnit : t.t1);  // in flight (zeros past the tile)
+    finish_quads(cur, p.idx, u0, u1);
+    mark_unit(p.seg_begin, s_seg, u0, u1, s_bits);
+    const uint32_t marks = quad_marks(s_seg, s_bits);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const uint32_t i = threadIdx.x + (uint32_t)kDT * j;
-      const uint32_t before = entry_before(cur, L, j);
-      if (u0 + i < u1) bytes += varint_len(bit_at(L.bits, i) ? cur.v[j] : cur.v[j] - before);
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t before = before_quad(cur, q), m = quad_len(u0, u1, q);
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {
+        const uint32_t i = 4 * q + j;
+        const uint32_t d = cur.v[i] - ((marks >> i) & 1u ? 0u : j ? cur.v[i - 1] : before);
+        bytes += j < m ? varint_len(d) : 0u;
+      }
     }
-    __syncthreads();  // the bitmap is rewritten by the next unit
+    if (s_seg.n) __syncthreads();  // the bitmap is rewritten by the next unit
   }
-  const uint32_t total = block_sum(bytes, L.w);
-  if (threadIdx.x == 0) stream_ring(p.ws)[blockIdx.x] = total;
-}
-
-// One block: each tile's first byte, the stream's length, and the byte offset
-// of every segment that starts at or past the last entry.
-__global__ __launch_bounds__(kST) void varint_place_kernel(VarintEncParams p) {
-  __shared__ Sum64 s_w[kST / 64];
-  const uint64_t e0 = *p.end;
-  const uint64_t nent = e0 < p.capacity ? e0 : p.capacity;
-  const Geo g = stream_geometry(nent);
-  uint64_t* ring = stream_ring(p.ws);
-  Sum64 all;
-  single_block_scan<Sum64>(
-      g.ntiles, [&](uint32_t i) { return Sum64{ring[i]}; },
-      [&](uint32_t i, Sum64 x) { ring[i] = x.v; }, s_w, &all);
-  if (threadIdx.x == 0) *p.total = all.v;
-  if (p.seg_bytes && p.nseg > 0 && threadIdx.x < 64) {
-    const uint32_t from = lower_bound_wave(p.seg_begin, p.nseg, nent);
-    for (uint32_t s = from + (uint32_t)lane_id(); s < p.nseg; s += 64) p.seg_bytes[s] = all.v;
-  }
+  uint32_t total;
+  (void)block_count_excl(bytes, s_w, &total);
+  if (threadIdx.x == 0) stream_words(p.ws)[blockIdx.x] = total;
 }
 
 __global__ __launch_bounds__(kDT) void varint_emit_kernel(VarintEncParams p) {
-  __shared__ EntryLds L;
-  __shared__ uint8_t s_bytes[kStageBytes];
-  __shared__ uint32_t s_toff[kDT];   // byte offset of each thread's first entry in the unit
+  __shared__ uint32_t s_bits[kDUnit / 32];
+  __shared__ uint2 s_w[2][kDWaves];
+  __shared__ uint64_t s_w64[kDWaves];
+  __shared__ SegCache s_seg;
+  __shared__ __align__(16) uint8_t s_bytes[2][kStageBytes + 32];
   const int tid = (int)threadIdx.x;
-  const uint64_t e0 = *p.end;
-  const uint64_t nent = e0 < p.capacity ? e0 : p.capacity;
-  const Geo g = stream_geometry(nent);
-  if (blockIdx.x >= g.ntiles) return;
-  uint64_t* ring = stream_ring(p.ws);
-  uint64_t base = ring[blockIdx.x];
-  const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
-  const uint64_t t1 = t0 + g.tile < nent ? t0 + g.tile : nent;
-  UnitEntries x = load_unit(p.idx, t0, t1);
-  cache_tile_segments(p.seg_begin, p.nseg, t0, t1, L.seg);  // ends with a barrier: every
-  if (tid == 0) ring[blockIdx.x] = 0;                        // thread has read the tile's word
-  for (uint64_t u0 = t0; u0 < t1; u0 += kDUnit) {
-    const uint64_t u1 = u0 + kDUnit < t1 ? u0 + kDUnit : t1;
-    const uint32_t cnt = (uint32_t)(u1 - u0);
-    stage_unit(x, p.seg_begin, u0, u1, L);
-    if (u1 < t1) x = load_unit(p.idx, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1);  // in flight
-    // this thread's 16 consecutive entries: the lengths' sum, then (from the
-    // unit's exclusive sum) their bytes
-    const uint32_t i0 = (uint32_t)tid * 16u;
-    uint32_t d[16], sum = 0;
+  const Tile t = entry_tile(p.end, p.capacity);
+  if (!t.some) return;
+  Quads x = load_quads(p.idx, t.t0, t.t1);
+  uint64_t base = fold_before(stream_words(p.ws), blockIdx.x, s_w64);
+  cache_tile_segments(p.seg_begin, p.nseg, t.t0, t.t1, s_seg);
+  int buf = 0;
+  for (uint64_t u0 = t.t0; u0 < t.t1; u0 += kDUnit, buf ^= 1) {
+    const uint64_t u1 = u0 + kDUnit < t.t1 ? u0 + kDUnit : t.t1;
+    Quads cur = x;
+    x = load_quads(p.idx, u1, u1 + kDUnit < t.t1 ? u1 + kDUnit : t.t1);  // in flight (zeros past the tile)
+    finish_quads(cur, p.idx, u0, u1);
+    mark_unit(p.seg_begin, s_seg, u0, u1, s_bits);
+    const uint32_t marks = quad_marks(s_seg, s_bits);
+    uint32_t d[16], m[4], size[4], at[4], ubytes, top = 0;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      d[j] = i0 + j < cnt ? staged_diff(L, i0 + j) : 0u;
-      sum += i0 + j < cnt ? varint_len(d[j]) : 0u;
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t before = before_quad(cur, q);
+      m[q] = quad_len(u0, u1, q);
+      size[q] = 0;
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {
+        const uint32_t i = 4 * q + j;
+        d[i] = cur.v[i] - ((marks >> i) & 1u ? 0u : j ? cur.v[i - 1] : before);
+        if (j >= m[q]) d[i] = 0;
+        size[q] += j < m[q] ? varint_len(d[i]) : 0u;
+        top |= d[i];
+      }
     }
-    uint32_t ubytes;
-    uint32_t o = block_count_excl(sum, L.w, &ubytes);
-    s_toff[tid] = o;
+    scan_quads(size, s_w, buf, at, &ubytes);
     // The unit's bytes are one contiguous run [base, base + ubytes).  Up to
-    // kStageBytes of them (always, below ~3 bytes per index) are staged and
-    // written by consecutive lanes; a longer run is written by each thread for
-    // its own entries.
+    // kStageBytes of them (always, below ~3 bytes per index) are staged, at
+    // the alignment they have in memory, and written in aligned 16-byte
+    // chunks; a longer run is written by each thread for its own entries.
     const bool staged = ubytes <= kStageBytes;  // block-uniform
+    const uint32_t sh = (uint32_t)((uintptr_t)(p.out + base) & 15u);
     if (staged) {
+      uint8_t* const to = s_bytes[buf] + sh;
+      if (__ballot(top >= (1u << 14)) == 0) {
+        // one or two bytes each
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        if (i0 + j < cnt) {
-          uint32_t v = d[j];
-          const uint32_t len = varint_len(v);
-          for (uint32_t q = 0; q < len; ++q) {
-            s_bytes[o + q] = (uint8_t)((v & 0x7Fu) | (q + 1 < len ? 0x80u : 0u));
-            v >>= 7;
+        for (int q = 0; q < 4; ++q) {
+          uint32_t o = at[q];
+#pragma unroll
+          for (uint32_t j = 0; j < 4; ++j) {
+            const uint32_t v = d[4 * q + j];
+            if (j < m[q]) {
+              const bool two = v >= 128u;
+              to[o] = (uint8_t)((v & 0x7Fu) | (two ? 0x80u : 0u));
+              if (two) to[o + 1] = (uint8_t)(v >> 7);
+              o += two ? 2u : 1u;
+            }
           }
-          o += len;
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          uint32_t o = at[q];
+#pragma unroll
+          for (uint32_t j = 0; j < 4; ++j) {
+            uint32_t v = d[4 * q + j];
+            if (j < m[q]) {
+              const uint32_t len = varint_len(v);
+              for (uint32_t b = 0; b < len; ++b) {
+                to[o + b] = (uint8_t)((v & 0x7Fu) | (b + 1 < len ? 0x80u : 0u));
+                v >>= 7;
+              }
+              o += len;
+            }
+          }
         }
       }
     } else {
-      for (int j = 0; j < 16; ++j) {
-        if (i0 + j < cnt) {
-          uint32_t v = d[j];
-          const uint32_t len = varint_len(v);
-          for (uint32_t q = 0; q < len; ++q) {
-            if (base + o + q < p.out_capacity)
-              p.out[base + o + q] = (uint8_t)((v & 0x7Fu) | (q + 1 < len ? 0x80u : 0u));
-            v >>= 7;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint64_t o = base + at[q];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          uint32_t v = d[4 * q + j];
+          if (j < m[q]) {
+            const uint32_t len = varint_len(v);
+            for (uint32_t b = 0; b < len; ++b) {
+              if (o + b < p.out_capacity) p.out[o + b] = (uint8_t)((v & 0x7Fu) | (b + 1 < len ? 0x80u : 0u));
+              v >>= 7;
+            }
+            o += len;
           }
-          o += len;
+        }
+      }
+    }
+    // the byte offset of each segment that starts here, from the thread that
+    // holds its first entry
+    if (marks && p.seg_bytes) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint64_t k = u0 + 4ull * ((uint32_t)q * kDT + (uint32_t)tid);
+        uint64_t o = base + at[q];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          if ((marks >> (4 * q + j)) & 1u)
+            for (uint32_t s = lower_bound_cached(p.seg_begin, s_seg, k + j);
+                 s < s_seg.lo + s_seg.n && start_of(p.seg_begin, s_seg, s) == k + j; ++s)
+              p.seg_bytes[s] = o;
+          o += varint_len(d[4 * q + j]);
         }
       }
     }
     __syncthreads();
     if (staged) {
-      for (uint32_t b = (uint32_t)tid; b < ubytes; b += kDT) {
-        const uint64_t at = base + b;
-        if (at < p.out_capacity) p.out[at] = s_bytes[b];
-      }
-    }
-    // byte offset of each segment that starts in the unit: its entry's
-    // thread's offset plus the lengths of that thread's entries before it
-    if (p.seg_bytes && tid < 64) {
-      for (uint32_t s = L.range[0] + (uint32_t)lane_id(); s < L.range[1]; s += 64) {
-        const uint32_t i = (uint32_t)(start_of(p.seg_begin, L.seg, s) - u0);
-        uint32_t off = s_toff[i >> 4];
-        for (uint32_t q = i & ~15u; q < i; ++q)
-          off += varint_len(staged_diff(L, q));
-        p.seg_bytes[s] = base + off;
+      const uint8_t* const from = s_bytes[buf];
+      for (uint32_t c = (uint32_t)tid * 16; c < sh + ubytes; c += kDT * 16) {
+        const uint64_t g = base + c - sh;  // of the chunk's first byte (may lie before the unit)
+        if (c >= sh && c + 16 <= sh + ubytes && g + 16 <= p.out_capacity) {
+          *reinterpret_cast<uint4*>(p.out + g) = *reinterpret_cast<const uint4*>(from + c);
+        } else {
+          for (uint32_t b = c < sh ? sh : c; b < c + 16 && b < sh + ubytes; ++b)
+            if (base + (b - sh) < p.out_capacity) p.out[base + (b - sh)] = from[b];
+        }
       }
     }
     base += ubytes;
-    __syncthreads();  // the LDS arrays are rewritten by the next unit
+    // no barrier here: the next unit stages into the other buffer, and its
+    // scan's barrier separates this unit's copy from the unit after it
   }
+  if (t.last) {
+    // the stream's length, and the segments that start at or past the last entry
+    if (tid == 0) *p.total = base;
+    if (p.seg_bytes && p.nseg > 0 && tid < 64) {
+      const uint32_t from = lower_bound_wave(p.seg_begin, p.nseg, t.nent);
+      for (uint32_t s = from + (uint32_t)lane_id(); s < p.nseg; s += 64) p.seg_bytes[s] = base;
+    }
+  }
+  stream_finish(p.ws, t.ntiles, t.ntiles);
 }
 
 // ---------------------------------------------------------------- 2-D COO
 //
-// Ring word b: tile b's pair count, then its first pair.
+// Table word b: tile b's pair count.
+
+__device__ __forceinline__ Cols cols_at(const CooEncParams& p, const SegCache& C, uint64_t k) {
+  return make_cols(p.cols[segment_at(p.seg_begin, C, k)]);
+}
 
 __global__ __launch_bounds__(kDT) void coo_size_kernel(CooEncParams p) {
-  __shared__ EntryLds L;
-  const uint64_t e0 = *p.end;
-  const uint64_t nent = e0 < p.capacity ? e0 : p.capacity;
-  const Geo g = stream_geometry(nent);
-  if (blockIdx.x >= g.ntiles) return;
-  const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
-  const uint64_t t1 = t0 + g.tile < nent ? t0 + g.tile : nent;
-  cache_tile_segments(p.seg_begin, p.nseg, t0, t1, L.seg);
+  __shared__ uint32_t s_bits[kDUnit / 32];
+  __shared__ uint64_t s_w[kDWaves];
+  __shared__ SegCache s_seg;
+  const Tile t = entry_tile(p.end, p.capacity);
+  if (!t.some) return;
+  Quads x = load_quads(p.idx, t.t0, t.t1);
+  cache_tile_segments(p.seg_begin, p.nseg, t.t0, t.t1, s_seg);
+  const uint32_t c_first = p.cols[segment_at(p.seg_begin, s_seg, t.t0)];
   uint64_t pairs = 0;
-  uint32_t seg = 0xFFFFFFFFu;  // the tensor of this thread's last entry, and its columns
-  Cols cols = make_cols(1u);
-  UnitEntries x = load_unit(p.idx, t0, t1);
-  for (uint64_t u0 = t0; u0 < t1; u0 += kDUnit) {
-    const uint64_t u1 = u0 + kDUnit < t1 ? u0 + kDUnit : t1;
-    const UnitEntries cur = x;
-    if (u1 < t1) x = load_unit(p.idx, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1);  // in flight
-    for (uint32_t i = threadIdx.x; i < kDUnit / 32; i += kDT) L.bits[i] = 0;
-    publish_tail(cur, L);
-    __syncthreads();
-    mark_unit_starts(p.seg_begin, L.seg, u0, u1, L.bits, L.range);
-    const uint32_t lo = L.range[0], hi = L.range[1];
+  for (uint64_t u0 = t.t0; u0 < t.t1; u0 += kDUnit) {
+    const uint64_t u1 = u0 + kDUnit < t.t1 ? u0 + kDUnit : t.t1;
+    Quads cur = x;
+    x = load_quads(p.idx, u1, u1 + kDUnit < t.t1 ? u1 + kDUnit : t.t1);  // in flight (zeros past the tile)
+    finish_quads(cur, p.idx, u0, u1);
+    mark_unit(p.seg_begin, s_seg, u0, u1, s_bits);
+    const uint32_t marks = quad_marks(s_seg, s_bits);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const uint32_t i = threadIdx.x + (uint32_t)kDT * j;
-      const uint32_t before = entry_before(cur, L, j);
-      if (u0 + i < u1) {
-        const uint32_t s = segment_of(p.seg_begin, L.seg, lo, hi, u0 + i);
-        if (s != seg) {  // a new tensor for this thread (rare)
-          seg = s;
-          cols = make_cols(p.cols[s]);
+    for (int q = 0; q < 4; ++q) {
+      const uint64_t k = u0 + 4ull * ((uint32_t)q * kDT + threadIdx.x);
+      const uint32_t before = before_quad(cur, q), m = quad_len(u0, u1, q);
+      uint32_t C = c_first;
+      if (s_seg.n && m) C = p.cols[segment_at(p.seg_begin, s_seg, k)];
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {
+        const uint32_t i = 4 * q + j;
+        if (j < m) {
+          const uint32_t prev = j ? cur.v[i - 1] : before, v = cur.v[i];
+          if ((marks >> i) & 1u || k + j == 0) {
+            // a segment's first entry has no pair
+            if (j) C = p.cols[segment_at(p.seg_begin, s_seg, k + j)];
+          } else {
+            const uint32_t c = C > 0 ? C : 1u;
+            ++pairs;
+            // entries fewer than 255 rows apart have no escape, whatever their columns
+            if ((uint64_t)(v - prev) >= 255ull * c && v >= prev) pairs += (v / c - prev / c - 1) / 255u;
+          }
         }
-        uint32_t last;
-        pairs += coo_pairs(bit_at(L.bits, i), cur.v[j], before, cols, &last);
       }
     }
-    __syncthreads();  // the bitmap is rewritten by the next unit
+    if (s_seg.n) __syncthreads();  // the bitmap is rewritten by the next unit
   }
   // block sum (64-bit: escapes may be many)
-  const int lane = lane_id(), wid = (int)threadIdx.x >> 6;
   const uint64_t w = wave_sum_u64(pairs);
-  __shared__ uint64_t s_w[kDWaves];
-  if (lane == 0) s_w[wid] = w;
+  if (lane_id() == 0) s_w[threadIdx.x >> 6] = w;
   __syncthreads();
   if (threadIdx.x == 0) {
     uint64_t total = 0;
     for (int v = 0; v < kDWaves; ++v) total += s_w[v];
-    stream_ring(p.ws)[blockIdx.x] = total;
+    stream_words(p.ws)[blockIdx.x] = total;
   }
 }
 
-// One block: each tile's first pair, the stream's length, and the pair offset
-// (and first index 0) of every segment that starts at or past the last entry.
-__global__ __launch_bounds__(kST) void coo_place_kernel(CooEncParams p) {
-  __shared__ Sum64 s_w[kST / 64];
-  const uint64_t e0 = *p.end;
-  const uint64_t nent = e0 < p.capacity ? e0 : p.capacity;
-  const Geo g = stream_geometry(nent);
-  uint64_t* ring = stream_ring(p.ws);
-  Sum64 all;
-  single_block_scan<Sum64>(
-      g.ntiles, [&](uint32_t i) { return Sum64{ring[i]}; },
-      [&](uint32_t i, Sum64 x) { ring[i] = x.v; }, s_w, &all);
-  if (threadIdx.x == 0) *p.total = all.v;
-  if (threadIdx.x < 64) {
-    const uint32_t from = lower_bound_wave(p.seg_begin, p.nseg, nent);
-    for (uint32_t s = from + (uint32_t)lane_id(); s < p.nseg; s += 64) {
-      p.seg_pairs[s] = all.v;
-      p.first[s] = 0u;
-    }
-  }
-}
+// Four or eight bytes at any address (the compiler stores them as the target
+// takes them, from the declared alignment of 1).
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
+typedef uint32_t u32x2_a1 __attribute__((ext_vector_type(2), aligned(1)));
 
 __global__ __launch_bounds__(kDT) void coo_emit_kernel(CooEncParams p) {
-  __shared__ EntryLds L;
+  __shared__ uint32_t s_bits[kDUnit / 32];
+  __shared__ SegCache s_seg;
+  __shared__ uint32_t s_ent[padded(kDUnit + 1)];    // at pad(0) the entry before the unit, at pad(1 + i) entry i
   __shared__ uint32_t s_pairs[padded(kDUnit + 1)];  // the unit's pairs, pair q at pad(q)
-  __shared__ uint64_t s_toff[kDT];  // pair offset of each thread's first entry in the unit
   __shared__ Sum64 s_w64[kDWaves];
+  __shared__ uint64_t s_wf[kDWaves];
   const int tid = (int)threadIdx.x;
-  const uint64_t e0 = *p.end;
-  const uint64_t nent = e0 < p.capacity ? e0 : p.capacity;
-  const Geo g = stream_geometry(nent);
-  if (blockIdx.x >= g.ntiles) return;
-  uint64_t* ring = stream_ring(p.ws);
-  uint64_t base = ring[blockIdx.x];
-  const uint64_t t0 = (uint64_t)blockIdx.x * g.tile;
-  const uint64_t t1 = t0 + g.tile < nent ? t0 + g.tile : nent;
-  UnitEntries x = load_unit(p.idx, t0, t1);
-  cache_tile_segments(p.seg_begin, p.nseg, t0, t1, L.seg);  // ends with a barrier: every
-  if (tid == 0) ring[blockIdx.x] = 0;                        // thread has read the tile's word
-  for (uint64_t u0 = t0; u0 < t1; u0 += kDUnit) {
-    const uint64_t u1 = u0 + kDUnit < t1 ? u0 + kDUnit : t1;
-    const uint32_t cnt = (uint32_t)(u1 - u0);
-    stage_unit(x, p.seg_begin, u0, u1, L);
-    if (u1 < t1) x = load_unit(p.idx, u1, u1 + kDUnit < t1 ? u1 + kDUnit : t1);  // in flight
-    // this thread's 16 consecutive entries: the pair counts' sum, then (from
-    // the unit's exclusive sum) their pairs
-    const uint32_t lo = L.range[0], hi = L.range[1];
-    const uint32_t i0 = (uint32_t)tid * 16u;
-    Cols cols0 = make_cols(1u);
-    if (i0 < cnt) cols0 = make_cols(p.cols[segment_of(p.seg_begin, L.seg, lo, hi, u0 + i0)]);
-    uint32_t sum = 0;
-    Cols cols = cols0;
-#pragma unroll 4
-    for (int j = 0; j < 16; ++j) {
-      const uint32_t i = i0 + (uint32_t)j;
-      if (i < cnt) {
-        const bool start = bit_at(L.bits, i);
-        if (start && i != i0) cols = make_cols(p.cols[segment_of(p.seg_begin, L.seg, lo, hi, u0 + i)]);
-        uint32_t last;
-        sum += coo_pairs(start, L.idx[pad(1 + i)], L.idx[pad(i)], cols, &last);
+  const Tile t = entry_tile(p.end, p.capacity);
+  if (!t.some) return;
+  Quads x = load_quads(p.idx, t.t0, t.t1);
+  uint64_t base = fold_before(stream_words(p.ws), blockIdx.x, s_wf);
+  cache_tile_segments(p.seg_begin, p.nseg, t.t0, t.t1, s_seg);
+  const Cols c_first = cols_at(p, s_seg, t.t0);
+  for (uint64_t u0 = t.t0; u0 < t.t1; u0 += kDUnit) {
+    const uint64_t u1 = u0 + kDUnit < t.t1 ? u0 + kDUnit : t.t1;
+    Quads cur = x;
+    x = load_quads(p.idx, u1, u1 + kDUnit < t.t1 ? u1 + kDUnit : t.t1);  // in flight (zeros past the tile)
+    finish_quads(cur, p.idx, u0, u1);
+    mark_unit(p.seg_begin, s_seg, u0, u1, s_bits);
+    // A unit of one segment whose entries lie fewer than 255 rows apart has one
+    // pair for each: they lie where the entries do, and if all of them fit the
+    // buffer they are written at once.
+    bool one = s_seg.n == 0 && u0 > 0;
+    const uint64_t far = 255ull * c_first.C;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t before = before_quad(cur, q), m = quad_len(u0, u1, q);
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {
+        const uint32_t gap = cur.v[4 * q + j] - (j ? cur.v[4 * q + j - 1] : before);
+        one &= j >= m || (uint64_t)gap < far;
       }
     }
+    if (__syncthreads_and(one) && base + (u1 - u0) <= p.out_capacity) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint64_t g = base + 4ull * ((uint32_t)q * kDT + (uint32_t)tid);
+        const uint32_t m = quad_len(u0, u1, q), before = before_quad(cur, q);
+        CooAt at{before, before - div_cols(before, c_first) * c_first.C};
+        uint32_t l[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          l[j] = 0;
+          if (j < m) (void)coo_step(at, cur.v[4 * q + j], c_first, &l[j]);
+        }
+        if (m == 4) {
+          *reinterpret_cast<u32_a1*>(p.drow + g) =
+              (l[0] >> 16) | ((l[1] >> 16) << 8) | ((l[2] >> 16) << 16) | ((l[3] >> 16) << 24);
+          *reinterpret_cast<u32x2_a1*>(p.dcol + g) =
+              u32x2_a1{(l[0] & 0xFFFFu) | (l[1] << 16), (l[2] & 0xFFFFu) | (l[3] << 16)};
+        } else {
+#pragma unroll
+          for (uint32_t j = 0; j < 3; ++j) {
+            if (j < m) {
+              p.drow[g + j] = (uint8_t)(l[j] >> 16);
+              p.dcol[g + j] = (uint16_t)l[j];
+            }
+          }
+        }
+      }
+      base += u1 - u0;
+      continue;
+    }
+    // The general unit: its entries go through LDS, a thread takes sixteen
+    // consecutive ones in loops that are not unrolled (unrolled, this path's
+    // registers left two waves per SIMD to the one above: 41 us instead of 33
+    // for the 0.5B set's patch).
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t i = 4u * ((uint32_t)q * kDT + (uint32_t)tid);
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) s_ent[pad(1 + i + j)] = cur.v[4 * q + j];
+    }
+    if (tid == 0) s_ent[pad(0)] = cur.edge[0];
+    __syncthreads();
+    const uint32_t run = run_marks(s_seg, s_bits);
+    const uint32_t i0 = 16u * (uint32_t)tid;
+    const uint64_t k0 = u0 + i0;
+    const uint32_t m = k0 < u1 ? (uint32_t)(u1 - k0 < 16 ? u1 - k0 : 16) : 0u;
+    // f(entry, its last pair, its pairs: one and its escapes, none for a
+    // segment's first entry)
+    auto walk = [&](auto f) {
+      Cols c = c_first;
+      if (s_seg.n && m) c = cols_at(p, s_seg, k0);
+      const uint32_t before = s_ent[pad(i0)];
+      CooAt at{before, before - div_cols(before, c) * c.C};
+#pragma unroll 1
+      for (uint32_t j = 0; j < m; ++j) {
+        const uint32_t v = s_ent[pad(1 + i0 + j)];
+        uint32_t last = 0, np = 0;
+        if ((run >> j) & 1u || k0 + j == 0) {
+          if (j) c = cols_at(p, s_seg, k0 + j);
+          at.prev = v;
+          at.col = v - div_cols(v, c) * c.C;
+        } else {
+          np = coo_step(at, v, c, &last);
+        }
+        f(j, v, last, np);
+      }
+    };
+    uint64_t sum = 0;
+    walk([&](uint32_t, uint32_t, uint32_t, uint32_t np) { sum += np; });
     // 64-bit offsets: valid lists keep a unit's pairs far below 2^32, but an
     // unsorted one need not, and positions must stay exact for the bounds
     // checks below to bound the work
     Sum64 all;
-    const uint64_t first_off = block_scan_excl<kDT>(Sum64{sum}, Sum64::id(), s_w64, &all).v;
+    uint64_t at = block_scan_excl<kDT>(Sum64{sum}, Sum64::id(), s_w64, &all).v;
     const uint64_t upairs = all.v;
-    s_toff[tid] = first_off;
-    // The unit's pairs are one contiguous run [base, base + upairs).  Without
-    // long escapes it fits s_pairs (as row field << 16 | column field) and
-    // consecutive lanes write consecutive pairs; otherwise each thread writes
-    // its own entries' pairs, stopping at the output capacity, so the work
-    // stays bounded by the buffer even for a list outside the contract.
+    // Without long escapes the unit's pairs fit s_pairs (as row field << 16 |
+    // column field) and consecutive lanes write consecutive pairs; otherwise
+    // each thread writes its own entries' pairs, stopping at the output
+    // capacity, so the work stays bounded by the buffer even for a list
+    // outside the contract.
     const bool staged = upairs <= kDUnit + 1;
-    uint64_t o = first_off;
-    cols = cols0;
-#pragma unroll 4
-    for (int j = 0; j < 16; ++j) {
-      const uint32_t i = i0 + (uint32_t)j;
-      if (i < cnt) {
-        const bool start = bit_at(L.bits, i);
-        if (start && i != i0) cols = make_cols(p.cols[segment_of(p.seg_begin, L.seg, lo, hi, u0 + i)]);
-        uint32_t last;
-        const uint32_t np = coo_pairs(start, L.idx[pad(1 + i)], L.idx[pad(i)], cols, &last);
-        for (uint32_t q = 0; q < np; ++q) {
-          const uint32_t pair = q + 1 < np ? (255u << 16) : last;
-          if (staged) {
-            s_pairs[pad((uint32_t)o + q)] = pair;
-          } else {
-            const uint64_t at = base + o + q;
-            if (at >= p.out_capacity) break;
-            p.drow[at] = (uint8_t)(pair >> 16);
-            p.dcol[at] = (uint16_t)(pair & 0xFFFFu);
-          }
+    walk([&](uint32_t j, uint32_t v, uint32_t l, uint32_t n) {
+      // segments starting here: their pair offset and first index, from the
+      // thread that holds their first entry
+      if ((run >> j) & 1u) {
+        for (uint32_t s = lower_bound_cached(p.seg_begin, s_seg, k0 + j);
+             s < s_seg.lo + s_seg.n && start_of(p.seg_begin, s_seg, s) == k0 + j; ++s) {
+          const uint64_t e = s + 1 < p.nseg ? p.seg_begin[s + 1] : t.nent;
+          p.seg_pairs[s] = base + at;
+          p.first[s] = e > k0 + j ? v : 0u;
         }
-        o += np;
       }
-    }
+      if (staged) {
+        for (uint32_t r = 0; r + 1 < n; ++r) s_pairs[pad((uint32_t)at + r)] = 255u << 16;
+        if (n) s_pairs[pad((uint32_t)at + n - 1)] = l;
+      } else {
+        for (uint32_t r = 0; r < n && base + at + r < p.out_capacity; ++r) {
+          p.drow[base + at + r] = (uint8_t)(r + 1 < n ? 255u : l >> 16);
+          p.dcol[base + at + r] = (uint16_t)(r + 1 < n ? 0u : l);
+        }
+      }
+      at += n;
+    });
     __syncthreads();
-    // segments starting in this unit: their pair offset (their first entry's
-    // thread's offset plus that thread's pairs before it) and first index
-    if (tid < 64) {
-      for (uint32_t s = lo + (uint32_t)lane_id(); s < hi; s += 64) {
-        const uint64_t b = start_of(p.seg_begin, L.seg, s);
-        const uint64_t e = s + 1 < p.nseg ? p.seg_begin[s + 1] : nent;
-        const uint32_t i = (uint32_t)(b - u0);
-        uint64_t off = s_toff[i >> 4];
-        for (uint32_t q = i & ~15u; q < i; ++q) {
-          uint32_t last;
-          const Cols c = make_cols(p.cols[segment_of(p.seg_begin, L.seg, lo, hi, u0 + q)]);
-          off += coo_pairs(bit_at(L.bits, q), L.idx[pad(1 + q)], L.idx[pad(q)], c, &last);
-        }
-        p.seg_pairs[s] = base + off;
-        p.first[s] = e > b ? L.idx[pad(1 + i)] : 0u;
-      }
-    }
     if (staged) {
       for (uint32_t q = (uint32_t)tid; q < (uint32_t)upairs; q += kDT) {
-        const uint64_t at = base + q;
-        if (at < p.out_capacity) {
+        const uint64_t g = base + q;
+        if (g < p.out_capacity) {
           const uint32_t pair = s_pairs[pad(q)];
-          p.drow[at] = (uint8_t)(pair >> 16);
-          p.dcol[at] = (uint16_t)(pair & 0xFFFFu);
+          p.drow[g] = (uint8_t)(pair >> 16);
+          p.dcol[g] = (uint16_t)(pair & 0xFFFFu);
         }
       }
     }
+    __syncthreads();  // s_ent, s_pairs and the bitmap are rewritten by a later unit
     base += upairs;
-    __syncthreads();  // the LDS arrays are rewritten by the next unit
   }
+  if (t.last) {
+    // the stream's length, and the pair offset (and first index 0) of every
+    // segment that starts at or past the last entry
+    if (tid == 0) *p.total = base;
+    if (tid < 64) {
+      const uint32_t from = lower_bound_wave(p.seg_begin, p.nseg, t.nent);
+      for (uint32_t s = from + (uint32_t)lane_id(); s < p.nseg; s += 64) {
+        p.seg_pairs[s] = base;
+        p.first[s] = 0u;
+      }
+    }
+  }
+  stream_finish(p.ws, t.ntiles, t.ntiles);
 }
 
 hipError_t launch_varint_encode(const VarintEncParams& p, hipStream_t stream) {
   const uint32_t grid = tile_grid(p.capacity);
   hipLaunchKernelGGL(varint_size_kernel, dim3(grid), dim3(kDT), 0, stream, p);
-  if (hipError_t e = hipGetLastError()) return e;
-  hipLaunchKernelGGL(varint_place_kernel, dim3(1), dim3(kST), 0, stream, p);
   if (hipError_t e = hipGetLastError()) return e;
   hipLaunchKernelGGL(varint_emit_kernel, dim3(grid), dim3(kDT), 0, stream, p);
   return hipGetLastError();
@@ -512,8 +551,6 @@ hipError_t launch_varint_encode(const VarintEncParams& p, hipStream_t stream) {
 hipError_t launch_coo_encode(const CooEncParams& p, hipStream_t stream) {
   const uint32_t grid = tile_grid(p.capacity);
   hipLaunchKernelGGL(coo_size_kernel, dim3(grid), dim3(kDT), 0, stream, p);
-  if (hipError_t e = hipGetLastError()) return e;
-  hipLaunchKernelGGL(coo_place_kernel, dim3(1), dim3(kST), 0, stream, p);
   if (hipError_t e = hipGetLastError()) return e;
   hipLaunchKernelGGL(coo_emit_kernel, dim3(grid), dim3(kDT), 0, stream, p);
   return hipGetLastError();
