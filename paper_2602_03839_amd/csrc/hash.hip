@@ -13,12 +13,13 @@
 // 64-byte block, ~26 per byte, so the kernel is bound by the vector ALU, not
 // by HBM (it reads 2 bytes per parameter once).  One lane hashes one leaf;
 // lanes of a wave hash neighbouring leaves, 16 KiB apart, and each lane reads
-// its own 64-byte blocks with 16-byte loads.
+// its own 64-byte blocks with 16-byte loads, a block ahead.
 //
 // Kernels:
 //   hash_setup_kernel  writes the tensor table and gathers the leaves that
 //                      cross a tensor boundary into scratch slots;
 //   hash_leaf_kernel   one lane per leaf: its digest;
+//   hash_leaf_pair_kernel  the same for few leaves, two lanes' waves per leaf;
 //   hash_tree_kernel   one block per 512 digests: the 9 tree levels above
 //                      them, in LDS; the host repeats it until one remains.
 #include "launch.hpp"
@@ -119,6 +120,42 @@ __device__ __forceinline__ void sha256_block(uint32_t (&st)[8], uint32_t (&w)[16
   st[7] += h;
 }
 
+// The 64 rounds alone, on wk[t] = message schedule word + round constant, which
+// get(t / 4) hands out four at a time.
+template <typename Get>
+__device__ __forceinline__ void sha256_rounds(uint32_t (&st)[8], Get get) {
+  uint32_t a = st[0], b = st[1], c = st[2], d = st[3];
+  uint32_t e = st[4], f = st[5], g = st[6], h = st[7];
+#pragma unroll
+  for (int t4 = 0; t4 < 16; ++t4) {
+    const uint4 q = get(t4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t wk = i == 0 ? q.x : i == 1 ? q.y : i == 2 ? q.z : q.w;
+      const uint32_t S1 = xor3(rotr(e, 6), rotr(e, 11), rotr(e, 25));
+      const uint32_t t1 = (h + wk) + S1 + ch(e, f, g);
+      const uint32_t S0 = xor3(rotr(a, 2), rotr(a, 13), rotr(a, 22));
+      const uint32_t t2 = S0 + maj(a, b, c);
+      h = g;
+      g = f;
+      f = e;
+      e = d + t1;
+      d = c;
+      c = b;
+      b = a;
+      a = t1 + t2;
+    }
+  }
+  st[0] += a;
+  st[1] += b;
+  st[2] += c;
+  st[3] += d;
+  st[4] += e;
+  st[5] += f;
+  st[6] += g;
+  st[7] += h;
+}
+
 __device__ __forceinline__ void sha256_init(uint32_t (&st)[8]) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) st[i] = kSha.h0[i];
@@ -135,7 +172,21 @@ __global__ __launch_bounds__(256) void hash_setup_kernel(HashSetupParams p) {
   if (blockIdx.x >= p.njobs) return;
   const HashCopyJob j = p.jobs[blockIdx.x];
   uint16_t* dst = (uint16_t*)(p.scratch + j.dst);
-  for (uint64_t i = threadIdx.x; i < j.count; i += blockDim.x) dst[i] = j.src[i];
+  // eight loads in flight per thread (one at a time: 7.5 us for a full leaf)
+  constexpr int kAt = 8;
+  for (uint64_t i0 = threadIdx.x; i0 < j.count; i0 += kAt * blockDim.x) {
+    uint16_t v[kAt];
+#pragma unroll
+    for (int q = 0; q < kAt; ++q) {
+      const uint64_t i = i0 + (uint64_t)q * blockDim.x;
+      v[q] = j.src[i < j.count ? i : 0];
+    }
+#pragma unroll
+    for (int q = 0; q < kAt; ++q) {
+      const uint64_t i = i0 + (uint64_t)q * blockDim.x;
+      if (i < j.count) dst[i] = v[q];
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -145,13 +196,19 @@ __global__ __launch_bounds__(256) void hash_setup_kernel(HashSetupParams p) {
 // word of the source and three bytes of the next, put in order by one
 // v_perm_b32.  A leaf whose source starts 2 bytes into a word (after a tensor
 // of odd length) takes the other byte selector.
-__global__ __launch_bounds__(256) void hash_leaf_kernel(HashLeafParams p) {
-  const uint64_t l = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= p.nleaves) return;
+struct LeafSource {
+  // base[0 .. dmax] hold the leaf's bytes, starting sh bytes into base[0];
+  // message word k pairs base[k - 1 + o] with base[k + o] by selector sel
+  const uint32_t* base;
+  uint32_t sel, prev, o, dmax;
+  uint32_t len;  // bytes
+};
+
+__device__ __forceinline__ LeafSource leaf_source(const HashLeafParams& p, uint64_t l) {
   const uint64_t x = l * kHashLeafElems;
   const uint64_t le = p.total - x < kHashLeafElems ? p.total - x : kHashLeafElems;
-  const uint32_t len = (uint32_t)(2 * le);
-
+  LeafSource s;
+  s.len = (uint32_t)(2 * le);
   uint32_t lo = 0, hi = p.ntensors;
   while (hi - lo > 1) {
     const uint32_t mid = (lo + hi) >> 1;
@@ -160,33 +217,71 @@ __global__ __launch_bounds__(256) void hash_leaf_kernel(HashLeafParams p) {
   }
   const HashEntry t = p.table[lo];
   const uint64_t end = p.table[lo + 1].off;
-
-  // Source words: base[0 .. dmax] hold the leaf's bytes, starting sh bytes
-  // into base[0]; message word k pairs base[k - 1 + o] with base[k + o].
-  const uint32_t* base;
-  uint32_t sel, prev, o, dmax;
   if (hash_leaf_in_place(x, le, t.off, end)) {
     const uintptr_t A = (uintptr_t)(t.ptr + (x - t.off));
     const uint32_t sh = (uint32_t)(A & 3);  // 0 or 2
-    base = (const uint32_t*)(A - sh);
-    o = sh >> 1;
-    prev = sh ? (base[0] & 0xFFFF0000u) : 0u;  // the bytes before the leaf read as the prefix 0
-    sel = sh ? 0x05060700u : 0x07000102u;
-    dmax = (sh + len + 3) / 4 - 1;
+    s.base = (const uint32_t*)(A - sh);
+    s.o = sh >> 1;
+    s.prev = sh ? (s.base[0] & 0xFFFF0000u) : 0u;  // the bytes before the leaf read as the prefix 0
+    s.sel = sh ? 0x05060700u : 0x07000102u;
+    s.dmax = (sh + s.len + 3) / 4 - 1;
   } else {
-    base = (const uint32_t*)(p.scratch + (uint64_t)lo * kHashLeafBytes);
-    o = 0;
-    prev = 0u;
-    sel = 0x07000102u;
-    dmax = (len + 3) / 4 - 1;
+    s.base = (const uint32_t*)(p.scratch + (uint64_t)lo * kHashLeafBytes);
+    s.o = 0;
+    s.prev = 0u;
+    s.sel = 0x07000102u;
+    s.dmax = (s.len + 3) / 4 - 1;
   }
+  return s;
+}
 
+// Blocks of a leaf's message of len + 1 bytes (the prefix): those made of
+// message bytes only, and all of them with the padding.
+__device__ __forceinline__ uint32_t full_blocks(uint32_t len) { return (len + 1) / 64; }
+__device__ __forceinline__ uint32_t all_blocks(uint32_t len) { return (len + 1 + 1 + 8 + 63) / 64; }
+
+// Block b of the message's end: its tail, the byte 0x80, zeros and the bit
+// length (FIPS 180-4 5.1.1).  Reads are clamped to base[dmax]; the bytes past
+// the message that such a read brings in are masked off.
+__device__ __forceinline__ void tail_block(const LeafSource& s, uint32_t b, uint32_t& prev, uint32_t (&w)[16]) {
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const uint32_t k = 16 * b + j;
+    const uint32_t cur = ((gword)s.base)[k + s.o < s.dmax ? k + s.o : s.dmax];
+    uint32_t word = __builtin_amdgcn_perm(prev, cur, s.sel);
+    prev = cur;
+    const int nb = (int)(s.len + 1) - (int)(4 * k);  // message bytes left at this word
+    word &= nb >= 4 ? 0xFFFFFFFFu : nb <= 0 ? 0u : ~(0xFFFFFFFFu >> (8 * nb));
+    if (nb >= 0 && nb < 4) word |= 0x80u << (24 - 8 * nb);
+    w[j] = word;
+  }
+  if (b == all_blocks(s.len) - 1) {
+    w[14] = 0;
+    w[15] = 8 * (s.len + 1);
+  }
+}
+
+__device__ __forceinline__ void store_digest(uint8_t* digests, uint64_t l, const uint32_t (&st)[8]) {
+  uint32_t* out = (uint32_t*)(digests + 32 * l);
+  u32x4_a4 o0 = {__builtin_bswap32(st[0]), __builtin_bswap32(st[1]), __builtin_bswap32(st[2]),
+                 __builtin_bswap32(st[3])};
+  u32x4_a4 o1 = {__builtin_bswap32(st[4]), __builtin_bswap32(st[5]), __builtin_bswap32(st[6]),
+                 __builtin_bswap32(st[7])};
+  *(u32x4_a4*)out = o0;
+  *(u32x4_a4*)(out + 4) = o1;
+}
+
+__global__ __launch_bounds__(256) void hash_leaf_kernel(HashLeafParams p) {
+  const uint64_t l = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (l >= p.nleaves) return;
+  const LeafSource src = leaf_source(p, l);
+  const uint32_t nfull = full_blocks(src.len);
+  uint32_t prev = src.prev;
   uint32_t st[8];
   sha256_init(st);
-  const uint32_t nfull = (len + 1) / 64;  // blocks made of message bytes only
-  for (uint32_t b = 0; b < nfull; ++b) {
-    const gvec q = (gvec)(base + 16 * b + o);
-    uint32_t d[16];
+  uint32_t d[16];
+  auto load = [&](const uint32_t* at) {
+    const gvec q = (gvec)at;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const u32x4_a4 v = __builtin_nontemporal_load(q + i);
@@ -195,44 +290,112 @@ __global__ __launch_bounds__(256) void hash_leaf_kernel(HashLeafParams p) {
       d[4 * i + 2] = v.z;
       d[4 * i + 3] = v.w;
     }
+  };
+  // The next block's loads are in flight during each compression: with few waves
+  // per SIMD nothing else hides them (0.5B set 982 -> 895 us, 7B set 10.87 ->
+  // 10.76 ms).
+  if (nfull > 0) load(src.base + src.o);
+  for (uint32_t b = 0; b < nfull; ++b) {
     uint32_t w[16];
-    w[0] = __builtin_amdgcn_perm(prev, d[0], sel);
+    w[0] = __builtin_amdgcn_perm(prev, d[0], src.sel);
 #pragma unroll
-    for (int j = 1; j < 16; ++j) w[j] = __builtin_amdgcn_perm(d[j - 1], d[j], sel);
+    for (int j = 1; j < 16; ++j) w[j] = __builtin_amdgcn_perm(d[j - 1], d[j], src.sel);
     prev = d[15];
+    load(src.base + 16 * (b + 1 < nfull ? b + 1 : b) + src.o);
     sha256_block(st, w);
   }
-  // The last one or two blocks: the message's tail, the byte 0x80, zeros and
-  // the bit length (FIPS 180-4 5.1.1).  Reads are clamped to base[dmax]; the
-  // bytes past the message that such a read brings in are masked off.
-  const uint32_t nblocks = (len + 1 + 1 + 8 + 63) / 64;
+  const uint32_t nblocks = all_blocks(src.len);
   for (uint32_t b = nfull; b < nblocks; ++b) {
     uint32_t w[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const uint32_t k = 16 * b + j;
-      const uint32_t cur = ((gword)base)[k + o < dmax ? k + o : dmax];
-      uint32_t word = __builtin_amdgcn_perm(prev, cur, sel);
-      prev = cur;
-      const int nb = (int)(len + 1) - (int)(4 * k);  // message bytes left at this word
-      word &= nb >= 4 ? 0xFFFFFFFFu : nb <= 0 ? 0u : ~(0xFFFFFFFFu >> (8 * nb));
-      if (nb >= 0 && nb < 4) word |= 0x80u << (24 - 8 * nb);
-      w[j] = word;
-    }
-    if (b == nblocks - 1) {
-      w[14] = 0;
-      w[15] = 8 * (len + 1);
-    }
+    tail_block(src, b, prev, w);
     sha256_block(st, w);
   }
+  store_digest(p.digests, l, st);
+}
 
-  uint32_t* out = (uint32_t*)(p.digests + 32 * l);
-  u32x4_a4 o0 = {__builtin_bswap32(st[0]), __builtin_bswap32(st[1]), __builtin_bswap32(st[2]),
-                 __builtin_bswap32(st[3])};
-  u32x4_a4 o1 = {__builtin_bswap32(st[4]), __builtin_bswap32(st[5]), __builtin_bswap32(st[6]),
-                 __builtin_bswap32(st[7])};
-  *(u32x4_a4*)out = o0;
-  *(u32x4_a4*)(out + 4) = o1;
+// Few leaves: two waves per 64 leaves.  A leaf is one chain of 257 blocks, and a
+// SIMD with one wave of such chains issues an instruction every five cycles (at
+// best every four), however little there is to hash.  One wave forms the
+// message schedules, a block ahead, and leaves them in LDS with the round
+// constants added; the other has only the rounds to do.  Whole call, one wave
+// per 64 leaves / two: 1M values 691 / 531 us, 200M 855 / 667; where a CU gets
+// more than one such block (four waves, 128 leaves) the pairs lose: 300M
+// 881 / 940.
+constexpr uint64_t kPairLeaves = 128ull * 256;  // one block on each of the 256 CUs
+__device__ __align__(16) const uint32_t kHashZero[16] = {0};
+
+__global__ __launch_bounds__(256) void hash_leaf_pair_kernel(HashLeafParams p) {
+  __shared__ uint4 s_wk[2][2][16][64];  // [buffer][pair][schedule words 4 i .. 4 i + 3][leaf]
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  // two pairs per block, a wave on each SIMD
+  const uint32_t pair = wave & 1u;
+  const bool schedules = wave >= 2;
+  const uint64_t b0 = (uint64_t)blockIdx.x * 128, l0 = b0 + pair * 64;
+  const uint64_t l = l0 + lane < p.nleaves ? l0 + lane : p.nleaves - 1;  // (the last one again)
+  // the block's first leaf is its longest: all waves walk that many blocks
+  const uint64_t x0 = b0 * kHashLeafElems;
+  const uint32_t nb = all_blocks((uint32_t)(2 * (p.total - x0 < kHashLeafElems ? p.total - x0 : kHashLeafElems)));
+  if (schedules) {
+    const LeafSource src = leaf_source(p, l);
+    const uint32_t nfull = full_blocks(src.len);
+    uint32_t prev = src.prev;
+    uint32_t d[16];
+    auto load = [&](uint32_t b) {  // unconditional, so that it stays in flight
+      const gvec q = (gvec)(b < nfull ? src.base + 16 * b + src.o : kHashZero);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const u32x4_a4 v = q[i];
+        d[4 * i] = v.x;
+        d[4 * i + 1] = v.y;
+        d[4 * i + 2] = v.z;
+        d[4 * i + 3] = v.w;
+      }
+    };
+    load(0);
+    for (uint32_t b = 0; b < nb; ++b) {
+      uint32_t w[16];
+      if (b < nfull) {
+        w[0] = __builtin_amdgcn_perm(prev, d[0], src.sel);
+#pragma unroll
+        for (int j = 1; j < 16; ++j) w[j] = __builtin_amdgcn_perm(d[j - 1], d[j], src.sel);
+        prev = d[15];
+      } else {
+        tail_block(src, b, prev, w);
+      }
+      load(b + 1);
+      uint4(*const to)[64] = s_wk[b & 1][pair];
+#pragma unroll
+      for (int t4 = 0; t4 < 16; ++t4) {
+        uint32_t wk[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int t = 4 * t4 + i;
+          if (t >= 16) {
+            const uint32_t x = w[(t - 15) & 15], y = w[(t - 2) & 15];
+            const uint32_t s0 = xor3(rotr(x, 7), rotr(x, 18), x >> 3);
+            const uint32_t s1 = xor3(rotr(y, 17), rotr(y, 19), y >> 10);
+            w[t & 15] = w[t & 15] + s0 + w[(t - 7) & 15] + s1;
+          }
+          wk[i] = w[t & 15] + kSha.k[t];
+        }
+        to[t4][lane] = make_uint4(wk[0], wk[1], wk[2], wk[3]);
+      }
+      __syncthreads();  // block b is in buffer b & 1; the rounds of block b - 1 are done
+    }
+    return;
+  }
+  const uint32_t nblocks = l0 + lane < p.nleaves ? all_blocks((uint32_t)(2 * (p.total - l * kHashLeafElems < kHashLeafElems
+                                                                                  ? p.total - l * kHashLeafElems
+                                                                                  : kHashLeafElems)))
+                                                 : 0u;
+  uint32_t st[8];
+  sha256_init(st);
+  for (uint32_t b = 0; b < nb; ++b) {
+    __syncthreads();
+    const uint4(*const from)[64] = s_wk[b & 1][pair];
+    if (b < nblocks) sha256_rounds(st, [&](int t4) { return from[t4][lane]; });
+  }
+  if (l0 + lane < p.nleaves) store_digest(p.digests, l, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -319,6 +482,10 @@ hipError_t launch_hash_setup(const HashSetupParams& p, hipStream_t stream) {
 
 hipError_t launch_hash_leaves(const HashLeafParams& p, hipStream_t stream) {
   if (p.nleaves == 0) return hipSuccess;
+  if (p.nleaves <= kPairLeaves) {
+    hipLaunchKernelGGL(hash_leaf_pair_kernel, dim3((uint32_t)((p.nleaves + 127) / 128)), dim3(256), 0, stream, p);
+    return hipGetLastError();
+  }
   const uint64_t grid = (p.nleaves + 255) / 256;
   hipLaunchKernelGGL(hash_leaf_kernel, dim3((uint32_t)grid), dim3(256), 0, stream, p);
   return hipGetLastError();

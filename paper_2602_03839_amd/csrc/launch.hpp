@@ -216,7 +216,7 @@ static_assert(sizeof(LowpApplyParams) < 4096, "kernel argument block too large")
 // between tensors falls inside them) into one 16 KiB scratch slot each.
 constexpr uint64_t kHashLeafElems = 8192;
 constexpr uint64_t kHashLeafBytes = 2 * kHashLeafElems;
-constexpr int kHashSetupBatch = 64;
+constexpr int kHashSetupBatch = 96;
 constexpr uint32_t kHashTreeFan = 512;  // digests reduced by one tree block
 
 struct HashEntry {

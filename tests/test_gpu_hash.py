@@ -208,3 +208,29 @@ def test_32b_set_sampled_leaves_and_tree():
     del flat, views
     torch.cuda.empty_cache()
     assert _bottom_up_root(got_leaves) == got_root
+
+
+PAIR_LEAVES = 32768  # most leaves that are hashed by pairs of waves, 128 leaves per block
+
+
+@pytest.mark.parametrize("leaves", [1, 2, 63, 64, 65, 127, 128, 129, 300])
+@pytest.mark.parametrize("tail", [1, 27, 28, 31, 32, 8191, 8192])
+def test_hash_wave_pairs_leaf_counts_and_tails(leaves, tail):
+    """Leaf counts at the edges of a wave and a block of the paired kernel, and
+    last leaves whose message ends just before and after a padding block."""
+    rng = np.random.default_rng(leaves * 10_000 + tail)
+    n = (leaves - 1) * 8192 + tail
+    w = rng.integers(0, 1 << 16, n, dtype=np.uint16)
+    cut = min(n, 4097)  # a tensor boundary, the second tensor 2 bytes into a word
+    root, digests = pulse.hash_tree([dev(w[:cut]), dev(w[cut:])])
+    want = oracle.leaf_hashes(w)
+    np.testing.assert_array_equal(digests.cpu().numpy(), np.asarray(want).reshape(-1, 32))
+    assert bytes(root.cpu().numpy()) == bytes(oracle.merkle_root(want))
+
+
+@pytest.mark.parametrize("n", [PAIR_LEAVES * 8192, PAIR_LEAVES * 8192 + 1])
+def test_hash_last_paired_and_first_single_size(n):
+    rng = np.random.default_rng(n)
+    w = rng.integers(0, 1 << 16, n, dtype=np.uint16)
+    root, _ = pulse.hash_tree([dev(w)])
+    assert bytes(root.cpu().numpy()) == bytes(oracle.merkle_root(oracle.leaf_hashes(w)))
