@@ -10,12 +10,12 @@
 namespace pulse {
 
 constexpr int kApplyTB = 256;
-constexpr int kApplyBlocks = 2048;
+static_assert(kMaxApply <= 256, "segment_before covers 256 tensors");
 
 template <int TB>
 __global__ __launch_bounds__(TB) void apply_kernel(ApplyParams p) {
-  __shared__ uint64_t s_seg[kMaxBatch + 1];
-  __shared__ ApplyTensorDesc s_t[kMaxBatch];
+  __shared__ uint64_t s_seg[kMaxApply + 1];
+  __shared__ ApplyTensorDesc s_t[kMaxApply];
   const int nt = p.ntensors;
   const int tid = threadIdx.x;
   const uint64_t cap = p.capacity;
@@ -34,15 +34,13 @@ __global__ __launch_bounds__(TB) void apply_kernel(ApplyParams p) {
   const uint64_t hi = s_seg[nt];
   const uint64_t stride = (uint64_t)gridDim.x * TB;
   uint32_t rejected = 0;
-  int t = 0;
   for (uint64_t k = lo + (uint64_t)blockIdx.x * TB + tid; k < hi; k += stride) {
-    while (t + 1 < nt && s_seg[t + 1] <= k) ++t;
     const uint32_t id = load_nt(p.idx + k);
     const uint16_t v = load_nt(p.val + k);
-    const uint32_t base = s_t[t].index_base;
-    const uint64_t j = (uint64_t)(id - base);
-    if (id >= base && j < s_t[t].n) {
-      store_nt(s_t[t].dst + j, v);
+    const ApplyTensorDesc t = s_t[segment_before(s_seg, nt, k)];
+    const uint32_t j = id - t.index_base;
+    if (id >= t.index_base && t.dst != nullptr && j <= t.last) {
+      store_nt(t.dst + j, v);
     } else {
       ++rejected;
     }
@@ -54,7 +52,7 @@ __global__ __launch_bounds__(TB) void apply_kernel(ApplyParams p) {
 }
 
 hipError_t launch_apply(const ApplyParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL(apply_kernel<kApplyTB>, dim3(kApplyBlocks), dim3(kApplyTB), 0, stream, p);
+  hipLaunchKernelGGL(apply_kernel<kApplyTB>, dim3(apply_blocks(p.capacity)), dim3(kApplyTB), 0, stream, p);
   return hipGetLastError();
 }
 

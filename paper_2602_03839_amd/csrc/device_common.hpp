@@ -766,6 +766,15 @@ __device__ __forceinline__ uint32_t get_u32(const uint4& v, int i) {
   return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
 }
 
+// The last of the tensors [0, nt) whose entries begin at or before k (s: their
+// begins, never decreasing, in LDS).
+__device__ __forceinline__ int segment_before(const uint64_t* s, int nt, uint64_t k) {
+  int t = 0;
+#pragma unroll
+  for (int step = 128; step > 0; step >>= 1)
+    if (t + step < nt && s[t + step] <= k) t += step;
+  return t;
+}
 
 // Blocks of `kernel` (launched with `block` threads) that fit on the current
 // device at once: the grid of a persistent launch.  The occupancy query is

@@ -89,11 +89,15 @@ struct LocoParams {
   LocoTensorDesc t[kMaxBatch];
 };
 
+// A receiver's tensor in 16 bytes, so that a launch's kernel arguments hold 224
+// of them: n - 1 instead of n (at most 2^32), and no dst for an empty tensor.
 struct ApplyTensorDesc {
   uint16_t* dst;
-  uint64_t n;
+  uint32_t last;
   uint32_t index_base;
 };
+
+constexpr int kMaxApply = 224;  // tensors per apply launch
 
 struct ApplyParams {
   const uint32_t* idx;
@@ -103,7 +107,7 @@ struct ApplyParams {
   const uint64_t* end;
   uint64_t* rejected;
   int ntensors;
-  ApplyTensorDesc t[kMaxBatch];
+  ApplyTensorDesc t[kMaxApply];
 };
 
 constexpr int kMaxLists = 8;  // workers' lists per outer-step launch
@@ -188,11 +192,13 @@ struct LowpParams {
 };
 
 struct LowpApplyTensorDesc {
-  uint8_t* codes;
+  uint8_t* codes;   // null: an empty tensor
   uint8_t* scales;  // MXFP4 only
-  uint64_t n;
+  uint32_t last;    // n - 1
   uint32_t index_base;
 };
+
+constexpr int kMaxLowpApply = 160;  // tensors per launch
 
 struct LowpApplyParams {
   const uint32_t* idx;
@@ -203,8 +209,16 @@ struct LowpApplyParams {
   uint64_t* rejected;
   int ntensors;
   int dtype;
-  LowpApplyTensorDesc t[kMaxBatch];
+  LowpApplyTensorDesc t[kMaxLowpApply];
 };
+
+// Blocks of an apply launch over at most `capacity` entries, 256 per block and
+// pass: 2,048 stride over a large patch, a small one takes what it needs.  (512
+// to 8,192 blocks took 165-166 us on the 0.5B set's patch, one pass per block
+// 178.)
+constexpr uint32_t apply_blocks(uint64_t capacity) {
+  return capacity >= 2048ull * 256 ? 2048u : (uint32_t)((capacity + 255) / 256);
+}
 
 static_assert(sizeof(LowpParams) < 4096, "kernel argument block too large");
 static_assert(sizeof(LowpApplyParams) < 4096, "kernel argument block too large");

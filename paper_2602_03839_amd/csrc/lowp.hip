@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kOneNW * 64) void encode_lowp_one_kernel(LowpParams
 
 // ------------------------------------------------------------------ apply
 constexpr int kLowpApplyTB = 256;
-constexpr int kLowpApplyBlocks = 2048;
+static_assert(kMaxLowpApply <= 256, "segment_before covers 256 tensors");
 
 // FP8: dst[j] = code.  MXFP4: the code goes to nibble j of the packed codes
 // and the scale to byte j / 32.  Two entries can share a code byte (values 2b
@@ -427,8 +427,8 @@ constexpr int kLowpApplyBlocks = 2048;
 // rewrites it with the other nibble unchanged (no entry targets that nibble).
 // Scale bytes of one block all receive the same byte.
 __global__ __launch_bounds__(kLowpApplyTB) void apply_lowp_kernel(LowpApplyParams p) {
-  __shared__ uint64_t s_seg[kMaxBatch + 1];
-  __shared__ LowpApplyTensorDesc s_t[kMaxBatch];
+  __shared__ uint64_t s_seg[kMaxLowpApply + 1];
+  __shared__ LowpApplyTensorDesc s_t[kMaxLowpApply];
   const int nt = p.ntensors;
   const int tid = threadIdx.x;
   const uint64_t cap = p.capacity;
@@ -445,13 +445,12 @@ __global__ __launch_bounds__(kLowpApplyTB) void apply_lowp_kernel(LowpApplyParam
   const uint64_t lo = s_seg[0], hi = s_seg[nt];
   const uint64_t stride = (uint64_t)gridDim.x * kLowpApplyTB;
   uint32_t rejected = 0;
-  int t = 0;
   for (uint64_t k = lo + (uint64_t)blockIdx.x * kLowpApplyTB + tid; k < hi; k += stride) {
-    while (t + 1 < nt && s_seg[t + 1] <= k) ++t;
     const uint32_t id = p.idx[k];
+    const int t = segment_before(s_seg, nt, k);
     const uint32_t base = s_t[t].index_base;
-    const uint64_t j = (uint64_t)(id - base);
-    if (!(id >= base && j < s_t[t].n)) {
+    const uint32_t j = id - base;
+    if (!(id >= base && s_t[t].codes != nullptr && j <= s_t[t].last)) {
       ++rejected;
       continue;
     }
@@ -535,7 +534,7 @@ hipError_t launch_encode_lowp(int dtype, LowpParams& p, int one, hipStream_t str
 }
 
 hipError_t launch_apply_lowp(const LowpApplyParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL(apply_lowp_kernel, dim3(kLowpApplyBlocks), dim3(kLowpApplyTB), 0, stream, p);
+  hipLaunchKernelGGL(apply_lowp_kernel, dim3(apply_blocks(p.capacity)), dim3(kLowpApplyTB), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -414,10 +414,8 @@ int pulse_apply_batch(const pulse_apply_tensor* tensors, uint32_t ntensors, cons
   }
   uint32_t t0 = 0;
   while (t0 < ntensors) {
-    pulse::ApplyParams p;
-    memset(&p, 0, sizeof p);
-    const uint32_t k = (ntensors - t0) < (uint32_t)pulse::kMaxBatch ? (ntensors - t0)
-                                                                     : (uint32_t)pulse::kMaxBatch;
+    pulse::ApplyParams p;  // (the tensors past ntensors are not read)
+    const uint32_t k = std::min(ntensors - t0, (uint32_t)pulse::kMaxApply);
     p.idx = idx;
     p.val = val;
     p.capacity = capacity;
@@ -426,8 +424,8 @@ int pulse_apply_batch(const pulse_apply_tensor* tensors, uint32_t ntensors, cons
     p.rejected = rejected;
     p.ntensors = (int)k;
     for (uint32_t i = 0; i < k; ++i) {
-      p.t[i].dst = tensors[t0 + i].dst;
-      p.t[i].n = tensors[t0 + i].n;
+      p.t[i].dst = tensors[t0 + i].n > 0 ? tensors[t0 + i].dst : nullptr;
+      p.t[i].last = (uint32_t)(tensors[t0 + i].n - 1);
       p.t[i].index_base = tensors[t0 + i].index_base;
     }
     if (int rc = hip_status(pulse::launch_apply(p, (hipStream_t)stream), "apply launch")) return rc;
@@ -884,10 +882,8 @@ int pulse_apply_lowp_batch(int dtype, const pulse_lowp_apply_tensor* tensors, ui
   }
   uint32_t t0 = 0;
   while (t0 < ntensors) {
-    pulse::LowpApplyParams p;
-    memset(&p, 0, sizeof p);
-    const uint32_t k = (ntensors - t0) < (uint32_t)pulse::kMaxBatch ? (ntensors - t0)
-                                                                     : (uint32_t)pulse::kMaxBatch;
+    pulse::LowpApplyParams p;  // (the tensors past ntensors are not read)
+    const uint32_t k = std::min(ntensors - t0, (uint32_t)pulse::kMaxLowpApply);
     p.idx = idx;
     p.val = val;
     p.capacity = capacity;
@@ -897,9 +893,9 @@ int pulse_apply_lowp_batch(int dtype, const pulse_lowp_apply_tensor* tensors, ui
     p.ntensors = (int)k;
     p.dtype = dtype;
     for (uint32_t i = 0; i < k; ++i) {
-      p.t[i].codes = tensors[t0 + i].codes;
+      p.t[i].codes = tensors[t0 + i].n > 0 ? tensors[t0 + i].codes : nullptr;
       p.t[i].scales = tensors[t0 + i].scales;
-      p.t[i].n = tensors[t0 + i].n;
+      p.t[i].last = (uint32_t)(tensors[t0 + i].n - 1);
       p.t[i].index_base = tensors[t0 + i].index_base;
     }
     if (int rc = hip_status(pulse::launch_apply_lowp(p, (hipStream_t)stream), "apply_lowp launch"))

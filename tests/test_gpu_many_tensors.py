@@ -160,3 +160,58 @@ def test_all_empty_many_tensors(ws, T):
     torch.cuda.synchronize()
     assert read_count(count) == 3
     assert bool((seg == 3).all())
+
+
+@pytest.mark.parametrize("dtype", [None, pulse.FP8_E4M3, pulse.MXFP4])
+@pytest.mark.parametrize("T", [1, 159, 160, 161, 223, 224, 225, 449])
+def test_apply_many_tensors(T, dtype):
+    """BF16, FP8 and MXFP4 applies at the edges of a launch's tensors, empty ones
+    among them, entries outside their tensor counted and left out."""
+    rng = np.random.default_rng(T + 3)
+    sizes = [int(x) for x in rng.integers(0, 90, T)]
+    sizes[0] = 5000
+    idx, seg, at = [], [], 0
+    for n in sizes:
+        k = int(rng.integers(0, n + 1)) if n else 0
+        i = np.sort(rng.choice(n, k, replace=False)) if k else np.zeros(0, np.int64)
+        if rng.random() < 0.2:
+            i = np.append(i, n + 3)  # outside
+        idx.append(i.astype(np.uint32))
+        seg.append(at)
+        at += i.size
+    all_idx = np.concatenate(idx)
+    u8 = lambda a: dev(a) if a.size else torch.empty(0, dtype=torch.uint8, device="cuda")  # noqa: E731
+    bad = sum(int((i >= n).sum()) for i, n in zip(idx, sizes))
+    rej, end, seg_d = counter(0), counter(at), dev(np.array(seg, np.int64))
+    if dtype is None:
+        val = rng.integers(0, 1 << 16, at, dtype=np.uint16)
+        host = [rng.integers(0, 1 << 16, n, dtype=np.uint16) for n in sizes]
+        dst = [i16(h) for h in host]
+        pulse.ApplyBatch([pulse.ApplyTensor(d) for d in dst])(dev(all_idx), dev(val), seg_d, end, rejected=rej)
+        for t, (h, i, s) in enumerate(zip(host, idx, seg)):
+            ok = i < h.size
+            h[i[ok]] = val[s:s + i.size][ok]
+            np.testing.assert_array_equal(h16(dst[t]), h, err_msg=str(t))
+    else:
+        fp8 = dtype == pulse.FP8_E4M3
+        val = rng.integers(0, 256, at, dtype=np.uint8) if fp8 else \
+            ((7 << 8) | rng.integers(0, 16, at)).astype(np.uint16)
+        sz = [pulse.lowp_sizes(dtype, n) for n in sizes]
+        codes = [rng.integers(0, 256, a, dtype=np.uint8) for a, _ in sz]
+        scales = [rng.integers(0, 256, b, dtype=np.uint8) for _, b in sz]
+        cd, sd = [u8(c) for c in codes], [u8(s) for s in scales]
+        pulse.ApplyLowpBatch(dtype, [pulse.LowpApplyTensor(cd[t], None if fp8 else sd[t], n)
+                                     for t, n in enumerate(sizes)])(dev(all_idx), dev(val), seg_d, end, rejected=rej)
+        for t, (i, s, n) in enumerate(zip(idx, seg, sizes)):
+            for j, v in zip(i, val[s:s + i.size]):
+                if j >= n:
+                    continue
+                if fp8:
+                    codes[t][j] = v
+                else:
+                    b = codes[t][j // 2]
+                    codes[t][j // 2] = (b & 0x0F) | ((v & 0xF) << 4) if j & 1 else (b & 0xF0) | (v & 0xF)
+                    scales[t][j // 32] = v >> 8
+            np.testing.assert_array_equal(cd[t].cpu().numpy(), codes[t], err_msg=str(t))
+            np.testing.assert_array_equal(sd[t].cpu().numpy(), scales[t], err_msg=str(t))
+    assert read_count(rej) == bad
