@@ -67,18 +67,27 @@ Scratch scratch_at(void* base, uint32_t ntiles) {
                  reinterpret_cast<Staged*>(b + cnt_bytes + unit_bytes)};
 }
 
+// First tile of tensor k (kernel arguments, or the workspace's table), as a
+// scalar load for a wave-uniform k.
+template <bool TABLE>
+__device__ __forceinline__ uint32_t first_tile(const LocoParams& p, uint32_t k) {
+  if (!TABLE) return p.tile_begin[k];
+  return ((const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p.table_begin)[k];
+}
+
 // Tensor of a wave-uniform tile: the last tensor of the launch whose first
 // tile is <= tile (tile starts never decrease; an empty tensor shares its
-// start with the next one, which wins).  A binary search with scalar loads of
-// the kernel arguments, so that a short-lived block reaches its own loads
-// after six cached scalar loads instead of a lane-per-tensor vector pass.
+// start with the next one, which wins).  A binary search with scalar loads, so
+// that a short-lived block reaches its own loads after six cached scalar loads
+// (ten from the table) instead of a lane-per-tensor vector pass.
+template <bool TABLE>
 __device__ __forceinline__ int tile_owner(const LocoParams& p, uint32_t tile) {
-  static_assert(kMaxBatch == 64, "six halvings cover 64 tensors");
+  static_assert(kMaxBatch == 64 && kMaxTable == 1024, "the halvings cover a launch's tensors");
   uint32_t k = 0;
 #pragma unroll
-  for (uint32_t step = 32; step > 0; step >>= 1) {
+  for (uint32_t step = TABLE ? 512 : 32; step > 0; step >>= 1) {
     const uint32_t q = k + step;
-    if (q < (uint32_t)p.ntensors && p.tile_begin[q] <= tile) k = q;
+    if (q < (uint32_t)p.ntensors && first_tile<TABLE>(p, q) <= tile) k = q;
   }
   return (int)k;
 }
@@ -103,16 +112,18 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s_w, u
   return before + incl - v;
 }
 
+template <bool TABLE>
 __global__ __launch_bounds__(kL2Threads) void loco_stage_kernel(LocoParams p, Scratch sc) {
   __shared__ uint32_t s_w[kL2Waves];
   __shared__ Staged s_ent[kL2Cap];
   const uint32_t tile = blockIdx.x;
   const int tid = threadIdx.x;
-  const int k = tile_owner(p, tile);
-  const uint64_t n = p.t[k].n;
-  const float* const d = p.t[k].delta;
-  float* const r = p.t[k].residual;
-  const uint64_t e = (uint64_t)(tile - p.tile_begin[k]) * kL2Tile + (uint64_t)tid * 4;
+  const int k = tile_owner<TABLE>(p, tile);
+  const LocoTensorDesc td = tensor_at<TABLE>(p, k);
+  const uint64_t n = td.n;
+  const float* const d = td.delta;
+  float* const r = td.residual;
+  const uint64_t e = (uint64_t)(tile - first_tile<TABLE>(p, (uint32_t)k)) * kL2Tile + (uint64_t)tid * 4;
   const bool vec = e + 4 <= n;
   float a[4];
   if (vec) {
@@ -156,7 +167,7 @@ __global__ __launch_bounds__(kL2Threads) void loco_stage_kernel(LocoParams p, Sc
       }
     }
   } else {
-    const uint32_t ib = p.t[k].index_base + (uint32_t)e;
+    const uint32_t ib = td.index_base + (uint32_t)e;
     uint32_t mm = m;
     while (mm) {
       const int i = __builtin_ctz(mm);
@@ -185,6 +196,7 @@ __global__ __launch_bounds__(kL2Threads) void loco_unit_sum_kernel(Scratch sc, u
 // One block of 1024 threads: the units' sums become their patch positions.
 constexpr int kScanThreads = 1024;
 
+template <bool TABLE>
 __global__ __launch_bounds__(kScanThreads) void loco_unit_scan_kernel(LocoParams p, Scratch sc,
                                                                       uint32_t units) {
   __shared__ uint64_t s_part[kScanThreads];
@@ -210,16 +222,29 @@ __global__ __launch_bounds__(kScanThreads) void loco_unit_scan_kernel(LocoParams
     sc.unit[u] = pos;
     pos += c;
   }
-  if (tid == kScanThreads - 1) {
-    const uint64_t end = s_base + s_part[kScanThreads - 1];
-    *p.count = end;
-    // tensors with no tile at or after their start (empty ones at the end)
-    if (p.seg_begin)
-      for (int k = 0; k < p.ntensors; ++k)
-        if (p.tile_begin[k] >= p.ntiles) p.seg_begin[k] = end;
-  }
+  const uint64_t end = s_base + s_part[kScanThreads - 1];
+  if (tid == kScanThreads - 1) *p.count = end;
+  // tensors with no tile at or after their start (empty ones at the end)
+  static_assert(kMaxTable <= kScanThreads, "one tensor per thread");
+  if (p.seg_begin && tid < p.ntensors && (TABLE ? p.table_begin[tid] : p.tile_begin[tid]) >= p.ntiles)
+    p.seg_begin[tid] = end;
 }
 
+// A staged entry that is not sent: error feedback keeps s.  (The tile differs
+// between lanes, so the tensor's fields come by vector loads.)
+template <bool TABLE>
+__device__ __forceinline__ void put_back(const LocoParams& p, uint32_t tile, const Staged& v) {
+  uint32_t k = 0;
+#pragma unroll
+  for (uint32_t step = TABLE ? 512 : 32; step > 0; step >>= 1) {
+    const uint32_t q = k + step;
+    if (q < (uint32_t)p.ntensors && (TABLE ? p.table_begin[q] : p.tile_begin[q]) <= tile) k = q;
+  }
+  float* const r = TABLE ? p.table[k].residual : p.t[k].residual;
+  r[v.idx - (TABLE ? p.table[k].index_base : p.t[k].index_base)] = __uint_as_float(v.val);
+}
+
+template <bool TABLE>
 __global__ __launch_bounds__(kL2Threads) void loco_gather_kernel(LocoParams p, Scratch sc) {
   __shared__ uint32_t s_w[kL2Waves];
   __shared__ uint32_t s_pre[kL2Unit];  // entries of the unit before each tile
@@ -243,10 +268,11 @@ __global__ __launch_bounds__(kL2Threads) void loco_gather_kernel(LocoParams p, S
   __syncthreads();
   // tensors whose first tile lies in this unit (an empty tensor shares its
   // start with the next one; starts at ntiles are written by the scan pass)
-  if (p.seg_begin && tid < p.ntensors) {
-    const uint32_t tb = p.tile_begin[tid];
-    if (tb < p.ntiles && tb >= t0 && tb < t0 + kL2Unit) p.seg_begin[tid] = ubase + s_pre[tb - t0];
-  }
+  if (p.seg_begin)
+    for (int k = tid; k < p.ntensors; k += kL2Threads) {
+      const uint32_t tb = TABLE ? p.table_begin[k] : p.tile_begin[k];
+      if (tb < p.ntiles && tb >= t0 && tb < t0 + kL2Unit) p.seg_begin[k] = ubase + s_pre[tb - t0];
+    }
   const uint64_t cap = p.capacity;
   // Staged entries, in the unit's order, one per lane: entry j of the unit is
   // taken by thread j mod kL2Threads, so every load and store instruction
@@ -283,9 +309,7 @@ __global__ __launch_bounds__(kL2Threads) void loco_gather_kernel(LocoParams p, S
           store_nt(p.idx + pos, v[b].idx);
           store_nt(p.val + pos, __uint_as_float(v[b].val));
         } else {
-          // selected but not sent: error feedback keeps s
-          const int kk = tile_owner(p, t0 + s_map[j]);
-          p.t[kk].residual[v[b].idx - p.t[kk].index_base] = __uint_as_float(v[b].val);
+          put_back<TABLE>(p, t0 + s_map[j], v[b]);
         }
       }
     }
@@ -317,8 +341,7 @@ __global__ __launch_bounds__(kL2Threads) void loco_gather_kernel(LocoParams p, S
           store_nt(p.idx + pos, v[r].idx);
           store_nt(p.val + pos, __uint_as_float(v[r].val));
         } else {
-          const int kk = tile_owner(p, tt);
-          p.t[kk].residual[v[r].idx - p.t[kk].index_base] = __uint_as_float(v[r].val);
+          put_back<TABLE>(p, tt, v[r]);
         }
       }
     }
@@ -329,10 +352,11 @@ __global__ __launch_bounds__(kL2Threads) void loco_gather_kernel(LocoParams p, S
   for (int i = 0; i < (int)kL2Unit; ++i) {
     if (s_cnt[i] <= kL2Cap) continue;  // block-uniform
     const uint32_t tt = t0 + (uint32_t)i;
-    const int kk = tile_owner(p, tt);
-    const uint64_t n = p.t[kk].n;
-    float* const r = p.t[kk].residual;
-    const uint64_t e = (uint64_t)(tt - p.tile_begin[kk]) * kL2Tile + (uint64_t)tid * 4;
+    const int kk = tile_owner<TABLE>(p, tt);
+    const LocoTensorDesc td = tensor_at<TABLE>(p, kk);
+    const uint64_t n = td.n;
+    float* const r = td.residual;
+    const uint64_t e = (uint64_t)(tt - first_tile<TABLE>(p, (uint32_t)kk)) * kL2Tile + (uint64_t)tid * 4;
     float a[4];
     uint32_t m = 0;
 #pragma unroll
@@ -342,7 +366,7 @@ __global__ __launch_bounds__(kL2Threads) void loco_gather_kernel(LocoParams p, S
     }
     uint32_t tot;
     uint64_t pos = ubase + s_pre[i] + block_excl_scan((uint32_t)__builtin_popcount(m), s_w, tot);
-    const uint32_t ib = p.t[kk].index_base + (uint32_t)e;
+    const uint32_t ib = td.index_base + (uint32_t)e;
     while (m) {
       const int q = __builtin_ctz(m);
       m &= m - 1;
@@ -366,16 +390,20 @@ size_t loco2_scratch_bytes(uint32_t ntiles) {
          (size_t)ntiles * kL2Cap * sizeof(Staged);
 }
 
-hipError_t launch_loco2(LocoParams& p, void* scratch, hipStream_t stream) {
-  if (p.ntiles == 0) return launch_loco(p, false, stream);
+template <bool TABLE>
+static hipError_t launch_loco2_form(const LocoParams& p, void* scratch, hipStream_t stream) {
   const Scratch sc = scratch_at(scratch, p.ntiles);
   const uint32_t units = (p.ntiles + kL2Unit - 1) / kL2Unit;
-  hipLaunchKernelGGL(loco_stage_kernel, dim3(p.ntiles), dim3(kL2Threads), 0, stream, p, sc);
-  hipLaunchKernelGGL(loco_unit_sum_kernel, dim3(units), dim3(kL2Threads), 0, stream, sc,
-                     p.ntiles);
-  hipLaunchKernelGGL(loco_unit_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, p, sc, units);
-  hipLaunchKernelGGL(loco_gather_kernel, dim3(units), dim3(kL2Threads), 0, stream, p, sc);
+  hipLaunchKernelGGL(loco_stage_kernel<TABLE>, dim3(p.ntiles), dim3(kL2Threads), 0, stream, p, sc);
+  hipLaunchKernelGGL(loco_unit_sum_kernel, dim3(units), dim3(kL2Threads), 0, stream, sc, p.ntiles);
+  hipLaunchKernelGGL(loco_unit_scan_kernel<TABLE>, dim3(1), dim3(kScanThreads), 0, stream, p, sc, units);
+  hipLaunchKernelGGL(loco_gather_kernel<TABLE>, dim3(units), dim3(kL2Threads), 0, stream, p, sc);
   return hipGetLastError();
+}
+
+hipError_t launch_loco2(LocoParams& p, void* scratch, hipStream_t stream) {
+  if (p.ntiles == 0) return launch_loco(p, false, stream);
+  return p.table ? launch_loco2_form<true>(p, scratch, stream) : launch_loco2_form<false>(p, scratch, stream);
 }
 
 }  // namespace pulse

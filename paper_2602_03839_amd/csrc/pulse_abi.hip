@@ -495,45 +495,27 @@ int loco_batch(const pulse_loco_tensor* tensors, const float* inv_scales, uint32
     p.tau = tau;
     p.gate_dtype = gate_dtype;
     p.gm = gm;
-    uint32_t tiles = 0;
-    int k = 0;
-    if (max2 > 0) {
-      while (t0 + k < ntensors && k < pulse::kMaxBatch) {
-        const pulse_loco_tensor& d = tensors[t0 + k];
-        const uint32_t nt = tiles_for(d.n, pulse::kL2Tile);
-        if ((uint64_t)tiles + nt > max2) break;
-        p.tile_begin[k] = tiles;
-        p.t[k].delta = d.delta;
-        p.t[k].residual = d.residual;
-        p.t[k].theta = d.theta;
-        p.t[k].n = d.n;
-        p.t[k].index_base = d.index_base;
-        p.t[k].inv_scale = 1.0f;
-        tiles += nt;
-        ++k;
-      }
-      if (k > 0) {
-        p.tile_begin[k] = tiles;
-        p.ntensors = k;
-        p.ntiles = tiles;
-        if (int rc = hip_status(pulse::launch_loco2(p, scratch, (hipStream_t)stream),
-                                "loco launch (two-pass)"))
-          return rc;
-        t0 += k;
-        continue;
-      }
-    }
+    auto fill = [&](uint32_t i, pulse::LocoTensorDesc& e) {
+      const pulse_loco_tensor& d = tensors[t0 + i];
+      e.delta = d.delta;
+      e.residual = d.residual;
+      e.theta = d.theta;
+      e.n = d.n;
+      e.index_base = d.index_base;
+      e.inv_scale = inv_scales ? inv_scales[t0 + i] : 1.0f;
+    };
     uint32_t taken = 0;
-    if (int rc = gather_launch(p, tensors + t0, ntensors - t0, tile, pulse::kMaxTilesPerLaunch,
-                               [&](uint32_t i, pulse::LocoTensorDesc& e) {
-                                 const pulse_loco_tensor& d = tensors[t0 + i];
-                                 e.delta = d.delta;
-                                 e.residual = d.residual;
-                                 e.theta = d.theta;
-                                 e.n = d.n;
-                                 e.index_base = d.index_base;
-                                 e.inv_scale = inv_scales ? inv_scales[t0 + i] : 1.0f;
-                               },
+    if (max2 > 0 && tiles_for(tensors[t0].n, pulse::kL2Tile) <= max2) {
+      if (int rc = gather_launch(p, tensors + t0, ntensors - t0, pulse::kL2Tile, max2, fill, workspace,
+                                 (hipStream_t)stream, &taken))
+        return rc;
+      if (int rc = hip_status(pulse::launch_loco2(p, scratch, (hipStream_t)stream),
+                              "loco launch (two-pass)"))
+        return rc;
+      t0 += taken;
+      continue;
+    }
+    if (int rc = gather_launch(p, tensors + t0, ntensors - t0, tile, pulse::kMaxTilesPerLaunch, fill,
                                workspace, (hipStream_t)stream, &taken))
       return rc;
     if (int rc = hip_status(pulse::launch_loco(p, one, (hipStream_t)stream), "loco launch")) return rc;

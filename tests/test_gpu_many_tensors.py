@@ -215,3 +215,39 @@ def test_apply_many_tensors(T, dtype):
             np.testing.assert_array_equal(cd[t].cpu().numpy(), codes[t], err_msg=str(t))
             np.testing.assert_array_equal(sd[t].cpu().numpy(), scales[t], err_msg=str(t))
     assert read_count(rej) == bad
+
+
+@pytest.mark.parametrize("T", [1024, 1025, 1100])
+@pytest.mark.parametrize("cap_frac", [1.0, 0.3])
+def test_threshold_two_pass_many_tensors(T, cap_frac):
+    """The two-pass threshold form over more tensors than kernel arguments hold,
+    with dense tiles that overflow their staging and entries past the capacity."""
+    rng = np.random.default_rng(T + 4)
+    sizes = make_sizes(rng, T, 30_000)
+    N, tau = sum(sizes), 3e-4
+    ws = pulse.loco_workspace(N)
+    descs, res, want, o_seg, cnt = [], [], [], [], 0
+    o_idx, o_val = np.zeros(N, np.uint32), np.zeros(N, np.float32)
+    host = [(rng.normal(0, 2e-4, n).astype(np.float32), rng.normal(0, 5e-5, n).astype(np.float32)) for n in sizes]
+    nnz = sum(int((np.abs(d + e) >= np.float32(tau)).sum()) for d, e in host)
+    cap = int(nnz * cap_frac)
+    for d, e in host:
+        e_d = f32(e)
+        descs.append(pulse.LocoTensor(f32(d), e_d, None, 0))
+        o_seg.append(cnt)
+        if d.size:
+            room = max(0, cap - cnt)
+            k, oi, ov = oracle.loco(d, e, tau, capacity=room)
+            o_idx[cnt:cnt + min(k, room)], o_val[cnt:cnt + min(k, room)] = oi[:min(k, room)], ov[:min(k, room)]
+            cnt += k
+        res.append(e_d)
+        want.append(e)
+    idx, val, count, seg = buffers(cap, T, torch.float32)
+    pulse.LocoBatch(descs)(tau, idx, val, count, ws, seg_begin=seg, capacity=cap)
+    torch.cuda.synchronize()
+    assert read_count(count) == cnt == nnz
+    np.testing.assert_array_equal(seg.cpu().numpy(), np.array(o_seg))
+    np.testing.assert_array_equal(h32(idx)[:cap], o_idx[:cap])
+    np.testing.assert_array_equal(hf32(val)[:cap].view(np.uint32), o_val[:cap].view(np.uint32))
+    for t, (r_d, r) in enumerate(zip(res, want)):
+        np.testing.assert_array_equal(hf32(r_d).view(np.uint32), r.view(np.uint32), err_msg=str(t))
