@@ -268,9 +268,10 @@ typedef struct pulse_loco_tensor {
  * The part of the workspace past pulse_workspace_bytes() holds the staging
  * area and needs no initialisation; the first pulse_workspace_bytes() keep
  * the rules above (zero-filled once), so one workspace may serve every call
- * ordered on a stream.  A call whose launch (<= 64 tensors) needs more
- * staging than the workspace holds runs that launch in one pass; the gate
- * forms always run in one pass.  About 1 byte of workspace per element.
+ * ordered on a stream.  A launch takes as many tensors as the staging area
+ * holds; one that does not fit on its own runs in one pass, as do the gate
+ * forms and small calls (up to a few million elements), whatever the
+ * workspace.  About 1 byte of workspace per element.
  */
 size_t pulse_loco_workspace_bytes(uint64_t n);
 

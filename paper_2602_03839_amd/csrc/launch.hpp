@@ -1,7 +1,8 @@
 // launch.hpp -- kernel parameter blocks and launcher declarations shared by
 // the kernels and the C ABI layer.  Parameter blocks travel as kernel
-// arguments (they stay below the 4 KiB kernel-argument limit), so a batched
-// call needs no device-side descriptor table and no extra copy.
+// arguments (they stay below the 4 KiB kernel-argument limit): a batch that
+// fits them needs no device-side descriptor table and no extra copy.  Larger
+// batches of the encoders and sparsifiers have theirs in the workspace.
 #pragma once
 
 #include <hip/hip_runtime.h>

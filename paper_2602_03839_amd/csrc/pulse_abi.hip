@@ -212,7 +212,8 @@ extern "C" {
 size_t pulse_workspace_bytes(void) { return pulse::kWorkspaceBytes; }
 
 size_t pulse_loco_workspace_bytes(uint64_t n) {
-  // every launch holds at most 64 tensors, each adding at most one partial tile
+  // room for 64 tensors' partial tiles: a launch takes as many tensors as fit,
+  // and any one tensor of at most n elements does
   uint64_t tiles = n / pulse::kL2Tile + pulse::kMaxBatch;
   if (tiles > kMaxLoco2Tiles) tiles = kMaxLoco2Tiles;
   return pulse::kWorkspaceBytes + pulse::loco2_scratch_bytes((uint32_t)tiles);
