@@ -954,7 +954,7 @@ int pulse_hash_tree(const pulse_hash_tensor* tensors, uint32_t ntensors, uint8_t
     }
   }
 
-  // Setup launches: the table and the gathers, 64 of each per launch.
+  // Setup launches: the table and the gathers, kHashSetupBatch of each per launch.
   const size_t E = ent.size(), J = jobs.size();
   const size_t nsetup = std::max((E + pulse::kHashSetupBatch - 1) / pulse::kHashSetupBatch,
                                  (J + pulse::kHashSetupBatch - 1) / pulse::kHashSetupBatch);
