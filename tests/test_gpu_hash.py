@@ -234,3 +234,14 @@ def test_hash_last_paired_and_first_single_size(n):
     w = rng.integers(0, 1 << 16, n, dtype=np.uint16)
     root, _ = pulse.hash_tree([dev(w)])
     assert bytes(root.cpu().numpy()) == bytes(oracle.merkle_root(oracle.leaf_hashes(w)))
+
+
+def test_hash_tree_every_last_byte():
+    """An interior node's second block is chosen by its right digest's last byte:
+    one level whose right digests hold all 256, whole numbers of tree blocks and not."""
+    for leaves in (4096, 4609):
+        w = np.random.default_rng(leaves).integers(0, 1 << 16, leaves * 8192, dtype=np.uint16)
+        root, digests = pulse.hash_tree([dev(w)])
+        d = digests.cpu().numpy().reshape(-1, 32)
+        assert np.unique(d[1::2, 31]).size == 256
+        assert bytes(root.cpu().numpy()) == bytes(oracle.merkle_root(oracle.leaf_hashes(w)))
