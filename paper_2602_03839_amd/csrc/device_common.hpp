@@ -762,6 +762,13 @@ __device__ __forceinline__ T load_nt(const T* p) {
   return __builtin_nontemporal_load(p);
 }
 
+// Stand-in source for lanes with no whole group of 8 in range: zero, never
+// written (global, not constant, memory, so that selecting between it and a
+// tensor keeps the loads global rather than flat).
+namespace {
+__device__ __align__(16) uint32_t zero_group[8];
+}  // namespace
+
 __device__ __forceinline__ uint32_t get_u32(const uint4& v, int i) {
   return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
 }

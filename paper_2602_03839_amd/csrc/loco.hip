@@ -54,11 +54,6 @@ struct LocoRegs {
   uint4 t0[GATE ? U : 1], t1[GATE ? U : 1];
 };
 
-// Stand-in source of the prefetch for lanes with no whole group of 8 in range:
-// zero, never written (global, not constant, memory, so that selecting between
-// it and a tensor keeps the loads global rather than flat).
-__device__ __align__(16) uint32_t zero_group[8];
-
 // Loads of group u of a tile for lane `cl`: always the same 16-byte loads into
 // the same registers, from the tensor where all 8 elements of the lane's group
 // lie in it (`live` and in range), else from zero_group.  No branch chooses

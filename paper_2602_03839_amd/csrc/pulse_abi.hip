@@ -69,12 +69,17 @@ uint32_t tiles_for(uint64_t n, uint32_t tile) { return (uint32_t)((n + tile - 1)
 //   n = 2M  11.6 / 11.0 / 12.2 / 20.8     n = 16M  49.6 / 39.5 / 32.3 / 36.7
 //   n = 4M  17.6 / 12.9 / 13.6 / 23.4     n = 32M     - / 72.2 / 56.4 / 51.3
 // A block costs ~30 ns of the ticket and done counters and of the look-back
-// chain, so a form is left where it passes 128, 256 and 512 blocks.  The FP8
-// and MXFP4 encodes cross at the same places (4M in three tensors, with the
-// apply: 31 against 38; 16M: 45 both).  The sparsifier holds one group (three
-// FP32 streams and the values until the positions are known) and crosses later:
-// 4M gate 25.5 against 30.9, threshold in two passes 31.2; 8M 42.5 against
-// 39.7, threshold 38.2 against 41.5.
+// chain, so a form is left where it passes 128, 256 and 512 blocks.  The line
+// holds for many ragged tensors, and for the other encodes (chosen form /
+// persistent; 1, 37, 150 and 300 tensors):
+//   4M, plain        14.9 / 23.9   16.0 / 33.4   21.7 / 39.4   32.5 / 48.9
+//   12M, mirrored    30.1 / 34.2   30.3 / 39.8   34.1 / 49.7   59.5 (persistent)
+//   16M, FP8         29.2 / 35.6   29.8 / 45.3   56.4 (persistent)  64.1
+//   16M, MXFP4       27.4 / 34.1   28.1 / 44.4   55.0 (persistent)  66.5
+// The sparsifier holds one group (three FP32 streams and the values until the
+// positions are known) and crosses later: 4M gate 25.6 against 32.6 (in 300
+// tensors 39.8, 42.5), threshold in two passes 32.1; 6M gate 34.6 against 36.5,
+// 8M 46.7 against 42.1, threshold 38.0 against 38.4 in two passes.
 constexpr uint64_t kOneTileBlocks[3] = {128, 256, 512};
 constexpr uint64_t kOneTileBlocksLoco = 768;
 

@@ -157,3 +157,25 @@ def test_lowp_one_tile_and_persistent(ws, dtype, sizes):
     got = val.cpu().numpy() if fp8 else h16(val)
     np.testing.assert_array_equal(got[:cnt], np.concatenate(o_val))
     pulse.check_workspace(ws)
+
+
+# Many tensors with ragged ends in the four-group form, past 256 blocks: every
+# length modulo 8 (and modulo the 32 values of an MXFP4 block), ends at and beside
+# the edges of groups, waves and tiles, and tensors of less than one lane's load.
+RAGGED4 = [4 * G * (3 + i) + [0, 1, 7, 8, 9, 511, G - 1, G, G + 1, 2 * G + 25, 3 * G + 3][i % 11] + 13 * i
+           for i in range(22)] + [n for n in range(1, 18)] + [31, 32, 33, 4 * G, 4 * G - 1]
+
+
+def test_ragged4_takes_the_four_group_form():
+    tiles = [sum(-(-n // (g * G)) for n in RAGGED4) for g in (1, 2, 4)]
+    assert tiles[0] > 128 and tiles[1] > 256 and 256 < tiles[2] <= 512
+
+
+@pytest.mark.parametrize("density,cap_frac", [(0.01, 1.0), (0.3, 0.6)])
+def test_encode_many_ragged_tensors_four_groups(ws, density, cap_frac):
+    encode_check(ws, RAGGED4, density, cap_frac, count_in=3)
+
+
+@pytest.mark.parametrize("dtype", [pulse.FP8_E4M3, pulse.MXFP4])
+def test_lowp_many_ragged_tensors_four_groups(ws, dtype):
+    test_lowp_one_tile_and_persistent(ws, dtype, RAGGED4)
