@@ -91,3 +91,35 @@ def test_coo_units_and_tiles(n, how, cols):
     np.testing.assert_array_equal(h32(back)[:n], idx)
     assert (h32(back)[n:] == 0xFFFFFFFF).all()
     assert int(ws.view(torch.int64)[64:].abs().sum().item()) == 0
+
+
+@pytest.mark.parametrize("nseg,most", [(300, 7), (3000, 7), (3000, 40), (2500, 3000)])
+def test_varint_many_segments(nseg, most):
+    """Segments of 0 to `most` entries, so that starts fall on every entry of a
+    thread's quads, several at one entry, hundreds in a unit (past the 256 kept per
+    tile) or several tiles apart, with numbers of one to four bytes: the stream, each
+    segment's byte offset, and the list decoded back."""
+    rng = np.random.default_rng(nseg + most)
+    sizes = rng.integers(0, most + 1, nseg)
+    segs = []
+    for k in sizes:
+        gap = np.exp2(rng.uniform(0, [6, 6, 13, 20][rng.integers(0, 4)] if most > 100 else 26, k)).astype(np.int64)
+        segs.append(np.cumsum(gap).astype(np.uint32))
+    begins = np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.int64)
+    parts = [oracle.varint_encode(s) for s in segs]
+    want, offs = np.concatenate(parts), np.concatenate([[0], np.cumsum([p.size for p in parts])[:-1]])
+    idx, n = np.concatenate(segs), int(sizes.sum())
+    ws, seg_d = pulse.workspace(), dev(begins)
+    out = torch.zeros(want.size + 8, dtype=torch.uint8, device="cuda")
+    total, at = counter(0), torch.full((nseg,), -1, dtype=torch.int64, device="cuda")
+    pulse.varint_encode(dev(idx), counter(n), out, total, ws, seg_begin=seg_d, seg_bytes=at)
+    torch.cuda.synchronize()
+    assert read_count(total) == want.size
+    np.testing.assert_array_equal(out[:want.size].cpu().numpy(), want)
+    np.testing.assert_array_equal(at.cpu().numpy(), offs)
+    back, got = torch.full((n + 3,), -1, dtype=torch.int32, device="cuda"), counter(0)
+    pulse.varint_decode(out, total, back, got, ws, seg_begin=seg_d)
+    torch.cuda.synchronize()
+    assert read_count(got) == n
+    np.testing.assert_array_equal(h32(back)[:n], idx)
+    assert (h32(back)[n:] == 0xFFFFFFFF).all()
