@@ -402,6 +402,9 @@ __global__ __launch_bounds__(kDT) void varint_count_kernel(VarintDecParams p) {
     for (uint64_t q = 0; q < 4; ++q) b[q] = unit_bytes(p.in, u0 + q * kDUnit, t1);
 #pragma unroll
     for (uint64_t q = 0; q < 4; ++q) {
+      // (a unit past the tile would be walked byte by byte: 400M set's patch,
+      // one-unit tiles, 20.8 us instead of 8)
+      if (u0 + q * kDUnit >= t1) break;  // block-uniform
       finish_bytes(b[q], p.in, u0 + q * kDUnit, t1);
       cnt += terminators(b[q]);
       sum += sum_numbers(b[q]);
@@ -440,52 +443,61 @@ __device__ __forceinline__ Before shfl_up(Before x, int d) {
 // Block s, s + grid, ...: segment s (and block 0 the entries before the first
 // segment).  The tiles whose first entry lies past its start, up to its end,
 // carry in the plain sum before them less the one before the segment: the
-// block folds the tile words, sums the numbers of the start's tile up to it,
-// and writes those tiles' first entries and carries.  Every tile's first entry
-// lies in exactly one segment's range.
+// block folds the tile words into LDS, searches the segment's tiles there, sums
+// the numbers of the start's tile up to it, and writes those tiles' first
+// entries and carries.  Every tile's first entry lies in exactly one segment's
+// range.  What bounds it: the latency of the fold, then of each segment with
+// such a tile (~2 us: its starts, its tile's bytes, the block sums).  Searching
+// the tiles in registers, all of them for each segment, took as long again:
+// decode of the 150M set's patch in 300 / 1,500 / 3,000 tensors 29.1 / 36.1 /
+// 45.2 us, now 22.5 / 25.5 / 28.4.
 __global__ __launch_bounds__(kDT) void varint_carry_kernel(VarintDecParams p) {
   __shared__ Before s_wb[kDWaves];
   __shared__ uint32_t s_w[kDWaves];
-  __shared__ Before s_at;  // before the tile that holds the segment's start
-  __shared__ uint32_t s_tile;
+  __shared__ uint64_t s_cnt[padded(kMaxStreamTiles)];  // entries before each tile (tile i at pad(i))
+  __shared__ uint32_t s_sum[padded(kMaxStreamTiles)];  // and their plain sum
   const uint64_t n = stream_length(p.nbytes, p.in_capacity);
   const Geo g = stream_geometry(n);
   uint64_t* words = stream_words(p.ws);
+  const uint32_t per = (g.ntiles + kDT - 1) / kDT;  // tiles of a thread
   Before run = Before::id(), total;
   uint64_t x[kFoldPer];
 #pragma unroll
   for (uint32_t q = 0; q < kFoldPer; ++q) {
-    const uint32_t i = threadIdx.x * kFoldPer + q;
+    if (q >= per) break;  // block-uniform
+    const uint32_t i = threadIdx.x * per + q;
     x[q] = i < g.ntiles ? words[i] : 0ull;
+  }
+#pragma unroll
+  for (uint32_t q = 0; q < kFoldPer; ++q) {
+    if (q >= per) break;
     run = comb(run, Before{(uint32_t)x[q], (uint32_t)(x[q] >> 32)});
   }
-  const Before mine = block_scan_excl<kDT>(run, Before::id(), s_wb, &total);
-  // f(tile, entries and sum before it, entries before the next) for this thread's tiles
-  auto tiles = [&](auto f) {
-    Before at = mine;
+  Before at = block_scan_excl<kDT>(run, Before::id(), s_wb, &total);
 #pragma unroll
-    for (uint32_t q = 0; q < kFoldPer; ++q) {
-      const uint32_t i = threadIdx.x * kFoldPer + q;
-      const Before next = comb(at, Before{(uint32_t)x[q], (uint32_t)(x[q] >> 32)});
-      if (i < g.ntiles) f(i, at, next.cnt);
-      at = next;
+  for (uint32_t q = 0; q < kFoldPer; ++q) {
+    if (q >= per) break;
+    const uint32_t i = threadIdx.x * per + q;
+    if (i < g.ntiles) {
+      s_cnt[pad(i)] = at.cnt;
+      s_sum[pad(i)] = at.sum;
     }
+    at = comb(at, Before{(uint32_t)x[q], (uint32_t)(x[q] >> 32)});
+  }
+  __syncthreads();
+  // The first tile with more than e entries before it; every wave searches for itself.
+  auto past = [&](uint64_t e) {
+    return e == ~0ull ? g.ntiles
+                      : lower_bound_wave([&](uint32_t i) { return s_cnt[pad(i)]; }, g.ntiles, e + 1);
   };
   auto segment = [&](uint64_t e, uint64_t next) {  // block-uniform
-    bool any = false;
-    __syncthreads();  // the last segment's shared words are read
-    tiles([&](uint32_t i, Before at, uint64_t end) {
-      any |= (at.cnt > e || e == 0) && at.cnt <= next;
-      if (at.cnt <= e && e < end) {
-        s_at = at;
-        s_tile = i;
-      }
-    });
-    if (!__syncthreads_or(any)) return;
+    const uint32_t i0 = e == 0 ? 0u : past(e), i1 = past(next);
+    if (i0 >= i1) return;  // no tile's first entry lies in the segment
     uint32_t before = 0;  // the sum of all numbers before entry e
     if (e > 0) {
-      const uint32_t want = (uint32_t)(e - s_at.cnt);  // the tile's entries before e
-      const uint64_t t0 = (uint64_t)s_tile * g.tile;
+      const uint32_t tile = i0 - 1;  // holds entry e
+      const uint32_t want = (uint32_t)(e - s_cnt[pad(tile)]);  // its entries before e
+      const uint64_t t0 = (uint64_t)tile * g.tile;
       const uint64_t t1 = t0 + g.tile < n ? t0 + g.tile : n;
       uint32_t seen = 0, sum = 0;
       for (uint64_t u0 = t0; u0 < t1 && seen < want; u0 += kDUnit) {  // block-uniform
@@ -501,14 +513,12 @@ __global__ __launch_bounds__(kDT) void varint_carry_kernel(VarintDecParams p) {
       }
       uint32_t all;
       (void)block_count_excl(sum, s_w, &all);
-      before = s_at.sum + all;
+      before = s_sum[pad(tile)] + all;
     }
-    tiles([&](uint32_t i, Before at, uint64_t) {
-      if ((at.cnt > e || e == 0) && at.cnt <= next) {
-        words[kFirstWords + i] = at.cnt;
-        words[kCarryWords + i] = (uint64_t)(at.sum - before);
-      }
-    });
+    for (uint32_t i = i0 + threadIdx.x; i < i1; i += kDT) {
+      words[kFirstWords + i] = s_cnt[pad(i)];
+      words[kCarryWords + i] = (uint64_t)(s_sum[pad(i)] - before);
+    }
   };
   const uint32_t nseg = p.seg_begin ? p.nseg : 0u;
   if (blockIdx.x == 0) {
@@ -527,7 +537,6 @@ __global__ __launch_bounds__(kDT) void varint_carry_kernel(VarintDecParams p) {
 __global__ __launch_bounds__(kDT) void varint_write_kernel(VarintDecParams p) {
   __shared__ uint32_t s_val[padded(kDUnit)];  // the unit's indices, in entry order (entry i at pad(i))
   __shared__ uint32_t s_bits[kDUnit / 32];
-  __shared__ uint32_t s_range[2];
   __shared__ uint32_t s_w[kDWaves];
   __shared__ Sum64 s_wu[kDWaves];
   __shared__ SegSum s_ws[kDWaves];
@@ -588,9 +597,8 @@ __global__ __launch_bounds__(kDT) void varint_write_kernel(VarintDecParams p) {
       acc = carry + (uint32_t)(ex >> 32);
       carry += (uint32_t)(all.v >> 32);
     } else {
-      for (uint32_t i = (uint32_t)tid; i < kDUnit / 32; i += kDT) s_bits[i] = 0;
-      k = block_count_excl(mine, s_w, &ucnt);  // its barriers order the clearing
-      mark_unit_starts(p.seg_begin, s_seg, e, e + ucnt, s_bits, s_range);
+      k = block_count_excl(mine, s_w, &ucnt);
+      mark_unit(p.seg_begin, s_seg, e, e + ucnt, s_bits);
       SegSum own = SegSum::id();
       uint32_t r = k;
 #pragma unroll
@@ -699,7 +707,9 @@ hipError_t launch_varint_decode(const VarintDecParams& p, hipStream_t stream) {
   const uint32_t grid = tile_grid(p.in_capacity);
   hipLaunchKernelGGL(varint_count_kernel, dim3(grid), dim3(kDT), 0, stream, p);
   if (hipError_t e = hipGetLastError()) return e;
-  const uint32_t nseg = p.nseg < 1u ? 1u : p.nseg < 512u ? p.nseg : 512u;
+  // as many blocks as are resident: each folds all tile words (3,000 segments of
+  // the 150M set: 512 blocks 32.6 us, 768 28.4, 1,024 30.7)
+  const uint32_t nseg = p.nseg < 1u ? 1u : p.nseg < 768u ? p.nseg : 768u;
   hipLaunchKernelGGL(varint_carry_kernel, dim3(nseg), dim3(kDT), 0, stream, p);
   if (hipError_t e = hipGetLastError()) return e;
   hipLaunchKernelGGL(varint_write_kernel, dim3(grid), dim3(kDT), 0, stream, p);

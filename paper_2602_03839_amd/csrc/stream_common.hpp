@@ -103,14 +103,15 @@ __device__ inline uint32_t block_count_excl(uint32_t v, uint32_t* s_w, uint32_t*
   return before + incl - v;
 }
 
-// First position in [0, n) with a[pos] >= key (a non-decreasing), whole wave.
-__device__ inline uint32_t lower_bound_wave(const uint64_t* a, uint32_t n, uint64_t key) {
+// First position in [0, n) with a(pos) >= key (a non-decreasing), whole wave.
+template <typename At>
+__device__ uint32_t lower_bound_wave(At a, uint32_t n, uint64_t key) {
   const int lane = lane_id();
   uint32_t lo = 0, hi = n;
   while (hi - lo > 64) {
     const uint32_t span = hi - lo;
     const uint32_t q = lo + (uint32_t)((uint64_t)span * (uint32_t)(lane + 1) / 65u);
-    const uint64_t ge = __ballot(a[q] >= key);
+    const uint64_t ge = __ballot(a(q) >= key);
     if (ge == 0) {
       lo = (uint32_t)__shfl((int)q, 63, 64) + 1;
     } else {
@@ -121,8 +122,12 @@ __device__ inline uint32_t lower_bound_wave(const uint64_t* a, uint32_t n, uint6
     }
   }
   const uint32_t q = lo + (uint32_t)lane;
-  const uint64_t ge = __ballot(q < hi && a[q] >= key);
+  const uint64_t ge = __ballot(q < hi && a(q) >= key);
   return ge == 0 ? hi : lo + (uint32_t)__builtin_ctzll(ge);
+}
+
+__device__ inline uint32_t lower_bound_wave(const uint64_t* a, uint32_t n, uint64_t key) {
+  return lower_bound_wave([a](uint32_t i) { return a[i]; }, n, key);
 }
 
 // ---------------------------------------------------------------- segment starts
@@ -185,28 +190,6 @@ __device__ inline uint32_t lower_bound_cached(const uint64_t* starts, const SegC
     else hi = mid;
   }
   return C.lo + lo;
-}
-
-// Marks in the LDS bitmap (bit k - u0; zero and visible before the call) every
-// k in [u0, u1) -- a part of the cached tile -- at which a segment starts, and
-// bit 0 when u0 == 0 (the stream's first item always starts one).  range
-// receives the segments starting in [u0, u1).  Every thread calls it; it ends
-// with a barrier.
-__device__ inline void mark_unit_starts(const uint64_t* starts, const SegCache& C, uint64_t u0, uint64_t u1,
-                                        uint32_t* bits, uint32_t* range) {
-  for (uint32_t i = threadIdx.x; i < C.n; i += kDT) {
-    const uint64_t v = start_of(starts, C, C.lo + i);
-    if (v >= u0 && v < u1) {
-      const uint32_t b = (uint32_t)(v - u0);
-      atomicOr(&bits[b >> 5], 1u << (b & 31));
-    }
-  }
-  if (threadIdx.x == 0) {
-    if (u0 == 0 && u1 > 0) atomicOr(&bits[0], 1u);
-    range[0] = lower_bound_cached(starts, C, u0);
-    range[1] = lower_bound_cached(starts, C, u1);
-  }
-  __syncthreads();
 }
 
 __device__ __forceinline__ bool bit_at(const uint32_t* s_bits, uint32_t i) {
