@@ -117,12 +117,37 @@ def test_outer_step_out_of_range_indices_capacity_and_max_base():
     np.testing.assert_array_equal(hf32(th_d), th)
 
 
-def test_outer_step_batch_segments_and_launch_split():
+@pytest.mark.parametrize("n", [TILE - 1, 2 * TILE + 5, 256 * TILE, 256 * TILE + 1])
+@pytest.mark.parametrize("low", [0, 1, 200, 7000])
+def test_outer_step_both_launch_forms_and_entries_below(n, low):
+    """The last size of the form for small launches and the first past it, with
+    entries below the tensor in front of its own (ignored, however many), one list
+    with nothing else, one without entries and one starting past the first tile."""
+    rng = np.random.default_rng(n + low)
+    base = 10_000
+    below = np.arange(base - low, base)
+    th = (rng.standard_normal(n) * 0.1).astype(np.float32)
+    m = (rng.standard_normal(n) * 0.01).astype(np.float32)
+    th_d, m_d = dev(th), dev(m)
+    own = np.sort(rng.choice(n, max(1, n // 30), replace=False)) + base
+    lists = []
+    for at in (np.concatenate([below, own]), below, own[:0], own[own >= base + TILE], np.concatenate([below, own[:3]])):
+        lists.append((at.astype(np.uint32), rng.standard_normal(at.size).astype(np.float32)))
+    oracle.outer_step(th, m, lists, mu=MU, alpha=ALPHA, index_base=base)
+    pulse.outer_step(th_d, m_d, gpu_lists(lists, extra=2), mu=MU, alpha=ALPHA, index_base=base)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(hf32(m_d), m)
+    np.testing.assert_array_equal(hf32(th_d), th)
+
+
+@pytest.mark.parametrize("big", [0, 300 * TILE])
+def test_outer_step_batch_segments_and_launch_split(big):
     """Per-tensor segments of each worker's patch, flat index space, more
     tensors than one launch takes, empty and ragged tensors."""
     rng = np.random.default_rng(8)
     sizes = [0, 5, UNIT, 0, 8192 * 3 + 1, 1, 40_000] + [int(rng.integers(0, 3000)) for _ in range(70)]
-    sizes += [UNIT + 17]
+    sizes += [UNIT + 17 + big]
+    sizes[2] += big  # past the small launches' form in the first launch, and in the last
     offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
     N = int(offs[-1])
     th = (rng.standard_normal(N) * 0.1).astype(np.float32)
