@@ -214,11 +214,17 @@ struct LowpApplyParams {
 };
 
 // Blocks of an apply launch over at most `capacity` entries, 256 per block and
-// pass: 2,048 stride over a large patch, a small one takes what it needs.  (512
-// to 8,192 blocks took 165-166 us on the 0.5B set's patch, one pass per block
-// 178.)
+// pass: a small patch takes what it needs, a large one strides, with four passes
+// per block up to 8,192 blocks.  A block's passes drift apart from its neighbours',
+// and the patch's writes lose locality: 2,048 / 8,192 blocks took 88.3 / 86.9 us on
+// the 150M set's patch (2.4% density), 166 / 164 on the 0.5B set's; one pass per
+// block 178 there.  (Launches of 64 tensors each drift least, 85.2 us in 170
+// tensors, but cost a launch each: 50M in 300 at 0.9% 46.5 us against 19.8.)
 constexpr uint32_t apply_blocks(uint64_t capacity) {
-  return capacity >= 2048ull * 256 ? 2048u : (uint32_t)((capacity + 255) / 256);
+  return capacity >= 8192ull * 1024   ? 8192u
+         : capacity >= 2048ull * 1024 ? (uint32_t)(capacity / 1024)
+         : capacity >= 2048ull * 256  ? 2048u
+                                      : (uint32_t)((capacity + 255) / 256);
 }
 
 static_assert(sizeof(LowpParams) < 4096, "kernel argument block too large");

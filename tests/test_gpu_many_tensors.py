@@ -251,3 +251,24 @@ def test_threshold_two_pass_many_tensors(T, cap_frac):
     np.testing.assert_array_equal(hf32(val)[:cap].view(np.uint32), o_val[:cap].view(np.uint32))
     for t, (r_d, r) in enumerate(zip(res, want)):
         np.testing.assert_array_equal(hf32(r_d).view(np.uint32), r.view(np.uint32), err_msg=str(t))
+
+
+@pytest.mark.parametrize("capacity", [1, 255, 257, 2048 * 256 - 1, 2048 * 256 + 1, 2048 * 1024 + 5, 8192 * 1024 - 1,
+                                      8192 * 1024 + 3])
+def test_apply_capacity_sets_the_grid(capacity):
+    """Each size of an apply's grid, with the entries at the capacity's end and
+    more of them than one pass of the blocks takes."""
+    rng = np.random.default_rng(capacity)
+    k = min(capacity, 3_000_000)
+    n = 4 * k + 9
+    at = np.sort(rng.choice(n, k, replace=False)).astype(np.uint32)
+    dst = rng.integers(0, 1 << 16, n).astype(np.uint16)
+    idx = np.zeros(capacity, np.uint32)
+    val = np.zeros(capacity, np.uint16)
+    idx[capacity - k:], val[capacity - k:] = at, rng.integers(0, 1 << 16, k)
+    dst_d, rejected = dev(dst), counter(0)
+    pulse.apply(dst_d, dev(idx), dev(val), counter(capacity - k), counter(capacity + 10), rejected=rejected)
+    torch.cuda.synchronize()
+    dst[at] = val[capacity - k:]
+    np.testing.assert_array_equal(h16(dst_d), dst)
+    assert read_count(rejected) == 0
