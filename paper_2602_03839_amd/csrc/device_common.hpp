@@ -21,11 +21,11 @@ namespace pulse {
 // The header holds four words, each on its own 128-byte cache line so that
 // polls of one never contend with the atomics on another:
 // word kWordTicket: ticket counter = (G0 << 24) | c, where c counts the chunks
-//         of kChunk consecutive tiles drawn in the current launch and G0 is the
+//         of consecutive tiles (kChunk) drawn in the current launch and G0 is the
 //         global sequence number of that launch's first tile.  Blocks are
 //         persistent and draw chunks until they get one past the launch's last
 //         tile.  A single device-wide counter sustains only ~75M atomics/s on
-//         MI355X, so tiles are handed out kChunk at a time.
+//         MI355X, so tiles are handed out a chunk at a time.
 // word kWordGaveUp: set to 1 if a look-back ever gave up waiting (see look_back).
 // word kWordDone: number of blocks of the current launch that have finished.
 //         The last block out (every other block has made its final draw before
@@ -196,14 +196,15 @@ __device__ __forceinline__ void finish_launch(uint64_t* ws, uint64_t g0, uint32_
 constexpr uint64_t kNoTicket = kTicketMask;
 
 // Tiles per ticket.  A chunk's tiles are processed in consecutive iterations,
-// so the chunk's last aggregate appears kChunk - 1 iterations after its first;
-// with kChunk <= RES + 1 later tiles never wait for it at resolution time.
-// Two, measured against four, three and one (us; the encode with RES 2, the
-// lower-precision encode with RES 4): 0.5B set in place 645 / 693 / 685 / 671,
-// mirrored 7B set 9,274 / 9,556 / 9,452 / 9,847, FP8 0.5B set 468 / 508 / - / -.
-// Fewer tiles per ticket keep the chip's reads closer to address order and the
-// last wave of tiles shorter, until the one ticket counter (70-88M draws a
-// second) becomes the bound.
+// so the chunk's last aggregate appears chunk - 1 iterations after its first;
+// with chunk <= RES + 1 later tiles never wait for it at resolution time.
+// Two, measured against four, three and one (us; the refreshing encode with RES 2,
+// the lower-precision encode with RES 4): 0.5B set in place 645 / 693 / 685 / 671,
+// mirrored 7B set 9,274 / 9,556 / 9,452 / 9,847, FP8 0.5B set 468 / 508 / - / -,
+// MXFP4 7B set 5,431 / 5,482 / - / -.  Fewer tiles per ticket keep the chip's reads
+// closer to address order and the last wave of tiles shorter, until the one ticket
+// counter (70-88M draws a second) becomes the bound.  The encode without refresh,
+// which writes next to nothing, takes four on large sets (encode.hip).
 constexpr uint32_t kChunk = 2;
 
 // Tiles whose loads a block keeps in flight: while a block computes tile T(i),
@@ -517,16 +518,19 @@ struct KnownPrefix {
 };
 constexpr uint32_t kNoTile = 0xFFFFFFFFu;
 
+// chunk: tiles per ticket, at most RES + 1 (every tile of a chunk must be computed
+// before its first resolves).
 template <int U, int NW, int RES, bool TABLE, typename Params, int AHEAD = kAhead>
 __device__ void scan_wave_loop(const Params& p, const uint32_t* s_begin, uint64_t* s_tk, uint32_t* s_wtot2,
                                uint32_t* s_wexcl, uint64_t* s_excl2, uint32_t* s_cnt2,
-                               uint32_t* s_ovf2, uint32_t seg_cap, KnownPrefix* s_known) {
+                               uint32_t* s_ovf2, uint32_t seg_cap, KnownPrefix* s_known,
+                               uint32_t chunk = kChunk) {
   constexpr int kResolve = RES;
   constexpr int kDefer = RES + 1;
   constexpr int kWexclRing = wexcl_ring(RES);
   static_assert(kChunk <= kDefer, "a chunk's tiles must all be computed before the first resolves");
   const int lane = lane_id();
-  // tiles come in chunks of kChunk consecutive tiles, one atomic per chunk;
+  // tiles come in chunks of consecutive tiles, one atomic per chunk;
   // next_tile / left: the unused part of the block's current chunk.  The next
   // chunk is always drawn one chunk ahead (`pre`, lane 0), so the atomic's
   // round trip overlaps a whole chunk of iterations instead of delaying the
@@ -538,8 +542,8 @@ __device__ void scan_wave_loop(const Params& p, const uint32_t* s_begin, uint64_
       const uint64_t c = pre;
       pre = draw_ticket(p.ws);
       g0 = c >> kTicketBits;
-      next_tile = (uint32_t)(c & kTicketMask) * kChunk;
-      left = kChunk;
+      next_tile = (uint32_t)(c & kTicketMask) * chunk;
+      left = chunk;
     }
     --left;
     return make_ticket(g0, next_tile++, p.ntiles);

@@ -135,14 +135,20 @@ __device__ __forceinline__ void finish_group(TileRegs<TBC, U>& r, int u, const T
 // computing iteration i + kDefer + 1 at different times, so the slot may be
 // refilled only from iteration i + kDefer + 2 on, after the next barrier.
 constexpr uint32_t kSegCap = 64;
-// Iterations from a tile's compute to its resolution and to its write-out.  Two
-// iterations find the predecessors published with two tiles per ticket, and a
-// launch drains in three: the 0.5B set in place took 645 us (4: 678, 3: 663),
-// the mirrored 7B set the same within 0.4%.
-constexpr int kResolve = 2;
-constexpr int kDefer = kResolve + 1;
-constexpr int kWexclRing = wexcl_ring(kResolve);
-constexpr int kSegSlots = kDefer + 2;
+// Iterations from a tile's compute to its resolution (and, one later, to its
+// write-out), and tiles per ticket.  With a refresh: two and two; two iterations
+// find the predecessors published with two tiles per ticket, and a launch drains in
+// three: the 0.5B set in place took 645 us (4 iterations: 678, 3: 663), the
+// mirrored 7B set the same within 0.4%.  The encode without refresh only reads, and
+// waits on the look-back sooner: four iterations, and four tiles per ticket in
+// launches of 2^16 tiles (1.0B elements) and more.  Iterations x tiles per ticket,
+// us: 400M in 64 tensors 2 x 2 442, 4 x 4 437, 4 x 2 425; 0.5B set 561 / 562 / 522;
+// 1.5B in 100 1,551-1,620 / 1,419-1,475 / 1,548; 7B set 7,600 / 7,185 / 7,480; 32B
+// set 32,650 / 31,390 / 32,170.
+constexpr int encode_resolve(bool refresh) { return refresh ? 2 : 4; }
+constexpr uint32_t kPlainChunk = 4;
+constexpr uint32_t kPlainChunkTiles = 1u << 16;
+static_assert(kPlainChunk <= (uint32_t)encode_resolve(false) + 1, "a chunk is computed before its first tile resolves");
 
 // What the write-out of a tile needs kDefer iterations after its compute:
 // where it lies (wave-uniform) and, per lane, the change masks (8 bits per
@@ -172,6 +178,10 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
   constexpr int TBC = NW * 64;
   constexpr uint32_t TILE = TBC * U * 8;
   constexpr int NSEG = U * NW;  // wave-groups per tile, group-major
+  constexpr int kResolve = encode_resolve(REFRESH);
+  constexpr int kDefer = kResolve + 1;
+  constexpr int kWexclRing = wexcl_ring(kResolve);
+  constexpr int kSegSlots = kDefer + 2;
   __shared__ uint64_t s_tk[kTkRing];
   __shared__ uint64_t s_excl[2];
   __shared__ uint32_t s_tcnt[2];
@@ -193,7 +203,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void encode_kernel(EncodeParams p) {
   TileMap<TABLE, EncodeParams>::fill(p, s_begin);
   if (wid == NW) {
     scan_wave_loop<U, NW, kResolve, TABLE>(p, s_begin, s_tk, s_wtot, s_wexcl, s_excl, s_tcnt, s_tovf, kSegCap,
-                                     s_known);
+                                           s_known, !REFRESH && p.ntiles >= kPlainChunkTiles ? kPlainChunk : kChunk);
     return;
   }
 

@@ -179,3 +179,35 @@ def test_encode_many_ragged_tensors_four_groups(ws, density, cap_frac):
 @pytest.mark.parametrize("dtype", [pulse.FP8_E4M3, pulse.MXFP4])
 def test_lowp_many_ragged_tensors_four_groups(ws, dtype):
     test_lowp_one_tile_and_persistent(ws, dtype, RAGGED4)
+
+
+@pytest.mark.parametrize("tiles,ragged", [((1 << 16) - 1, 0), (1 << 16, 5), ((1 << 16) + 3, 0)])
+@pytest.mark.parametrize("refresh", [False, True])
+def test_encode_tiles_per_ticket(ws, tiles, ragged, refresh):
+    """The persistent encode around the launch size where the form without refresh
+    takes four tiles per ticket instead of two: masters and snapshot zero but for
+    2M places whose patch the host knows, clustered in some tiles."""
+    n = tiles * 15360 - ragged
+    rng = np.random.default_rng(tiles + ragged)
+    at = np.unique(np.concatenate([rng.integers(0, n, 1_500_000), rng.integers(n // 2, n // 2 + 900_000, 500_000),
+                                   np.arange(n - 300, n), np.arange(300)]))
+    v = rng.standard_normal(at.size, dtype=np.float32)
+    bits = oracle.cast(v)
+    w = torch.zeros(n, dtype=torch.float32, device="cuda")
+    w[torch.from_numpy(at).cuda()] = dev(v)
+    snap = torch.zeros(n, dtype=torch.int16, device="cuda")
+    keep = bits != 0
+    at, bits = at[keep], bits[keep]
+    idx = torch.zeros(at.size + 5, dtype=torch.int32, device="cuda")
+    val = torch.zeros(at.size + 5, dtype=torch.int16, device="cuda")
+    copy = torch.zeros(n, dtype=torch.int16, device="cuda") if refresh else None
+    count = counter(2)
+    pulse.encode(w, snap, idx, val, count, ws, refresh=copy)
+    torch.cuda.synchronize()
+    assert read_count(count) == at.size + 2
+    np.testing.assert_array_equal(h32(idx)[2:-3], at.astype(np.uint32))
+    np.testing.assert_array_equal(h16(val)[2:-3], bits)
+    if refresh:
+        assert int((copy != 0).sum().item()) == at.size
+        np.testing.assert_array_equal(h16(copy[torch.from_numpy(at).cuda()]), bits)
+    pulse.check_workspace(ws)
