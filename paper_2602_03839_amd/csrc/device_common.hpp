@@ -12,7 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <mutex>
+#include "persistent_grid.hpp"
 
 namespace pulse {
 
@@ -60,8 +60,6 @@ constexpr size_t kTableWords = 1u << 15;
 constexpr size_t kTableOffsetWords = kStatusOffsetWords + kSlots;
 constexpr size_t kWorkspaceBytes = (kTableOffsetWords + kTableWords) * sizeof(uint64_t);
 constexpr uint32_t kMaxTilesPerLaunch = (1u << kTicketBits) - 1;  // < kNoTicket
-// Largest grid of a ticketed launch.
-constexpr uint32_t kMaxGrid = 1u << 16;
 
 // status word: [63:62] flag, [61:54] lap tag, [53:0] value
 constexpr uint64_t kFlagAggregate = 1;  // value = this tile's own count
@@ -785,35 +783,6 @@ __device__ __forceinline__ int segment_before(const uint64_t* s, int nt, uint64_
   for (int step = 128; step > 0; step >>= 1)
     if (t + step < nt && s[t + step] <= k) t += step;
   return t;
-}
-
-// Blocks of `kernel` (launched with `block` threads) that fit on the current
-// device at once: the grid of a persistent launch.  The occupancy query is
-// made once per (device, kernel) and remembered.
-inline int persistent_grid(const void* kernel, int block) {
-  struct Entry {
-    const void* kernel;
-    int dev, block, grid;
-  };
-  static Entry cache[64];
-  static int used = 0;
-  static std::mutex mu;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  {
-    std::lock_guard<std::mutex> g(mu);
-    for (int i = 0; i < used; ++i)
-      if (cache[i].kernel == kernel && cache[i].dev == dev && cache[i].block == block)
-        return cache[i].grid;
-  }
-  int cus = 0, per_cu = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, 0) != hipSuccess) return 0;
-  int grid = cus * (per_cu > 0 ? per_cu : 1);
-  if (grid > (int)kMaxGrid) grid = (int)kMaxGrid;
-  std::lock_guard<std::mutex> g(mu);
-  if (used < 64) cache[used++] = Entry{kernel, dev, block, grid};
-  return grid;
 }
 
 }  // namespace pulse
