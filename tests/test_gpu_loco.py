@@ -2,10 +2,12 @@
 emitted indices, FP32 values and the FP32 residual, over shapes, thresholds,
 the BF16-gate form, overflow, batches, and a 10-round error-feedback chain.
 
-Every test runs twice: with a plain workspace (the one-pass persistent
-kernel) and with one that has room for the two-pass form's staging area
-(the threshold form then stages 1,024-element tiles and orders them in a
-second pass; the gate forms still run in one pass)."""
+Calls of up to ONE_TILE elements take one tile per block, whatever the workspace.
+The tests run at such sizes and, with `past` (a tensor of ONE_TILE elements more),
+in the forms for larger calls: with a plain workspace the one-pass persistent
+kernel, with one that has room for a staging area the two-pass form (the threshold
+form then stages 1,024-element tiles and orders them in a second pass; the gate
+forms still run in one pass)."""
 import math
 
 import numpy as np
@@ -19,8 +21,10 @@ from tests.gpu_helpers import counter, dev, h32, hf32, read_count
 
 pytestmark = pytest.mark.gpu
 
-TILE = 960 * 2 * 8  # sparsify tile (elements) of the threshold form
-GATE_TILE = 960 * 1 * 8  # and of the gate forms
+TILE = 960 * 2 * 8  # two tiles of the persistent kernel
+GATE_TILE = 960 * 1 * 8  # its tile (elements)
+ONE_TILE = 768 * 8192  # the largest call in the one-tile form
+past = pytest.mark.parametrize("past", [0, ONE_TILE], ids=["one_tile", "past"])
 EDGES = sorted({m * t + d for t in (7680, 15360) for m in (1, 3) for d in (-1, 0, 1)})
 
 
@@ -28,7 +32,7 @@ EDGES = sorted({m * t + d for t in (7680, 15360) for m in (1, 3) for d in (-1, 0
 def ws(request):
     if request.param == "one_pass":
         return pulse.workspace()
-    return pulse.loco_workspace(1 << 24)
+    return pulse.loco_workspace(1 << 24)  # holds every call below
 
 
 def run_loco(delta, res, tau, ws, theta=None, capacity=None, index_base=0, count_in=0):
@@ -54,7 +58,8 @@ def run_loco(delta, res, tau, ws, theta=None, capacity=None, index_base=0, count
     return o_cnt, o_res
 
 
-@pytest.mark.parametrize("n", [1, 9] + EDGES + [4 * TILE + 3, 123_457])
+@pytest.mark.parametrize("n", [1, 9] + EDGES + [4 * TILE + 3, 123_457, ONE_TILE, ONE_TILE + 1] +
+                         [820 * GATE_TILE + d for d in (-1, 0, 1, 5000)])
 def test_loco_threshold_shapes(ws, n):
     rng = np.random.default_rng(n)
     tau = wl.loco_tau()
@@ -63,9 +68,10 @@ def test_loco_threshold_shapes(ws, n):
     run_loco(d, e, tau, ws)
 
 
-def test_loco_special_thresholds_and_values(ws):
+@past
+def test_loco_special_thresholds_and_values(ws, past):
     rng = np.random.default_rng(3)
-    n = 2 * TILE + 17
+    n = 2 * TILE + 17 + past
     d = wl.loco_delta_np(rng, n)
     sp = np.array([0x7FC00000, 0x7F800000, 0xFF800000, 0x80000000, 0x00000001],
                   np.uint32).view(np.float32)
@@ -76,9 +82,10 @@ def test_loco_special_thresholds_and_values(ws):
         run_loco(d, e, tau, ws)
 
 
-def test_loco_gate_form(ws):
+@past
+def test_loco_gate_form(ws, past):
     rng = np.random.default_rng(4)
-    n = 3 * TILE + 5
+    n = 3 * TILE + 5 + past
     theta = rng.normal(0, math.sqrt(wl.W_VAR), n).astype(np.float32)
     d = (wl.loco_delta_np(rng, n) * np.float32(30)).astype(np.float32)
     e = (wl.loco_delta_np(rng, n) * np.float32(10)).astype(np.float32)
@@ -86,9 +93,10 @@ def test_loco_gate_form(ws):
     assert 0 < cnt < n
 
 
-def test_loco_overflow_append_base(ws):
+@past
+def test_loco_overflow_append_base(ws, past):
     rng = np.random.default_rng(5)
-    n = 5 * TILE + 99
+    n = 5 * TILE + 99 + past
     d = wl.loco_delta_np(rng, n)
     e = np.zeros(n, np.float32)
     tau = wl.loco_tau()
@@ -97,16 +105,18 @@ def test_loco_overflow_append_base(ws):
         run_loco(d, e, tau, ws, capacity=cap, count_in=7, index_base=999)
 
 
+@past
 @pytest.mark.parametrize("gate", [False, True])
-def test_loco_mixed_segment_overflow(ws, gate):
-    """Tiles where some 512-element wave-groups select more entries than their
+def test_loco_mixed_segment_overflow(ws, gate, past):
+    """Past the one-tile form: tiles where some 512-element wave-groups select more entries than their
     compaction segment holds (30%) and others few (1%): the write-out mixes
     entries from the segments with entries read back from the residual, with
-    and without the patch capacity cutting through both kinds of group."""
+    and without the patch capacity cutting through both kinds of group.  (The
+    one-tile form has no segments; its sizes run the same inputs.)"""
     rng = np.random.default_rng(21 + gate)
     tau = wl.loco_tau()
-    tile = GATE_TILE if gate else TILE
-    n = 3 * tile + 4 * 512 + 77
+    tile = GATE_TILE
+    n = 3 * tile + 4 * 512 + 77 + past
     region = (np.arange(n) % tile) // 512
     dense = (region % 3 == 0) | (region == 7)
     p = np.where(dense, 0.30, 0.01)
@@ -148,9 +158,10 @@ def test_loco_ten_round_chain(ws):
     assert abs(dens[0] - 0.02) < 0.002 and dens[-1] > dens[0]
 
 
-def test_loco_batch_with_empty_tensors(ws):
+@past
+def test_loco_batch_with_empty_tensors(ws, past):
     rng = np.random.default_rng(13)
-    sizes = [0, 3, TILE + 1, 0, 50_001, 8, 0] + [int(rng.integers(0, 5000)) for _ in range(66)]
+    sizes = [0, 3, TILE + 1, 0, 50_001 + past, 8, 0] + [int(rng.integers(0, 5000)) for _ in range(66)]
     tau = wl.loco_tau()
     descs, host = [], []
     base = 0
@@ -187,11 +198,15 @@ def test_loco_batch_with_empty_tensors(ws):
 L2_TILE = 1024  # tile of the two-pass form
 
 
+@past
 @pytest.mark.parametrize("n", [L2_TILE - 1, L2_TILE, L2_TILE + 1, 256 * L2_TILE, 256 * L2_TILE + 1,
                                300 * L2_TILE + 513])
-def test_loco_two_pass_tile_and_unit_edges(n):
+def test_loco_two_pass_tile_and_unit_edges(n, past):
     """Tile edges of the staging pass and unit edges (256 tiles) of the
-    ordering passes, with an append position and an index base."""
+    ordering passes (`past` is 24 whole units), with an append position and an
+    index base."""
+    assert past % (256 * L2_TILE) == 0
+    n += past
     rng = np.random.default_rng(n)
     tau = wl.loco_tau()
     d = wl.loco_delta_np(rng, n)
@@ -202,13 +217,14 @@ def test_loco_two_pass_tile_and_unit_edges(n):
     run_loco(d, e, tau, ws2, capacity=11 + nnz // 2, count_in=11, index_base=5)
 
 
-def test_loco_two_pass_dense_tiles():
-    """Tiles that select more than a staging slot holds (128 of 1,024) beside
+@past
+def test_loco_two_pass_dense_tiles(past):
+    """Past the one-tile form: tiles that select more than a staging slot holds (128 of 1,024) beside
     sparse ones, in every mix within a unit, with the capacity cutting
     through staged tiles, re-derived tiles and the boundary between them."""
     rng = np.random.default_rng(31)
     tau = wl.loco_tau()
-    ntile = 600
+    ntile = 600 + past // L2_TILE
     n = ntile * L2_TILE - 77
     frac = np.repeat(rng.choice([0.001, 0.02, 0.12, 0.13, 0.5, 1.0], ntile), L2_TILE)[:n]
     big = rng.random(n) < frac
@@ -226,14 +242,20 @@ def test_loco_two_pass_dense_tiles():
         run_loco(d, e, tau, ws2, capacity=cap + 2, count_in=2, index_base=1)
 
 
-def test_loco_two_pass_batches_and_fallback():
+@past
+@pytest.mark.parametrize("first", [False, True])
+def test_loco_two_pass_batches_and_fallback(past, first):
     """A threshold-form batch of 150 tensors (empty ones first, between and
-    last; more than 64, so several launches) on a workspace sized for the
-    whole call, then on one whose staging area holds only small launches, so
-    that the tensors too large for it take the one-pass kernel in between."""
+    last; more than 64, so their descriptors go through the table, rewritten for
+    each launch) on a workspace sized for the whole call, then on one whose
+    staging area holds only small launches: those up to the first tensor too
+    large for it, which takes the one-pass kernel with all that follow.  `first`:
+    the batch starts with such a tensor, so that the whole call runs in one pass."""
     rng = np.random.default_rng(41)
     sizes = [0, 0, 5, 3 * L2_TILE + 1, 0] + [int(rng.integers(0, 9000)) for _ in range(140)]
-    sizes += [200_003, 0, 1, 70_000, 0]
+    sizes += [200_003 + past, 0, 1, 70_000, 0] + [int(rng.integers(0, 9000)) for _ in range(70)]
+    if first:
+        sizes[0] = 150_001
     tau = wl.loco_tau()
     host = []
     base = 0

@@ -8,10 +8,12 @@ thousands of elements), a density per tensor from none to all selected (so
 some tiles select more than a staging slot holds), special values (NaN,
 infinities, signed zeros, subnormals), an index layout (one flat index space,
 per-tensor local indices, or bases near 2^32), an append position and a
-capacity that may cut the patch anywhere, and a workspace: a plain one (the
-one-pass kernel), one with room for the whole call (the two-pass form), or
-one whose staging area holds only small launches (the two forms alternate
-within the call)."""
+capacity that may cut the patch anywhere, and a workspace.  Most of these calls
+are small and take one tile per block whatever the workspace.  The second test
+puts a tensor past that form's limit at a random place, with each workspace in
+turn: a plain one (the one-pass kernel), one with room for the whole call (the
+two-pass form), or one whose staging area holds only small launches (two-pass
+launches up to the first tensor too large for it, one pass from there on)."""
 import numpy as np
 import pytest
 import torch
@@ -51,11 +53,25 @@ def draw_tensor(rng, n):
     return d, e
 
 
+ONE_TILE = 768 * 8192  # the largest call in the one-tile form
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_loco_random_batches(seed):
+    check_batch(seed, False)
+
+
+@pytest.mark.parametrize("seed", range(24, 36))
+def test_loco_random_batches_past_one_tile(seed):
+    check_batch(seed, True)
+
+
+def check_batch(seed, past):
     rng = np.random.default_rng(1000 + seed)
     nt = int(rng.integers(1, 160))
     sizes = [draw_size(rng) for _ in range(nt)]
+    if past:
+        sizes[int(rng.integers(0, nt))] = ONE_TILE + int(rng.integers(1, 20_000))
     total = sum(sizes)
     layout = rng.choice(["flat", "local", "high"])
     host, base = [], 0
@@ -73,7 +89,7 @@ def test_loco_random_batches(seed):
     nsel = sum(int((np.abs(d + e) >= np.float32(TAU)).sum()) for d, e, _ in host)
     cap = int(rng.choice([count_in + nsel, count_in + nsel // 2, count_in + 3, count_in]))
     cap = max(cap, 1)
-    wkind = int(rng.integers(0, 3))
+    wkind = seed % 3 if past else int(rng.integers(0, 3))
     ws = (pulse.workspace(), pulse.loco_workspace(total), pulse.loco_workspace(20_000))[wkind]
 
     o_idx = np.full(cap, 0xA5A5A5A5, np.uint32)

@@ -445,3 +445,53 @@ def test_loco_gate_lowp_overflow(dtype):
     np.testing.assert_array_equal(h32(idx), oi[:cap])
     np.testing.assert_array_equal(hf32(val).view(np.uint32), ov[:cap].view(np.uint32))
     np.testing.assert_array_equal(hf32(gr).view(np.uint32), res.view(np.uint32))
+
+
+@pytest.mark.parametrize("dtype", [FP8, MX])
+@pytest.mark.parametrize("T", [3, 70])
+@pytest.mark.parametrize("cap_frac", [1.0, 0.4])
+def test_loco_gate_lowp_past_one_tile(dtype, T, cap_frac):
+    """The gate in calls past the one-tile form's 768 tiles of 8,192 (the persistent
+    kernel), its descriptors as kernel arguments (3 tensors) and in the workspace's
+    table (70), ragged and empty tensors among them, the patch cut or not."""
+    rng = np.random.default_rng(70 + dtype + T)
+    sizes = [768 * 8192 + 33] + [int(x) for x in rng.integers(0, 9000, T - 2)] + [3 * 7680 + 31]
+    sizes[1] = 0
+    if T > 3:
+        sizes[T // 2] = 0
+    host, full = [], 0
+    for n in sizes:
+        theta = weights(rng, n, 0.02)
+        delta = (2e-3 * rng.standard_normal(n, dtype=np.float32)).astype(np.float32)
+        e = (5e-4 * rng.standard_normal(n, dtype=np.float32)).astype(np.float32)
+        s = inv_scale_for(theta) if n else 1.0
+        host.append((theta, delta, e, s))
+    want, parts_i, parts_v, seg = [], [], [], []
+    for theta, delta, e, s in host:
+        res = e.copy()
+        seg.append(full)
+        c, oi, ov = oracle.loco_gate_lp(dtype, delta, res, theta, s) if e.size else (0, e[:0].view(np.uint32), e[:0])
+        parts_i.append(oi[:c])
+        parts_v.append(ov[:c])
+        want.append(res)
+        full += c
+    cap = int(full * cap_frac)
+    o_idx, o_val = np.concatenate(parts_i)[:cap], np.concatenate(parts_v)[:cap]
+    for (theta, delta, e, s), res, b, i, v in zip(host, want, seg, parts_i, parts_v):
+        sent = max(0, min(i.size, cap - b))  # past the capacity error feedback keeps the sum
+        res[i[sent:]] = v[sent:]
+    mk = lambda a: dev(a) if a.size else torch.empty(0, dtype=torch.float32, device="cuda")
+    descs = [pulse.LocoTensor(mk(delta), mk(e), mk(theta)) for theta, delta, e, s in host]
+    idx = torch.zeros(cap, dtype=torch.int32, device="cuda")
+    val = torch.zeros(cap, dtype=torch.float32, device="cuda")
+    count, seg_d = counter(0), torch.full((len(sizes),), -1, dtype=torch.int64, device="cuda")
+    ws = pulse.workspace()
+    pulse.LocoLowpBatch(dtype, descs, [h[3] for h in host])(idx, val, count, ws, seg_begin=seg_d, capacity=cap)
+    torch.cuda.synchronize()
+    assert read_count(count) == full > 0
+    np.testing.assert_array_equal(seg_d.cpu().numpy(), np.array(seg))
+    np.testing.assert_array_equal(h32(idx), o_idx)
+    np.testing.assert_array_equal(hf32(val).view(np.uint32), o_val.view(np.uint32))
+    for d, res in zip(descs, want):
+        np.testing.assert_array_equal(hf32(d.residual).view(np.uint32), res.view(np.uint32))
+    pulse.check_workspace(ws)
