@@ -269,9 +269,9 @@ typedef struct pulse_loco_tensor {
  * area and needs no initialisation; the first pulse_workspace_bytes() keep
  * the rules above (zero-filled once), so one workspace may serve every call
  * ordered on a stream.  A launch takes as many tensors as the staging area
- * holds; one that does not fit on its own runs in one pass, as do the gate
- * forms and small calls (up to a few million elements), whatever the
- * workspace.  About 1 byte of workspace per element.
+ * holds.  A tensor that does not fit on its own runs in one pass, and so do the
+ * tensors after it (a launch of up to 1,024 in all).  The gate forms and small
+ * calls (up to 6.3M elements) run in one pass whatever the workspace.  About 1 byte of workspace per element.
  */
 size_t pulse_loco_workspace_bytes(uint64_t n);
 
@@ -376,8 +376,9 @@ int pulse_varint_encode(const uint32_t *idx, uint64_t capacity, const uint64_t *
  *               capacity are not written.
  *   count       device uint64: the number of entries in the stream.
  *   workspace   as for encode.  The decode keeps its per-tile sums in the
- *               workspace and leaves them zero, so the workspace stays valid
- *               for the other ordered kernels on the same stream.
+ *               workspace, in words that every call writes before it reads
+ *               (batches keep their tensors there) and leaves zero, so one
+ *               workspace serves all calls ordered on a stream.
  * Three launches (count, carries, write): the stream is read twice and the
  * indices written once; no block waits on another.
  */
@@ -432,7 +433,8 @@ int pulse_coo_encode(const uint32_t *idx, uint64_t capacity, const uint64_t *end
  * the tile folds, write) give every pair its row, column and escape count since
  * its segment's start, and its entry lands at seg_begin[s] + 1 + (pairs of s
  * before it) - (escapes of s before it).  The library allocates nothing: the
- * per-tile folds live in the workspace and are left zero.  A
+ * per-tile folds live in the workspace, in words written before they are read
+ * and left zero.  A
  * stream that encode did not write decodes to unspecified indices but no
  * access leaves the buffers.
  */

@@ -331,7 +331,7 @@ struct PutWords {
 static_assert(sizeof(PutWords) < 4096, "kernel argument block too large");
 hipError_t launch_put_words(const PutWords& p, hipStream_t stream);
 // refresh: some tensor of the launch has a copy to refresh.  one: 0 = the
-// persistent kernel (encode_tile_elems()), 1 or 2 = one tile per block, of
+// persistent kernel (encode_tile_elems()), 1, 2 or 4 = one tile per block, of
 // one_tile_elems(one) elements
 hipError_t launch_encode(EncodeParams& p, bool refresh, int one, hipStream_t stream);
 // one: one tile of one_tile_elems(1) elements per block, else the persistent kernel

@@ -31,9 +31,10 @@
 //     the residual, which holds s there.  Tensors' patch offsets (seg_begin)
 //     are written here and in pass 2b.
 //
-// Staging memory is the part of the caller's workspace past the fixed header
-// and status ring (see loco2_scratch_bytes); nothing in the fixed part is
-// read or written, so calls of either form may share a workspace.
+// Staging memory is the part of the caller's workspace past the fixed part (see
+// loco2_scratch_bytes).  Of the fixed part only the tensor table of a launch of
+// more than kMaxBatch tensors is read; tickets and status words are not, so calls
+// of either form may share a workspace.
 #include "device_common.hpp"
 #include "launch.hpp"
 

@@ -7,9 +7,9 @@
 //   2. write   one block per tile starts from the fold of the aggregates
 //              before its own, reads its part again and writes its output.
 // The encoders' blocks fold plain sums themselves (a few words per thread cost
-// less than a launch); the decoders have a small launch in between.  The words
-// are left zero, so a zero-filled workspace stays so.  No block waits on
-// another.
+// less than a launch); the decoders have a small launch in between.  Every word is
+// written before it is read, so what a batch's tensor table left there does not
+// matter, and the words a call used are left zero.  No block waits on another.
 #pragma once
 
 #include "device_common.hpp"

@@ -123,3 +123,50 @@ def test_varint_many_segments(nseg, most):
     assert read_count(got) == n
     np.testing.assert_array_equal(h32(back)[:n], idx)
     assert (h32(back)[n:] == 0xFFFFFFFF).all()
+
+
+def test_streams_after_a_tensor_table():
+    """One workspace for a batch whose descriptors lie in its table and for both
+    streams: they write every word before they read it, so what the batch left
+    there does not matter, and a batch after them finds its own."""
+    rng = np.random.default_rng(77)
+    ws = pulse.workspace()
+    sizes = rng.integers(1, 5000, 300)
+    w = [rng.standard_normal(n, dtype=np.float32) for n in sizes]
+    s = [oracle.cast(x) ^ (rng.random(x.size) < 0.05).astype(np.uint16) for x in w]
+    want = [oracle.encode(a, b) for a, b in zip(w, s)]
+    o_idx = np.concatenate([i[:c] for c, i, _ in want])
+    begins = np.concatenate([[0], np.cumsum([c for c, _, _ in want])[:-1]]).astype(np.int64)
+    nnz = o_idx.size
+    cols = np.minimum(sizes, 1000).astype(np.uint32)
+    stream = np.concatenate([oracle.varint_encode(o_idx[a:a + c]) for a, (c, _, _) in zip(begins, want)])
+    of, od, oc, osp = oracle.coo_encode(o_idx, begins.astype(np.uint64), cols)
+    batch = pulse.EncodeBatch([pulse.EncodeTensor(dev(a), dev(b)) for a, b in zip(w, s)])
+    for _ in range(3):
+        idx = torch.zeros(nnz, dtype=torch.int32, device="cuda")
+        val = torch.zeros(nnz, dtype=torch.int16, device="cuda")
+        count, seg = counter(0), torch.full((sizes.size,), -1, dtype=torch.int64, device="cuda")
+        batch(idx, val, count, ws, seg_begin=seg)
+        out = torch.zeros(stream.size + 16, dtype=torch.uint8, device="cuda")
+        total, got, back = counter(0), counter(0), torch.zeros(nnz, dtype=torch.int32, device="cuda")
+        pulse.varint_encode(idx, count, out, total, ws, seg_begin=seg)
+        batch(idx, val, counter(0), ws, seg_begin=seg)  # the table again, between encode and decode
+        pulse.varint_decode(out, total, back, got, ws, seg_begin=seg)
+        drow = torch.zeros(od.size, dtype=torch.uint8, device="cuda")
+        dcol = torch.zeros(od.size, dtype=torch.int16, device="cuda")
+        first = torch.zeros(sizes.size, dtype=torch.int32, device="cuda")
+        sp, pairs, back2 = torch.zeros_like(seg), counter(0), torch.zeros_like(back)
+        pulse.coo_encode(idx, count, seg, dev(cols), first, drow, dcol, sp, pairs, ws)
+        batch(idx, val, counter(0), ws, seg_begin=seg)
+        pulse.coo_decode(drow, dcol, pairs, seg, sp, dev(cols), first, count, back2, ws)
+        torch.cuda.synchronize()
+        assert read_count(count) == read_count(got) == nnz and read_count(total) == stream.size
+        np.testing.assert_array_equal(seg.cpu().numpy(), begins)
+        for i in (idx, back, back2):
+            np.testing.assert_array_equal(h32(i), o_idx)
+        np.testing.assert_array_equal(out[:stream.size].cpu().numpy(), stream)
+        np.testing.assert_array_equal(drow.cpu().numpy(), od)
+        np.testing.assert_array_equal(dcol.cpu().numpy().view(np.uint16), oc)
+        np.testing.assert_array_equal(h32(first), of)
+        np.testing.assert_array_equal(sp.cpu().numpy(), osp.astype(np.int64))
+    pulse.check_workspace(ws)
