@@ -54,7 +54,7 @@ if ROOT not in sys.path:
 METRIC = "encode+apply GB/s of weights scanned, % of MI355X HBM peak; patch density"
 HBM_PEAK_GBS = 8000.0
 WORKLOAD_IDS = {"0.5b": 2, "7b": 3, "32b": 4}
-CHUNK = 64  # tensors per launch (the library's batch limit)
+CHUNK = 64  # tensors per call: as many as a launch's kernel arguments hold
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "encode_fused_32b_traffic.txt")
 CALIB_WORDS = 1 << 28  # int32 words of the plain copy kernel run for counter calibration
 # Vector-ALU peak for 32-bit integer work: 256 CUs x 4 SIMDs x 16 lanes, one

@@ -24,9 +24,13 @@ import glob
 import hashlib
 import json
 import os
+import re
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("encode.hip", "device_common.hpp", "launch.hpp")
+KERNEL_SOURCES = ("encode.hip", "device_common.hpp", "launch.hpp", "persistent_grid.hpp")
+# encode_kernel<waves, groups, refresh, table>: the refresh form, its tensors as
+# kernel arguments or in the workspace's table
+REFRESH_KERNEL = re.compile(r"encode_kernel<\d+, \d+, true, (true|false)>")
 CALIB_KERNEL = "bitwise_not"
 CALIB_BYTES = (1 << 28) * 4  # read, and written, by the calibration kernel
 
@@ -79,7 +83,7 @@ def _rows(directory: str, counter: str):
 def _measure(directory: str, counter: str, n_launch: int):
     rows = _rows(directory, counter)
     calib = [v for _, k, v in rows if CALIB_KERNEL in k]
-    enc = [v for _, k, v in rows if "encode_kernel" in k and "true>" in k][:n_launch]
+    enc = [v for _, k, v in rows if REFRESH_KERNEL.search(k)][:n_launch]
     if not calib or len(enc) < n_launch:
         raise SystemExit(f"{counter}: calibration or encode dispatches missing in {directory}")
     scale = CALIB_BYTES / (calib[0] * 1024.0)
@@ -106,7 +110,6 @@ def kernel_table(dirs, counters_wanted=None, match="pulse|bitwise_not"):
     """Per kernel: dispatches, mean duration and the mean of every counter per
     dispatch over the counter-collection runs in `dirs` (FETCH_SIZE and
     WRITE_SIZE in bytes, calibrated on the copy kernel; other counters raw)."""
-    import re
     per = {}   # label -> counter -> [values]
     dur = {}   # label -> [ns]
     scale = {}
@@ -178,7 +181,6 @@ def stats_main(argv):
     """Markdown summary of a rocprofv3 --kernel-trace --stats run of bench.py:
     the library's kernels, and the headline kernel's average beside the
     benchmark's own event timing of the same run."""
-    import re
     ap = argparse.ArgumentParser(prog="traffic stats")
     ap.add_argument("--stats-csv", required=True, help="the run's *_kernel_stats.csv")
     ap.add_argument("--bench-json", required=True, help="file holding the JSON line bench.py printed")
@@ -210,7 +212,7 @@ def stats_main(argv):
         # the headline's dispatches are the first refresh-form encode launches
         # of the run: warm-up steps, then the timed ones
         with open(args.trace_csv, newline="") as fh:
-            tr = [r for r in csv.DictReader(fh) if re.search(r"encode_kernel<\d+, \d+, true>", r["Kernel_Name"])]
+            tr = [r for r in csv.DictReader(fh) if REFRESH_KERNEL.search(r["Kernel_Name"])]
         tr.sort(key=lambda r: int(r["Dispatch_Id"]))
         nl = int(d["config"]["launches_per_step"])
         first = int(d["warmup"]) * nl
