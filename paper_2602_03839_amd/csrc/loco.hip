@@ -154,6 +154,14 @@ __device__ __forceinline__ uint32_t loco_select(const float (&a)[8], const float
 
 // Iterations from a tile's compute to its resolution and to its write-out.
 constexpr int kResolve = 4;
+// Tiles per ticket of the threshold form's launches of 2^15 tiles (252M elements)
+// and more: the 7B set took 17.2-17.4 ms with four, 17.6-17.8 with two, 2.0B in 60
+// tensors 4.53-4.68, 4.61-4.72, 400M 926-944 us, 944-955.  The gate forms, which
+// stream a third array, keep two: 0.5B set 1,499-1,507 us against 1,525-1,534, 7B
+// set 22.6 against 22.3-22.6 ms.
+constexpr uint32_t kThresholdChunk = 4;
+constexpr uint32_t kThresholdChunkTiles = 1u << 15;
+static_assert(kThresholdChunk <= (uint32_t)kResolve + 1, "a chunk is computed before its first tile resolves");
 constexpr int kDefer = kResolve + 1;
 constexpr int kWexclRing = wexcl_ring(kResolve);
 // Compaction segments, as in encode.hip: kSegCap selected entries per
@@ -224,8 +232,9 @@ __global__ __launch_bounds__((NW + 1) * 64) void loco_kernel(LocoParams p) {
 
   TileMap<TABLE, LocoParams>::fill(p, s_begin);
   if (wid == NW) {
-    scan_wave_loop<U, NW, kResolve, TABLE, LocoParams, AH>(p, s_begin, s_tk, s_wtot, s_wexcl, s_excl, s_tcnt,
-                                                     s_tovf, kSegCap, nullptr);
+    scan_wave_loop<U, NW, kResolve, TABLE, LocoParams, AH>(
+        p, s_begin, s_tk, s_wtot, s_wexcl, s_excl, s_tcnt, s_tovf, kSegCap, nullptr,
+        GM == 0 && p.ntiles >= kThresholdChunkTiles ? kThresholdChunk : kChunk);
     return;
   }
 

@@ -290,3 +290,34 @@ def test_loco_two_pass_batches_and_fallback(past, first):
                                       o_val[4:cnt].view(np.uint32))
         for r, desc in zip(o_res, descs):
             np.testing.assert_array_equal(hf32(desc.residual).view(np.uint32), r.view(np.uint32))
+
+
+@pytest.mark.parametrize("tiles,ragged", [((1 << 15) - 1, 0), (1 << 15, 3), ((1 << 15) + 2, 0)])
+def test_loco_tiles_per_ticket(tiles, ragged):
+    """The one-pass threshold form around the launch size where a ticket draws four
+    tiles instead of two: sums of zero but for 1M places that the host knows."""
+    n = tiles * GATE_TILE - ragged
+    rng = np.random.default_rng(tiles + ragged)
+    at = np.unique(np.concatenate([rng.integers(0, n, 900_000), rng.integers(n // 2, n // 2 + 300_000, 100_000),
+                                   np.arange(n - 200, n), np.arange(200)]))
+    d = rng.normal(0, 1.0, at.size).astype(np.float32)
+    e = rng.normal(0, 0.2, at.size).astype(np.float32)
+    a = d + e
+    sel = np.abs(a) >= np.float32(0.9)
+    where = torch.from_numpy(at).cuda()
+    d_d, e_d = (torch.zeros(n, dtype=torch.float32, device="cuda") for _ in range(2))
+    d_d[where], e_d[where] = dev(d), dev(e)
+    cap = int(sel.sum()) - 1000  # the last thousand are not sent
+    idx = torch.zeros(cap, dtype=torch.int32, device="cuda")
+    val = torch.zeros(cap, dtype=torch.float32, device="cuda")
+    count, ws = counter(0), pulse.workspace()
+    pulse.loco_sparsify(d_d, e_d, 0.9, idx, val, count, ws)
+    torch.cuda.synchronize()
+    assert read_count(count) == cap + 1000
+    np.testing.assert_array_equal(h32(idx), at[sel][:cap].astype(np.uint32))
+    np.testing.assert_array_equal(hf32(val).view(np.uint32), a[sel][:cap].view(np.uint32))
+    a[np.flatnonzero(sel)[:cap]] = 0.0
+    np.testing.assert_array_equal(hf32(e_d[where]).view(np.uint32), a.view(np.uint32))
+    e_d[where] = 0.0
+    assert int((e_d != 0).sum().item()) == 0
+    pulse.check_workspace(ws)
