@@ -2,8 +2,9 @@
 // App. H.5, Alg. 4): dst[idx[k] - index_base] = val[k].  A pure copy of bit
 // patterns into the receiver's BF16 copy in place; the destination is never
 // read, so the kernel streams the patch once and issues one 2-byte store per
-// entry (loads and stores non-temporal: nothing here is touched twice).  The entry range comes from device memory (encode's running count),
-// so the grid is fixed and strides over it.
+// entry (loads and stores non-temporal: nothing here is touched twice).  The entry
+// range comes from device memory (encode's running count), so the grid is sized by
+// the capacity (apply_blocks in launch.hpp) and strides over the entries.
 #include "device_common.hpp"
 #include "launch.hpp"
 
